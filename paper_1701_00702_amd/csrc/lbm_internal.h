@@ -26,23 +26,65 @@ enum Wall { W_LEFT = 0, W_RIGHT = 1, W_BOTTOM = 2, W_TOP = 3 };
 #define LBM_BAND_BYTES (256ll << 20)
 #endif
 
-// Constants of the PCM enthalpy field, kept in both arithmetic types (the
-// mixed storage form runs this field in FP64 and the others in FP32).
+// Constants of the PCM enthalpy field that only walls, diagnostics and the
+// initial state read, in both arithmetic types (the mixed storage form runs
+// this field's H, T_f and f_l in FP64 and the others in FP32).  c_pl, c_ps,
+// c_pm and rho_l are 1 in lattice units (Sec. IV parameter list).
 template <typename T>
 struct ThermalConst {
-    // enthalpy -> temperature, liquid fraction (Eqs. 38-39)
-    T H_fs, H_fl, T_fs, T_fl, inv_dH, dT_band, inv_cps, inv_cpl;
-    // equilibrium (Eq. 34 / Eq. B2)
-    T c_pl, c_fref, inv_phi;
-    // relaxation rates Theta (Eq. 31; D2Q5: the first five in the moment
-    // order of Eq. B1) folded with the factors g_k of the inverse transform
-    // (D2Q9: 1/|M_k|^2 of Eq. 13; D2Q5: 1, 1/2, 1/2, 1/4, 1/4 of Eq. B1):
-    // (1 - zeta_k) g_k and zeta_k g_k
-    T zA[9], zB[9];
+    T T_fs, T_fl, H_fs, H_fl, c_fref, inv_phi;
     // D2Q5: varpi and 1/c_sT^2 = 2/varpi (D2Q9: 1/c_s^2 = 3)
     T varpi, inv_cs2;
     // reference state and the isothermal wall values per wall
     T T_ref, H_ref, T_wall[4], H_wall[4];
+};
+
+// Relaxation rates of the flow field that Sec. III C fixes, in the moment
+// order of Eq. (13); moments 7 and 8 relax at s_v = 1 / tau_v.
+constexpr double kFlowRate[7] = {1.0, 1.1, 1.1, 1.0, 1.2, 1.0, 1.2};
+
+// The type the enthalpy field's moments are taken in: R in the mixed form
+// (RH wider than R), else RH.
+template <typename R, typename RH>
+struct MomentType {
+    using T = RH;
+};
+template <>
+struct MomentType<float, double> {
+    using T = float;
+};
+
+// The constants every node update reads, one of each distinct value (Sec.
+// III C relaxes moments 1 and 2, 3 and 5, 4 and 6, 7 and 8 in pairs, each
+// pair with one norm), products of constants formed once on the host with
+// the rounding the update would give them.  The FP32 step kernels load them
+// into scalar registers once per workgroup (node_const).
+template <typename R, typename RH>
+struct NodeConst {
+    using RG = typename MomentType<R, RH>::T;
+    // PCM enthalpy: H_ref and the equation of state, Eqs. (38)-(39)
+    RH H_ref, H_fs, H_fl, T_fs, T_fl, inv_dH, dT_band, Tf_ref, hv_f;
+    // flow: buoyancy, phi along the gravity axis (0 across it),
+    // porous drag, explicit velocity (Eqs. 3, 7, 23-25)
+    R gbeta, T0, px, py, inv_phi, drag_lin, drag_quad, l0, l0sq, l1;
+    // (1 - s_v) / 4, s_v / 4 and (1 - s_v / 2) / 4 of the flow's moments 7, 8
+    R fA7, fB7, fC7;
+    // interstitial exchange (Eqs. 36, 47): Sr_f = hv_f (T_m - T_f),
+    // Sr_m = hv_m (T_f - T_m); sr_ratio = hv_m / hv_f
+    R hv_m, sr_ratio;
+    // metal: reference temperature; (1 - eta_k) g_k and eta_k g_k with the
+    // factors g_k of the inverse transform (D2Q9: 1/|M_k|^2 of Eq. 13; D2Q5:
+    // 1, 1/2, 1/2, 1/4, 1/4 of Eq. B1); equilibrium factors of T_m (D2Q9:
+    // moments 1 and 2 of Eq. 45; D2Q5: moment 3 of Eq. B4)
+    R T_ref, mA0, mB0, mA1, mB1, mA3, mB3, mA4, mA7, me1, me2;
+    // enthalpy: (1 - zeta_k) g_k, zeta_k g_k; equilibrium factors of T_f
+    // (D2Q9: 2 and 3 c_f,ref; D2Q5: varpi c_f,ref)
+    RG zA1, zB1, zA3, zB3, zA4, zB4, zA7, ge1, ge2;
+    R w4;  // D2Q5: varpi / 4
+    RH cf_base;  // c_f,ref and c_m,ref of the split forms' bases
+    R cm_base;
+    R scale[3], inv_scale[3];  // of the 16-bit forms, as in CavityConst
+    int32_t bounce_back;  // solid phase: 0 volumetric (Eq. 20), 1 bounce-back (Sec. V B)
 };
 
 // Per-cavity constants in the arithmetic type R of the kernels.  One table
@@ -52,7 +94,7 @@ template <typename R>
 struct CavityConst {
     // geometry of the cavity inside the packed node index (the flat
     // per-node arrays of the interstitial source)
-    int32_t nx, ny, periodic, gaxis;
+    int32_t nx, ny, periodic, pitch;
     int64_t node0;  // first packed node of this cavity
     int64_t acc0;   // first wall-tally slot of this cavity (2*(nx+ny) slots)
     // Populations are stored by bands: rows [b * band_rows, (b + 1) *
@@ -64,33 +106,27 @@ struct CavityConst {
     // reads and writes close together in the address space; the row pitch
     // (nx rounded up to 64 nodes, the padding never read or written) starts
     // every row of every plane on a cache-line boundary.
-    int32_t band_rows, pitch;
     int64_t band_nodes, band_bytes, pop_off;
-    // materials
-    R phi, inv_phi, inv_cpm, c_pm, c_mref;
-    // rates folded with the factors of the inverse transform: flow (D2Q9,
-    // 1/|M_k|^2 of Eq. 13) (1 - s_k) / |M_k|^2, s_k / |M_k|^2 and the forcing
-    // factor (1 - s_k/2) / |M_k|^2; metal (1 - eta_k) g_k, eta_k g_k with the
-    // thermal lattice's g_k (D2Q5: 1, 1/2, 1/2, 1/4, 1/4 of Eq. B1)
-    R fA[9], fB[9], fC[9], mA[9], mB[9];
-    // flow: buoyancy, porous drag, explicit velocity (Eqs. 3, 7, 23-25)
-    R gbeta, T0, drag_lin, drag_quad, l0, l0sq, l1;
-    // interstitial exchange (Eqs. 36, 47): Sr_f = hv_f (T_m - T_f), Sr_m = hv_m (T_f - T_m)
-    R hv_f, hv_m, sr_ratio;  // sr_ratio = hv_m / hv_f
-    // reference temperature of the stored offsets; per wall (left, right,
-    // bottom, top): isothermal (1) or adiabatic (0) and its temperature
-    R T_ref, T_wall[4], varpi;
-    int32_t wall_iso[4];
-    int32_t bounce_back;  // solid phase: 0 volumetric (Eq. 20), 1 bounce-back (Sec. V B)
+    int32_t band_rows;
+    uint32_t band_recip;  // 2^32 / band_rows, rounded up
     // storage scale per field (populations are stored as (X - X_ref) * scale)
     R scale[3], inv_scale[3];
+    // the update's constants with the enthalpy field in R, and in FP64
+    NodeConst<R, R> nr;
+    NodeConst<R, double> nd;
+    // walls, diagnostics, initial state
+    R inv_phi, c_mref, T_ref, varpi;
+    // per wall (left, right, bottom, top): its temperature, and isothermal
+    // (1) or adiabatic (0)
+    R T_wall[4];
+    int32_t wall_iso[4];
     // PCM enthalpy field
     ThermalConst<float> tf;
     ThermalConst<double> td;
     // FP64 copies for the energy/mass tallies
     double we, wm;  // phi rho_l and (1 - phi) rho_m
     double g_ref[9], h_ref[9];
-    double T_init;
+    double T_init, hv_f;
 };
 
 // A tile is a run [k0, k1) of one cavity's nodes.  Row tiles (kind 0)

@@ -89,18 +89,21 @@ __device__ __forceinline__ void step_tile(const void *__restrict__ src, void *__
                                           double *__restrict__ acc, const CavityConst<R> *__restrict__ cav,
                                           const Tile &tl) {
     const CavityConst<R> &c = cav[tl.cav];
+    const NodeConst<R, RH> &n = node_const<Lay, RH>(c);
     const bool wall = tl.kind != TILE_INTERIOR;
-    int yb;
+    int yb, ye;
     if (wall) {
         yb = tl.k0 < c.nx ? 0 : c.ny - 3;
+        ye = yb + 2;
     } else {
         const int y0 = tl.k0 / c.pitch;
         yb = y0 >= 1 ? y0 - 1 : 0;
+        ye = (tl.k1 - 1) / c.pitch + 1;
     }
-    const BandOrigin org = band_origin(c, yb);
-    const int ba = yb / c.band_rows;
-    const void *sblk = band_block(c, src, ba);
-    void *dblk = band_block(c, dst, ba);
+    const int ba = band_of(c, yb);
+    const View v = view_of(c, ba, ye);
+    const Blocks sblk = blocks_of(band_block(c, src, ba));
+    const Blocks dblk = blocks_of(band_block(c, dst, ba));
 #pragma unroll
     for (int j = 0; j < NPT; ++j) {
         const int k = tl.k0 + (int)threadIdx.x + j * (int)blockDim.x;
@@ -116,7 +119,7 @@ __device__ __forceinline__ void step_tile(const void *__restrict__ src, void *__
             // along (each stored cache line then has one writer); lanes on
             // the row padding idle
             if (wall || x < c.nx)
-                step_node_at<Lay, R, RH, PULL>(c, sblk, dblk, sr_src, sr_dst, acc, x, y, org);
+                step_node_view<Lay, R, RH, PULL>(c, n, true, sblk, dblk, v, sr_src, sr_dst, acc, x, y);
         }
     }
 }
@@ -194,28 +197,34 @@ template <class Lay, typename R, typename RH, int TW, int TH, int NT, int K>
 __device__ __forceinline__ void stepk_advance(const void *__restrict__ src, void *__restrict__ dst,
                                               const R *__restrict__ sr_src, R *__restrict__ sr_dst,
                                               double *__restrict__ acc, const CavityConst<R> *__restrict__ cav,
-                                              const Tile2 &tl, void *lds_q, R *lds_sr, float *lds_b) {
+                                              const Tile2 &tl, void *lds_q, R *lds_sr, float *lds_b, double *lds_t) {
     using Sh = StepKShape<Lay, TW, TH, K>;
     const CavityConst<R> &c = cav[tl.cav];
+    const TileView<R> tv = tile_view<Sh>(c, tl);
+    const NodeConst<R, RH> &n = node_const<Lay, RH>(c);
+    using InTile = typename std::conditional<Sh::TILE_TALLY, TileTally<TW, TH, false, R>, CavityTally<R>>::type;
+    using InLast = typename std::conditional<Sh::TILE_TALLY, TileTally<TW, TH, true, R>, CavityTally<R>>::type;
+    const CavityTally<R> all{acc, c};
+    const InTile tally = tally_of<InTile>(all, lds_t, tv);
+    const InLast last = tally_of<InLast>(all, lds_t, tv);
     // NT >= NFIRST: each thread advances at most one node per update
     const int s = (int)threadIdx.x;
     if constexpr (Sh::STAGE_BASE) {
-        stepk_stage_bases<Lay, R, TW, TH, K, NT>(c, tl, src, lds_b, s);
+        stepk_stage_bases<Lay, R, TW, TH, K, NT>(tv, src, lds_b, s);
         __syncthreads();
     }
-    if (s < Sh::LW * (tl.h + 2 * Sh::RING))
-        stepk_first<Lay, R, RH, TW, TH, K>(c, tl, src, sr_src, acc, lds_q, lds_sr, lds_b, s);
+    if (s < Sh::LW * (tv.tl.h + 2 * Sh::RING))
+        stepk_first<Lay, R, RH, TW, TH, K>(tv, n, src, sr_src, tally, lds_q, lds_sr, lds_b, s);
     __syncthreads();
-#pragma unroll
-    for (int j = K - 2; j >= 1; --j) {
-        MidNode<R, RH> n;
-        const bool act = s < (TW + 2 * j) * (tl.h + 2 * j) &&
-                         stepk_mid_load<Lay, R, RH, TW, TH, K>(c, tl, j, lds_q, lds_sr, s, n);
+    if constexpr (K == 3) {
+        MidNode<R, RH> q;
+        const bool act = s < (TW + 2) * (tv.tl.h + 2) &&
+                         stepk_mid_load<Lay, R, RH, TW, TH, K, 1>(tv, n, lds_q, lds_sr, s, q);
         __syncthreads();  // every pull of this update is in registers
-        if (act) stepk_mid_store<Lay, R, RH, TW, TH, K>(c, tl, acc, lds_q, lds_sr, n);
+        if (act) stepk_mid_store<Lay, R, RH, TW, TH, K, 1>(tv, n, tally, lds_q, lds_sr, q);
         __syncthreads();
     }
-    if (s < TW * tl.h) stepk_last<Lay, R, RH, TW, TH, K>(c, tl, dst, sr_dst, acc, lds_q, lds_sr, s);
+    if (s < TW * tv.tl.h) stepk_last<Lay, R, RH, TW, TH, K>(tv, n, dst, sr_dst, last, lds_q, lds_sr, s);
 }
 
 // Waves per SIMD a multi-step kernel is built for: as many workgroups per
@@ -224,7 +233,7 @@ __device__ __forceinline__ void stepk_advance(const void *__restrict__ src, void
 template <class Lay, typename R, int TW, int TH, int NT, int K>
 constexpr int stepk_waves_per_eu() {
     using Sh = StepKShape<Lay, TW, TH, K>;
-    constexpr int lds = (int)(Sh::LDS_BYTES + Sh::NSLOT * sizeof(R) + Sh::BASE_BYTES);
+    constexpr int lds = (int)Sh::total_lds(Sh::TILE_TALLY);
     constexpr int by_lds = (160 * 1024) / lds;
     constexpr int by_waves = 32 / (NT / 64);
     constexpr int wgs = by_lds < by_waves ? by_lds : by_waves;
@@ -239,7 +248,7 @@ constexpr int stepk_waves_per_eu() {
 // CU); the 16-bit and D2Q9 FP32_H64 forms fit the bound only by spilling
 // and lose 5-24%.
 #ifndef LBM_WPE_MASK
-#define LBM_WPE_MASK ((1 << ST5_F32) | (1 << ST5_F32H))
+#define LBM_WPE_MASK ((1 << ST_F32) | (1 << ST5_F32) | (1 << ST5_F32H))
 #endif
 template <int ST, class Lay, typename R, int TW, int TH, int NT, int K>
 constexpr int stepk_wpe() {
@@ -258,15 +267,17 @@ __global__ __launch_bounds__(NT, WPE) void stepk_kernel(const void *__restrict__
     __shared__ __align__(16) unsigned char lds_q[Sh::LDS_BYTES];
     __shared__ R lds_sr[Sh::NSLOT];
     __shared__ float lds_b[Sh::STAGE_BASE ? 3 * Sh::NBASE : 1];
+    __shared__ double lds_t[Sh::TILE_TALLY ? 4 * (TW + TH) : 1];
     const int b = remap_block(blockIdx.x, gridDim.x, xcd_remap);
     if (!LOOP) {
         if (b < ntiles)
             stepk_advance<Lay, R, RH, TW, TH, NT, K>(src, dst, sr_src, sr_dst, acc, cav, tiles[b], lds_q, lds_sr,
-                                                     lds_b);
+                                                     lds_b, lds_t);
         return;
     }
     for (int t = b; t < ntiles; t += gridDim.x) {
-        stepk_advance<Lay, R, RH, TW, TH, NT, K>(src, dst, sr_src, sr_dst, acc, cav, tiles[t], lds_q, lds_sr, lds_b);
+        stepk_advance<Lay, R, RH, TW, TH, NT, K>(src, dst, sr_src, sr_dst, acc, cav, tiles[t], lds_q, lds_sr, lds_b,
+                                                 lds_t);
         __syncthreads();  // the next tile reuses the LDS
     }
 }

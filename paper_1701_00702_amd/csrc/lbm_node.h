@@ -106,6 +106,64 @@ LBM_HD const ThermalConst<RH> &thermal(const CavityConst<R> &c) {
     return ThermalPick<RH>::get(c);
 }
 
+// The constants of the node update with the enthalpy field in RH.
+template <typename RH, typename R>
+LBM_HD const NodeConst<R, RH> &node_const_of(const CavityConst<R> &c) {
+    if constexpr (std::is_same<R, RH>::value) return c.nr;
+    else return c.nd;
+}
+
+// A workgroup-uniform value kept in a scalar register from here on: the
+// empty asm keeps the compiler from loading it again at each use.
+template <typename T>
+LBM_HD void resident(T &v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    asm volatile("" : "+s"(v));
+#else
+    (void)v;
+#endif
+}
+
+// The constants of the node update for the step kernels.  With FP32
+// arithmetic they are loaded once per workgroup and stay in scalar
+// registers; loaded at each use, every update waited on chains of scalar
+// loads (they return out of order, so each wait is for all of them and for
+// the LDS reads too).  Together with one vector offset for all pulls and the
+// scalar branch past the wall code this took the three-step FP32_H64 kernel
+// (8192^2) from 1125 VALU, 558 scalar and 98 scalar-load instructions per
+// wave to 961, 302 and 24.  FP64 constants would take twice the registers
+// there are (700 spills to vector lanes, 13% slower) and stay in memory.
+template <class Lay, typename RH>
+LBM_HD const NodeConst<double, RH> &node_const(const CavityConst<double> &c) {
+    return node_const_of<RH>(c);
+}
+template <class Lay, typename RH>
+LBM_HD NodeConst<float, RH> node_const(const CavityConst<float> &c) {
+    NodeConst<float, RH> n = node_const_of<RH>(c);
+#if defined(__HIP_DEVICE_COMPILE__)
+    {
+        constexpr bool q9 = Lay::QT == 9;
+        resident(n.H_ref), resident(n.H_fs), resident(n.H_fl), resident(n.T_fs), resident(n.T_fl);
+        resident(n.inv_dH), resident(n.dT_band), resident(n.Tf_ref), resident(n.hv_f);
+        resident(n.gbeta), resident(n.T0), resident(n.px), resident(n.py);
+        resident(n.inv_phi), resident(n.drag_lin), resident(n.drag_quad), resident(n.l0), resident(n.l0sq);
+        resident(n.l1), resident(n.fA7), resident(n.fB7), resident(n.fC7), resident(n.hv_m), resident(n.sr_ratio);
+        resident(n.T_ref), resident(n.mA0), resident(n.mB0), resident(n.mA1), resident(n.mA3), resident(n.me1);
+        resident(n.zA1), resident(n.zB1), resident(n.zA3), resident(n.zB3), resident(n.ge1);
+        resident(n.bounce_back);
+        if constexpr (q9) {
+            resident(n.mB1), resident(n.mA4), resident(n.mA7), resident(n.me2);
+            resident(n.zA4), resident(n.zB4), resident(n.zA7), resident(n.ge2);
+        } else {
+            resident(n.mB3), resident(n.w4);
+        }
+        if constexpr (Lay::SCALED)
+            for (int f = 0; f < 3; ++f) resident(n.scale[f]), resident(n.inv_scale[f]);
+    }
+#endif
+    return n;
+}
+
 // ---------------------------------------------------------------------------
 // Streaming loads/stores and element codecs.  Every population is read and
 // written once per step; whether the GPU accesses carry the non-temporal
@@ -137,13 +195,9 @@ LBM_HD void st_stream(T *p, T v) {
 // A node's place in a population plane of a band block (the banded layout
 // of the state buffers is described with CavityConst).  NodeRef: the node's
 // offset rel within its band's plane plus the byte distance jump of its
-// band's block from the block the plane pointer points into, both 32-bit;
-// the step kernels use it with the same block for the whole workgroup (the
-// tile's first band), so the address of each plane stays in scalar
-// registers (the empty asm keeps the compiler from regrouping the sum into
-// a per-lane 64-bit base plus plane offsets) and an access is that scalar
-// base plus one 32-bit vector offset.  FarRef: the same in 64 bits, for an
-// access anywhere in a cavity from its first band's block.
+// band's block from the block of the workgroup's first band, both 32-bit.
+// FarRef: the same in 64 bits, for an access anywhere in a cavity from its
+// first band's block.
 struct NodeRef {
     uint32_t rel, jump;
 };
@@ -156,33 +210,59 @@ template <typename T>
 LBM_HD T *at(T *plane, FarRef r) {
     return (T *)((ByteOf<T> *)(plane + r.rel) + r.jump);
 }
-template <typename T>
-LBM_HD T *at(T *plane, NodeRef r) {
+
+// The blocks a workgroup reads or writes, from the block of its first band
+// on.  An access is at uniform + lane + imm bytes from there: on the GPU a
+// buffer access, which takes the three as a scalar register, a vector
+// register and a constant, so that the planes of a node differ in the scalar
+// alone and one vector offset serves them all.  Offsets stay below 2^31 (two
+// consecutive bands).
 #if defined(__HIP_DEVICE_COMPILE__)
-    __attribute__((address_space(1))) T *gp = (__attribute__((address_space(1))) T *)plane;  // global memory
-    asm("" : "+s"(gp));
-    plane = (T *)gp;
-#endif
-    return (T *)((ByteOf<T> *)plane + (r.rel * (uint32_t)sizeof(T) + r.jump));
+using Blocks = __amdgpu_buffer_rsrc_t;
+LBM_HD Blocks blocks_of(const void *first) {
+    return __builtin_amdgcn_make_buffer_rsrc((void *)first, 0, 0x7fffffff, 0x00020000);
 }
-// The address of a store of v to plane p (of stride elements) from base:
-// as at(), with the plane's scalar base formed from a copy of the stride
-// that depends on v.  The bases are then computed next to the stores, not
-// shared with the loads' and held in scalar registers across the update.
-template <typename T, typename V>
-LBM_HD T *at_store(T *base, int p, int64_t stride, FarRef r, V v) {
-    (void)v;
-    return at(base + (int64_t)p * stride, r);
-}
-template <typename T, typename V>
-LBM_HD T *at_store(T *base, int p, int64_t stride, NodeRef r, V v) {
-#if defined(__HIP_DEVICE_COMPILE__)
-    asm("" : "+s"(stride) : "v"(v));
 #else
-    (void)v;
+using Blocks = char *;
+LBM_HD Blocks blocks_of(const void *first) { return (char *)first; }
 #endif
-    return at(base + (int64_t)p * stride, r);
+template <typename T>
+LBM_HD T ld_block(Blocks b, uint32_t uniform, uint32_t lane, uint32_t imm) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int aux = LBM_NT_LOADS ? 2 : 0;
+    if constexpr (sizeof(T) == 8)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b64(b, lane + imm, uniform, aux));
+    else if constexpr (sizeof(T) == 4)
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b32(b, lane + imm, uniform, aux));
+    else
+        return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(b, lane + imm, uniform, aux));
+#else
+    return *(const T *)(b + (uint32_t)(uniform + lane + imm));
+#endif
 }
+template <typename T>
+LBM_HD void st_block(Blocks b, uint32_t uniform, uint32_t lane, T v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    constexpr int aux = LBM_NT_STORES ? 2 : 0;
+    if constexpr (sizeof(T) == 8) {
+        using V2 = unsigned int __attribute__((ext_vector_type(2)));
+        __builtin_amdgcn_raw_buffer_store_b64(__builtin_bit_cast(V2, v), b, lane, uniform, aux);
+    } else if constexpr (sizeof(T) == 4) {
+        __builtin_amdgcn_raw_buffer_store_b32(__builtin_bit_cast(unsigned int, v), b, lane, uniform, aux);
+    } else {
+        __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), b, lane, uniform, aux);
+    }
+#else
+    *(T *)(b + (uint32_t)(uniform + lane)) = v;
+#endif
+}
+
+// One pull of a node: the element at node offset rel + dx of a plane, shift
+// nodes (uniform) from it, in the block jump bytes on.
+struct Pull {
+    int32_t shift;
+    uint32_t rel, dx, jump;
+};
 
 struct E64 {
     using T = double;
@@ -213,36 +293,55 @@ struct EB16 {  // bfloat16, round to nearest even (finite values)
 // Storage layouts.  load<V>() returns the offset q_i of field f (0 flow,
 // 1 enthalpy, 2 metal), direction i, at packed node k, in type V; store()
 // writes the offsets of one field at node k (nine for the flow, QT for the
-// thermal fields).  beta is the per-node base value the split layout stores
-// (unused elsewhere).
+// thermal fields); pull() and put() are the same within a workgroup's
+// blocks.  beta is the per-node base value the split layout stores (unused
+// elsewhere).  c holds the scales of the 16-bit forms.
 // ---------------------------------------------------------------------------
 
 // 9 + 2 QT planes of one element type, [f0..f8, g0..g(QT-1), h0..h(QT-1)];
 // 16-bit forms carry a power-of-two scale.
-template <class E, bool SCALED, int QT_ = 9>
+template <class E, bool SCALED_, int QT_ = 9>
 struct Plain {
     using T = typename E::T;
     using C = decltype(E::dec(T()));  // element arithmetic type of the codec
     static constexpr int QT = QT_;
+    static constexpr bool SCALED = SCALED_;
     static constexpr int bytes_per_node = (9 + 2 * QT) * (int)sizeof(T);
-    LBM_HD static int plane(int f, int i) { return f == 0 ? i : 9 + (f - 1) * QT + i; }
-    template <typename V, typename R, typename K>
-    LBM_HD static V load(const void *base, int64_t stride, int f, int i, K k, const CavityConst<R> &c) {
-        const T *p = at((const T *)base + (int64_t)plane(f, i) * stride, k);
-        const V v = (V)E::dec(ld_stream(p));
+    LBM_HD static constexpr int plane(int f, int i) { return f == 0 ? i : 9 + (f - 1) * QT + i; }
+    template <typename V, class S>
+    LBM_HD static V dec(T e, int f, const S &c) {
+        const V v = (V)E::dec(e);
         return SCALED ? v * (V)c.inv_scale[f] : v;
     }
-    template <typename V, typename R, typename K>
-    LBM_HD static void store(void *base, int64_t stride, int f, const V q[9], V beta, K k,
-                             const CavityConst<R> &c) {
+    template <typename V, class S>
+    LBM_HD static T enc(V q, int f, const S &c) {
+        return E::enc((C)(SCALED ? q * (V)c.scale[f] : q));
+    }
+    template <typename V, class S, typename K>
+    LBM_HD static V load(const void *base, int64_t stride, int f, int i, K k, const S &c) {
+        return dec<V>(ld_stream(at((const T *)base + (int64_t)plane(f, i) * stride, k)), f, c);
+    }
+    template <typename V, class S, typename K>
+    LBM_HD static void store(void *base, int64_t stride, int f, const V q[9], V beta, K k, const S &c) {
         (void)beta;
         const int n = f == 0 ? 9 : QT;
 #pragma unroll
         for (int i = 0; i < 9; ++i)
-            if (i < n) {
-                const T e = E::enc((C)(SCALED ? q[i] * (V)c.scale[f] : q[i]));
-                st_stream(at_store((T *)base, plane(f, i), stride, k, e), e);
-            }
+            if (i < n) st_stream(at((T *)base + (int64_t)plane(f, i) * stride, k), enc(q[i], f, c));
+    }
+    template <typename V, class S>
+    LBM_HD static V pull(Blocks b, uint32_t stride, int f, int i, Pull p, const S &c) {
+        return dec<V>(ld_block<T>(b, (plane(f, i) * stride + p.shift) * sizeof(T), p.rel * sizeof(T) + p.jump,
+                                  p.dx * sizeof(T)),
+                      f, c);
+    }
+    template <typename V, class S>
+    LBM_HD static void put(Blocks b, uint32_t stride, int f, const V q[9], V beta, NodeRef k, const S &c) {
+        (void)beta;
+        const int n = f == 0 ? 9 : QT;
+#pragma unroll
+        for (int i = 0; i < 9; ++i)
+            if (i < n) st_block<T>(b, plane(f, i) * stride * sizeof(T), k.rel * sizeof(T) + k.jump, enc(q[i], f, c));
     }
 };
 
@@ -252,31 +351,45 @@ struct Plain {
 template <int QT_ = 9>
 struct PlainH64 {
     static constexpr int QT = QT_;
+    static constexpr bool SCALED = false;
     static constexpr int NF32 = 8 + 2 * QT;
     static constexpr int bytes_per_node = NF32 * 4 + 8;
-    LBM_HD static int plane(int f, int i) { return f == 0 ? i : (f == 1 ? 8 + i : 8 + QT + i); }
-    template <typename V, typename R, typename K>
-    LBM_HD static V load(const void *base, int64_t stride, int f, int i, K k, const CavityConst<R> &c) {
+    LBM_HD static constexpr int plane(int f, int i) { return f == 0 ? i : (f == 1 ? 8 + i : 8 + QT + i); }
+    template <typename V, class S, typename K>
+    LBM_HD static V load(const void *base, int64_t stride, int f, int i, K k, const S &c) {
         (void)c;
         if (f == 1 && i == 0) return (V)ld_stream(at((const double *)((const float *)base + NF32 * stride), k));
         return (V)ld_stream(at((const float *)base + (int64_t)plane(f, i) * stride, k));
     }
-    template <typename V, typename R, typename K>
-    LBM_HD static void store(void *base, int64_t stride, int f, const V q[9], V beta, K k,
-                             const CavityConst<R> &c) {
+    template <typename V, class S, typename K>
+    LBM_HD static void store(void *base, int64_t stride, int f, const V q[9], V beta, K k, const S &c) {
         (void)beta;
         (void)c;
         const int n = f == 0 ? 9 : QT;
 #pragma unroll
         for (int i = 0; i < 9; ++i) {
             if (i >= n) continue;
-            if (f == 1 && i == 0) {
-                const double e = (double)q[0];
-                st_stream(at_store((double *)((float *)base + NF32 * stride), 0, stride, k, e), e);
-            } else {
-                const float e = (float)q[i];
-                st_stream(at_store((float *)base, plane(f, i), stride, k, e), e);
-            }
+            if (f == 1 && i == 0) st_stream(at((double *)((float *)base + NF32 * stride), k), (double)q[0]);
+            else st_stream(at((float *)base + (int64_t)plane(f, i) * stride, k), (float)q[i]);
+        }
+    }
+    template <typename V, class S>
+    LBM_HD static V pull(Blocks b, uint32_t stride, int f, int i, Pull p, const S &c) {
+        (void)c;
+        if (f == 1 && i == 0)
+            return (V)ld_block<double>(b, NF32 * stride * 4 + p.shift * 8, p.rel * 8 + p.jump, p.dx * 8);
+        return (V)ld_block<float>(b, (plane(f, i) * stride + p.shift) * 4, p.rel * 4 + p.jump, p.dx * 4);
+    }
+    template <typename V, class S>
+    LBM_HD static void put(Blocks b, uint32_t stride, int f, const V q[9], V beta, NodeRef k, const S &c) {
+        (void)beta;
+        (void)c;
+        const int n = f == 0 ? 9 : QT;
+#pragma unroll
+        for (int i = 0; i < 9; ++i) {
+            if (i >= n) continue;
+            if (f == 1 && i == 0) st_block<double>(b, NF32 * stride * 4, k.rel * 8 + k.jump, (double)q[0]);
+            else st_block<float>(b, plane(f, i) * stride * 4, k.rel * 4 + k.jump, (float)q[i]);
         }
     }
 };
@@ -320,38 +433,54 @@ LBM_HD float split_rem(int i, V q, V b, V scale) {
 template <class ER>
 struct SplitT {
     static constexpr int QT = 9;
+    static constexpr bool SCALED = true;
     static constexpr int bytes_per_node = 6 * 4 + 24 * 2;
-    // the stored base b of field f at node k
-    template <typename K>
-    LBM_HD static float load_base(const void *base, int64_t stride, int f, K k) {
-        return ld_stream(at((const float *)base + (int64_t)(2 * f + 1) * stride, k));
-    }
-    // moving population i (>= 1) of field f at node k, given that node's base
-    template <typename V, typename R, typename K>
-    LBM_HD static V load_moving(const void *base, int64_t stride, int f, int i, K k, V b, const CavityConst<R> &c) {
-        const uint16_t *Qp = (const uint16_t *)((const float *)base + 6 * stride);
+    template <typename V, class S, typename K>
+    LBM_HD static V load(const void *base, int64_t stride, int f, int i, K k, const S &c) {
+        const float *P = (const float *)base;
+        if (i == 0) return (V)ld_stream(at(P + (int64_t)(2 * f) * stride, k));
+        const V b = (V)ld_stream(at(P + (int64_t)(2 * f + 1) * stride, k));
+        const uint16_t *Qp = (const uint16_t *)(P + 6 * stride);
         const V r = (V)ER::dec(ld_stream(at(Qp + (int64_t)(8 * f + i - 1) * stride, k)));
         return split_dec<V>(i, b, r, (V)c.inv_scale[f]);
     }
-    template <typename V, typename R, typename K>
-    LBM_HD static V load(const void *base, int64_t stride, int f, int i, K k, const CavityConst<R> &c) {
-        const float *P = (const float *)base;
-        if (i == 0) return (V)ld_stream(at(P + (int64_t)(2 * f) * stride, k));
-        return load_moving<V>(base, stride, f, i, k, (V)load_base(base, stride, f, k), c);
-    }
-    template <typename V, typename R, typename K>
-    LBM_HD static void store(void *base, int64_t stride, int f, const V q[9], V beta, K k,
-                             const CavityConst<R> &c) {
+    template <typename V, class S, typename K>
+    LBM_HD static void store(void *base, int64_t stride, int f, const V q[9], V beta, K k, const S &c) {
         float *P = (float *)base;
-        const float e0 = (float)q[0], eb = (float)split_base<V>(beta);
-        st_stream(at_store(P, 2 * f, stride, k, e0), e0);
-        st_stream(at_store(P, 2 * f + 1, stride, k, eb), eb);
+        const float eb = (float)split_base<V>(beta);
+        st_stream(at(P + (int64_t)(2 * f) * stride, k), (float)q[0]);
+        st_stream(at(P + (int64_t)(2 * f + 1) * stride, k), eb);
         uint16_t *Qp = (uint16_t *)(P + 6 * stride);
 #pragma unroll
-        for (int i = 1; i < 9; ++i) {
-            const uint16_t e = ER::enc(split_rem<V>(i, q[i], (V)eb, (V)c.scale[f]));
-            st_stream(at_store(Qp, 8 * f + i - 1, stride, k, e), e);
-        }
+        for (int i = 1; i < 9; ++i)
+            st_stream(at(Qp + (int64_t)(8 * f + i - 1) * stride, k),
+                      ER::enc(split_rem<V>(i, q[i], (V)eb, (V)c.scale[f])));
+    }
+    // the stored base of field f of the node pulled from
+    LBM_HD static float pull_base(Blocks b, uint32_t stride, int f, Pull p) {
+        return ld_block<float>(b, ((2 * f + 1) * stride + p.shift) * 4, p.rel * 4 + p.jump, p.dx * 4);
+    }
+    // moving population i (>= 1) of field f, given that node's base
+    template <typename V, class S>
+    LBM_HD static V pull_moving(Blocks b, uint32_t stride, int f, int i, Pull p, V base, const S &c) {
+        const V r = (V)ER::dec(ld_block<uint16_t>(b, 24 * stride + ((8 * f + i - 1) * stride + p.shift) * 2,
+                                                  p.rel * 2 + p.jump, p.dx * 2));
+        return split_dec<V>(i, base, r, (V)c.inv_scale[f]);
+    }
+    template <typename V, class S>
+    LBM_HD static V pull(Blocks b, uint32_t stride, int f, int i, Pull p, const S &c) {
+        if (i == 0) return (V)ld_block<float>(b, (2 * f * stride + p.shift) * 4, p.rel * 4 + p.jump, p.dx * 4);
+        return pull_moving<V>(b, stride, f, i, p, (V)pull_base(b, stride, f, p), c);
+    }
+    template <typename V, class S>
+    LBM_HD static void put(Blocks b, uint32_t stride, int f, const V q[9], V beta, NodeRef k, const S &c) {
+        const float eb = (float)split_base<V>(beta);
+        st_block<float>(b, 2 * f * stride * 4, k.rel * 4 + k.jump, (float)q[0]);
+        st_block<float>(b, (2 * f + 1) * stride * 4, k.rel * 4 + k.jump, eb);
+#pragma unroll
+        for (int i = 1; i < 9; ++i)
+            st_block<uint16_t>(b, (24 + (8 * f + i - 1) * 2) * stride, k.rel * 2 + k.jump,
+                               ER::enc(split_rem<V>(i, q[i], (V)eb, (V)c.scale[f])));
     }
 };
 using Split16 = SplitT<E16>;
@@ -502,22 +631,22 @@ struct Thermo {  // PCM enthalpy field, Eqs. (37)-(39)
     RH dH, H, Tf, fl;
 };
 template <typename R>
-struct Macro {  // everything the flow and metal collisions need
+struct Macro {  // everything the flow and metal collisions need; G is phi times the buoyancy
     R Tf, fl, dTm, Tm, drho, rho, ux, uy, umag, Gx, Gy;
 };
 
-// Eqs. (38)-(39), branches in the order the paper lists them.
-template <typename RH>
-LBM_HD void eos(const ThermalConst<RH> &t, RH H, RH &T, RH &fl) {
-    if (H <= t.H_fs) {
-        T = H * t.inv_cps;
+// Eqs. (38)-(39), branches in the order the paper lists them (c_ps = c_pl = 1).
+template <typename RH, class N>
+LBM_HD void eos(const N &n, RH H, RH &T, RH &fl) {
+    if (H <= n.H_fs) {
+        T = H;
         fl = RH(0);
-    } else if (H >= t.H_fl) {
-        T = t.T_fl + (H - t.H_fl) * t.inv_cpl;
+    } else if (H >= n.H_fl) {
+        T = n.T_fl + (H - n.H_fl);
         fl = RH(1);
     } else {
-        fl = (H - t.H_fs) * t.inv_dH;
-        T = t.T_fs + fl * t.dT_band;
+        fl = (H - n.H_fs) * n.inv_dH;
+        T = n.T_fs + fl * n.dT_band;
     }
 }
 
@@ -538,7 +667,7 @@ LBM_HD void eos(const ThermalConst<RH> &t, RH H, RH &T, RH &fl) {
 template <typename R, typename RH>
 struct Moments {
     static constexpr bool SPLIT = !std::is_same<R, RH>::value;
-    using RG = typename std::conditional<SPLIT, R, RH>::type;
+    using RG = typename MomentType<R, RH>::T;
     R f[9], h[9];
     RG g[9];
     RH rest;  // SPLIT: the rest enthalpy population q_0
@@ -566,22 +695,21 @@ LBM_HD void field_moments(const R qf[9], const RH qg[9], const R qh[9], Moments<
 // are f_l d + (1 - f_l) delta rho (1, -2, 1, 0, ..., 0), M w having the
 // moments (1, -2, 1, 0, ..., 0)).  The bounce-back alternative of Sec. V B
 // keeps f+ unblended.
-template <int QT, typename R, typename RH>
-LBM_HD void macros_of(const CavityConst<R> &c, Moments<R, RH> &mo, Thermo<RH> &th, Macro<R> &m) {
-    const ThermalConst<RH> &t = thermal<RH>(c);
+template <typename R, typename RH>
+LBM_HD void macros_of(const NodeConst<R, RH> &n, Moments<R, RH> &mo, Thermo<RH> &th, Macro<R> &m) {
     // Eq. (37), Eqs. (38)-(39)
     th.dH = Moments<R, RH>::SPLIT ? (RH)mo.g[0] + mo.rest : (RH)mo.g[0];
-    th.H = t.H_ref + th.dH;
-    eos(t, th.H, th.Tf, th.fl);
+    th.H = n.H_ref + th.dH;
+    eos(n, th.H, th.Tf, th.fl);
     m.Tf = (R)th.Tf;
     m.fl = (R)th.fl;
-    // Eq. (48)
-    m.dTm = mo.h[0] * c.inv_cpm;
-    m.Tm = c.T_ref + m.dTm;
+    // Eq. (48), c_pm = 1
+    m.dTm = mo.h[0];
+    m.Tm = n.T_ref + m.dTm;
     // Eq. (21)
     m.drho = mo.f[0];
     m.rho = R(1) + m.drho;
-    if (!c.bounce_back) {
+    if (!n.bounce_back) {
         const R sol = (R(1) - m.fl) * m.drho;
         mo.f[0] = m.drho;
         mo.f[1] = fma_of(m.fl, mo.f[1], R(-2) * sol);
@@ -590,22 +718,22 @@ LBM_HD void macros_of(const CavityConst<R> &c, Moments<R, RH> &mo, Thermo<RH> &t
         for (int k = 3; k < 9; ++k) mo.f[k] = m.fl * mo.f[k];
     }
     // Eq. (7): buoyancy along +axis (gravity along -axis).
-    const R G = c.gbeta * (m.Tf - c.T0) * m.fl;
-    m.Gx = c.gaxis == 0 ? G : R(0);
-    m.Gy = c.gaxis == 1 ? G : R(0);
+    const R G = n.gbeta * (m.Tf - n.T0) * m.fl;
+    m.Gx = n.px * G;
+    m.Gy = n.py * G;
     // Eq. (24) (j = the blended moments 3 and 5), then the explicit root
     // Eq. (23) with Eq. (25).
     const R jx = mo.f[3], jy = mo.f[5];
     const R inv_rho = rcp_of(m.rho);
-    const R vx = fma_of(jx, inv_rho, R(0.5) * c.phi * m.Gx);
-    const R vy = fma_of(jy, inv_rho, R(0.5) * c.phi * m.Gy);
+    const R vx = fma_of(jx, inv_rho, R(0.5) * m.Gx);
+    const R vy = fma_of(jy, inv_rho, R(0.5) * m.Gy);
     const R vmag = sqrt_of(fma_of(vx, vx, vy * vy));
-    const R inv_den = rcp_of(c.l0 + sqrt_of(fma_of(c.l1, vmag, c.l0sq)));
+    const R inv_den = rcp_of(n.l0 + sqrt_of(fma_of(n.l1, vmag, n.l0sq)));
     m.ux = vx * inv_den;
     m.uy = vy * inv_den;
     m.umag = vmag * inv_den;  // |u| of Eq. (3)
     // bounce-back: below the interface value f_l = 0.5 a node is solid, at rest
-    if (c.bounce_back && m.fl < R(0.5)) {
+    if (n.bounce_back && m.fl < R(0.5)) {
         m.ux = R(0);
         m.uy = R(0);
         m.umag = R(0);
@@ -614,20 +742,36 @@ LBM_HD void macros_of(const CavityConst<R> &c, Moments<R, RH> &mo, Thermo<RH> &t
 
 // The same from populations (wall partners, diagnostics).
 template <int QT, typename R, typename RH>
-LBM_HD void macros(const CavityConst<R> &c, const R qf[9], const RH qg[9], const R qh[9], Thermo<RH> &th,
+LBM_HD void macros(const NodeConst<R, RH> &n, const R qf[9], const RH qg[9], const R qh[9], Thermo<RH> &th,
                    Macro<R> &m) {
     Moments<R, RH> mo;
     field_moments<QT>(qf, qg, qh, mo);
-    macros_of<QT>(c, mo, th, m);
+    macros_of(n, mo, th, m);
+}
+
+// (1 - s_k) / |M_k|^2, s_k / |M_k|^2 and the forcing factor (1 - s_k / 2) /
+// |M_k|^2 of the flow's moments with fixed rates, rounded as a table built
+// on the host would be.
+template <typename R>
+__host__ __device__ constexpr R flow_keep(int k) {
+    return (R)((1.0 - kFlowRate[k]) * moment_norm<double>(k));
+}
+template <typename R>
+__host__ __device__ constexpr R flow_relax(int k) {
+    return (R)(kFlowRate[k] * moment_norm<double>(k));
+}
+template <typename R>
+__host__ __device__ constexpr R flow_force(int k) {
+    return (R)((1.0 - 0.5 * kFlowRate[k]) * moment_norm<double>(k));
 }
 
 // Flow collision, Eqs. (14), (16)-(19), from the blended moments d (into q);
 // with the bounce-back alternative (Sec. V B) a solid node instead returns
 // every population of q along the opposite link (the reference w_i rho_0 is
 // symmetric, so the offsets swap the same way).
-template <typename R>
-LBM_HD void collide_flow(const CavityConst<R> &c, const Macro<R> &m, R d[9], R q[9]) {
-    if (c.bounce_back && m.fl < R(0.5)) {
+template <typename R, typename RH>
+LBM_HD void collide_flow(const NodeConst<R, RH> &n, const Macro<R> &m, R d[9], R q[9]) {
+    if (n.bounce_back && m.fl < R(0.5)) {
         R t;
         t = q[1]; q[1] = q[3]; q[3] = t;
         t = q[2]; q[2] = q[4]; q[4] = t;
@@ -638,13 +782,14 @@ LBM_HD void collide_flow(const CavityConst<R> &c, const Macro<R> &m, R d[9], R q
     const R ux = m.ux, uy = m.uy, rho = m.rho;
     const R uu = fma_of(ux, ux, uy * uy);
     // Eq. (3): F = -(drag_lin + drag_quad |u|) u + phi G
-    const R drag = fma_of(c.drag_quad, m.umag, c.drag_lin);
-    const R Fx = fma_of(-drag, ux, c.phi * m.Gx);
-    const R Fy = fma_of(-drag, uy, c.phi * m.Gy);
-    const R rip = rho * c.inv_phi;
+    const R drag = fma_of(n.drag_quad, m.umag, n.drag_lin);
+    const R Fx = fma_of(-drag, ux, m.Gx);
+    const R Fy = fma_of(-drag, uy, m.Gy);
+    const R rip = rho * n.inv_phi;
     R eq[9], S[9];
-    eq[1] = -R(2) * m.drho + R(3) * rip * uu;
-    eq[2] = m.drho - R(3) * rip * uu;
+    const R ru = R(3) * rip * uu;
+    eq[1] = fma_of(R(-2), m.drho, ru);
+    eq[2] = m.drho - ru;
     eq[3] = rho * ux;
     eq[4] = -eq[3];
     eq[5] = rho * uy;
@@ -661,10 +806,17 @@ LBM_HD void collide_flow(const CavityConst<R> &c, const Macro<R> &m, R d[9], R q
     S[7] = R(2) * rip * (ux * Fx - uy * Fy);
     S[8] = rip * (ux * Fy + uy * Fx);
     // scaled post-collision moments: ((1 - s) d + s eq + (1 - s/2) S) / |M_k|^2
+    // (s_3 = s_5 = 1: no part of d stays)
     R a[9];
     a[0] = m.drho * moment_norm<R>(0);
 #pragma unroll
-    for (int k = 1; k < 9; ++k) a[k] = fma_of(c.fC[k], S[k], fma_of(c.fB[k], eq[k], c.fA[k] * d[k]));
+    for (int k = 1; k < 7; ++k) {
+        const R relaxed = k == 3 || k == 5 ? flow_relax<R>(k) * eq[k]
+                                           : fma_of(flow_relax<R>(k), eq[k], flow_keep<R>(k) * d[k]);
+        a[k] = fma_of(flow_force<R>(k), S[k], relaxed);
+    }
+#pragma unroll
+    for (int k = 7; k < 9; ++k) a[k] = fma_of(n.fC7, S[k], fma_of(n.fB7, eq[k], n.fA7 * d[k]));
     from_scaled(a, q);
 }
 
@@ -681,15 +833,14 @@ LBM_HD void pcm_out(const RG qs[9], RH rest, RH q[9]) {
 // of the moving populations alone in the split form, where rest is q_0; d_0
 // is then delta H - q_0, and the equilibrium of Eq. 34 is taken at it).
 template <typename R, typename RH, typename RG>
-LBM_HD void collide_pcm(const CavityConst<R> &c, const Thermo<RH> &th, const Macro<R> &m, RH S_pcm,
-                        RG d[9], RH rest, RH q[9]) {
-    const ThermalConst<RG> &t = thermal<RG>(c);
-    const RG dT = (RG)(th.Tf - thermal<RH>(c).T_ref);
-    const RG jT = t.c_pl * (RG)th.Tf * t.inv_phi;
+LBM_HD void collide_pcm(const NodeConst<R, RH> &n, const Thermo<RH> &th, const Macro<R> &m, RH S_pcm, RG d[9],
+                        RH rest, RH q[9]) {
+    const RG dT = (RG)(th.Tf - n.Tf_ref);
+    const RG jT = (RG)th.Tf * (RG)n.inv_phi;  // c_pl = 1
     const RG S = (RG)S_pcm;
     RG eq[7];  // eq_0 = d_0; eq_7 = eq_8 = 0
-    eq[1] = -RG(4) * d[0] + RG(2) * t.c_fref * dT;
-    eq[2] = RG(4) * d[0] - RG(3) * t.c_fref * dT;
+    eq[1] = fma_of(RG(-4), d[0], n.ge1 * dT);
+    eq[2] = fma_of(RG(4), d[0], -(n.ge2 * dT));
     eq[3] = jT * (RG)m.ux;
     eq[4] = -eq[3];
     eq[5] = jT * (RG)m.uy;
@@ -698,31 +849,34 @@ LBM_HD void collide_pcm(const CavityConst<R> &c, const Thermo<RH> &th, const Mac
     // the zeroth moment is conserved (d_0 = eq_0), only S moves it
     RG a[9];
     a[0] = (d[0] + S) * moment_norm<RG>(0);
-    a[1] = fma_of(RG(-2) * moment_norm<RG>(1), S, fma_of(t.zB[1], eq[1], t.zA[1] * d[1]));
-    a[2] = fma_of(moment_norm<RG>(2), S, fma_of(t.zB[2], eq[2], t.zA[2] * d[2]));
-#pragma unroll
-    for (int k = 3; k < 7; ++k) a[k] = fma_of(t.zB[k], eq[k], t.zA[k] * d[k]);
-    a[7] = t.zA[7] * d[7];
-    a[8] = t.zA[8] * d[8];
+    a[1] = fma_of(RG(-2) * moment_norm<RG>(1), S, fma_of(n.zB1, eq[1], n.zA1 * d[1]));
+    a[2] = fma_of(moment_norm<RG>(2), S, fma_of(n.zB1, eq[2], n.zA1 * d[2]));
+    a[3] = fma_of(n.zB3, eq[3], n.zA3 * d[3]);
+    a[4] = fma_of(n.zB4, eq[4], n.zA4 * d[4]);
+    a[5] = fma_of(n.zB3, eq[5], n.zA3 * d[5]);
+    a[6] = fma_of(n.zB4, eq[6], n.zA4 * d[6]);
+    a[7] = n.zA7 * d[7];
+    a[8] = n.zA7 * d[8];
     RG qs[9];
     from_scaled(a, qs);
     pcm_out(qs, rest, q);
 }
 
 // Metal-foam collision, Eqs. (43), (45)-(46).
-template <typename R>
-LBM_HD void collide_metal(const CavityConst<R> &c, const Macro<R> &m, R S_metal, R d[9], R q[9]) {
-    R eq[3];  // eq_3 .. eq_8 = 0
-    eq[0] = c.c_pm * m.dTm;
-    eq[1] = (-R(4) * c.c_pm + R(2) * c.c_mref) * m.dTm;
-    eq[2] = (R(4) * c.c_pm - R(3) * c.c_mref) * m.dTm;
-    // scaled moments ((1 - eta) d + eta eq + S (1, -2, 1, 0, ...)) / |M_k|^2
+template <typename R, typename RH>
+LBM_HD void collide_metal(const NodeConst<R, RH> &n, const Macro<R> &m, R S_metal, R d[9], R q[9]) {
+    // equilibrium (1, me1, me2, 0, ...) T_m (c_pm = 1); scaled moments
+    // ((1 - eta) d + eta eq + S (1, -2, 1, 0, ...)) / |M_k|^2
     R a[9];
-    a[0] = fma_of(moment_norm<R>(0), S_metal, fma_of(c.mB[0], eq[0], c.mA[0] * d[0]));
-    a[1] = fma_of(R(-2) * moment_norm<R>(1), S_metal, fma_of(c.mB[1], eq[1], c.mA[1] * d[1]));
-    a[2] = fma_of(moment_norm<R>(2), S_metal, fma_of(c.mB[2], eq[2], c.mA[2] * d[2]));
-#pragma unroll
-    for (int k = 3; k < 9; ++k) a[k] = c.mA[k] * d[k];
+    a[0] = fma_of(moment_norm<R>(0), S_metal, fma_of(n.mB0, m.dTm, n.mA0 * d[0]));
+    a[1] = fma_of(R(-2) * moment_norm<R>(1), S_metal, fma_of(n.mB1, n.me1 * m.dTm, n.mA1 * d[1]));
+    a[2] = fma_of(moment_norm<R>(2), S_metal, fma_of(n.mB1, n.me2 * m.dTm, n.mA1 * d[2]));
+    a[3] = n.mA3 * d[3];
+    a[4] = n.mA4 * d[4];
+    a[5] = n.mA3 * d[5];
+    a[6] = n.mA4 * d[6];
+    a[7] = n.mA7 * d[7];
+    a[8] = n.mA7 * d[8];
     from_scaled(a, q);
 }
 
@@ -731,19 +885,18 @@ LBM_HD void collide_metal(const CavityConst<R> &c, const Macro<R> &m, R S_metal,
 // scaled moments e_k = g_k ((1 - zeta_k) d_k + zeta_k eq_k + S_k), the
 // zeroth moment conserved (d_0 = eq_0 = delta H) so only S moves it.
 template <typename R, typename RH, typename RG>
-LBM_HD void collide_pcm5(const CavityConst<R> &c, const Thermo<RH> &th, const Macro<R> &m, RH S_pcm,
-                         RG d[9], RH rest, RH q[9]) {
-    const ThermalConst<RG> &t = thermal<RG>(c);
-    const RG jT = t.c_pl * (RG)th.Tf * t.inv_phi;
+LBM_HD void collide_pcm5(const NodeConst<R, RH> &n, const Thermo<RH> &th, const Macro<R> &m, RH S_pcm, RG d[9],
+                         RH rest, RH q[9]) {
+    const RG jT = (RG)th.Tf * (RG)n.inv_phi;  // c_pl = 1
     const RG eq1 = jT * (RG)m.ux, eq2 = jT * (RG)m.uy;  // eq_4 = 0
-    const RG eq3 = t.varpi * t.c_fref * (RG)(th.Tf - thermal<RH>(c).T_ref);
+    const RG eq3 = n.ge1 * (RG)(th.Tf - n.Tf_ref);
     const RG S = (RG)S_pcm;
     RG e[5];
     e[0] = d[0] + S;
-    e[1] = fma_of(t.zB[1], eq1, t.zA[1] * d[1]);
-    e[2] = fma_of(t.zB[2], eq2, t.zA[2] * d[2]);
-    e[3] = fma_of(t.varpi * RG(0.25), S, fma_of(t.zB[3], eq3, t.zA[3] * d[3]));
-    e[4] = t.zA[4] * d[4];
+    e[1] = fma_of(n.zB1, eq1, n.zA1 * d[1]);
+    e[2] = fma_of(n.zB1, eq2, n.zA1 * d[2]);
+    e[3] = fma_of((RG)n.w4, S, fma_of(n.zB3, eq3, n.zA3 * d[3]));
+    e[4] = n.zA3 * d[4];
     RG qs[9];
     from_scaled5(e, qs);
     qs[5] = qs[6] = qs[7] = qs[8] = RG(0);
@@ -752,15 +905,15 @@ LBM_HD void collide_pcm5(const CavityConst<R> &c, const Thermo<RH> &th, const Ma
 
 // D2Q5 metal-foam collision (Appendix B): Eq. (B4), Q, S (1, 0, 0, varpi, 0),
 // in the scaled moments of from_scaled5.
-template <typename R>
-LBM_HD void collide_metal5(const CavityConst<R> &c, const Macro<R> &m, R S_metal, R d[9], R q[9]) {
-    const R eq0 = c.c_pm * m.dTm, eq3 = c.varpi * c.c_mref * m.dTm;  // eq_1 = eq_2 = eq_4 = 0
+template <typename R, typename RH>
+LBM_HD void collide_metal5(const NodeConst<R, RH> &n, const Macro<R> &m, R S_metal, R d[9], R q[9]) {
+    const R eq3 = n.me1 * m.dTm;  // eq_0 = T_m (c_pm = 1), eq_1 = eq_2 = eq_4 = 0
     R e[5];
-    e[0] = fma_of(c.mB[0], eq0, c.mA[0] * d[0]) + S_metal;
-    e[1] = c.mA[1] * d[1];
-    e[2] = c.mA[2] * d[2];
-    e[3] = fma_of(c.varpi * R(0.25), S_metal, fma_of(c.mB[3], eq3, c.mA[3] * d[3]));
-    e[4] = c.mA[4] * d[4];
+    e[0] = fma_of(n.mB0, m.dTm, n.mA0 * d[0]) + S_metal;
+    e[1] = n.mA1 * d[1];
+    e[2] = n.mA1 * d[2];
+    e[3] = fma_of(n.w4, S_metal, fma_of(n.mB3, eq3, n.mA3 * d[3]));
+    e[4] = n.mA3 * d[4];
     from_scaled5(e, q);
 }
 
@@ -780,47 +933,60 @@ LBM_HD int thermal_wall(const CavityConst<R> &c, int x, int y) {
 // the partner's pulled offsets (Eq. 52 with wall velocity 0; thermal
 // analogues with the isothermal or zero-gradient wall values).
 template <int QT, typename R, typename RH>
-LBM_HD void reconstruct_wall(const CavityConst<R> &c, int x, int y, R qf[9], RH qg[9], R qh[9]) {
+LBM_HD void reconstruct_wall(const CavityConst<R> &c, const NodeConst<R, RH> &n, int x, int y, R qf[9], RH qg[9],
+                             R qh[9]) {
     const ThermalConst<RH> &t = thermal<RH>(c);
     Thermo<RH> pt;
     Macro<R> p;
-    macros<QT>(c, qf, qg, qh, pt, p);
-    RH Tb, Hb;
-    R Tmb;
-    const int w = thermal_wall(c, x, y);
-    if (w >= 0) {
-        Tb = t.T_wall[w];
-        Hb = t.H_wall[w];
-        Tmb = c.T_wall[w];
-    } else {
-        Tb = pt.Tf;
-        Hb = pt.H;
-        Tmb = p.Tm;
-    }
+    macros<QT>(n, qf, qg, qh, pt, p);
+    // the wall values: the partner's (adiabatic), or those of the isothermal
+    // wall the node lies on (a vertical one before a horizontal one), taken by
+    // selects from uniform values rather than loaded per lane
+    RH Tb = pt.Tf, Hb = pt.H;
+    R Tmb = p.Tm;
+    const bool on[4] = {!c.periodic && x == 0, !c.periodic && x == c.nx - 1, y == 0, y == c.ny - 1};
+#pragma unroll
+    for (int w = 3; w >= 0; --w)
+        if (c.wall_iso[w]) {
+            Tb = on[w] ? t.T_wall[w] : Tb;
+            Hb = on[w] ? t.H_wall[w] : Hb;
+            Tmb = on[w] ? c.T_wall[w] : Tmb;
+        }
     const R uu = p.ux * p.ux + p.uy * p.uy;
     const RH dTg = Tb - pt.Tf;
     const R dTh = Tmb - p.Tm;
     // g^eq(H_b, T_b, 0) - g^eq(H, T, u) from Eq. (40) / Eq. (B3); h likewise
     // from Eq. (49) / Eq. (B5)
-    const RH jT = t.inv_cs2 * t.c_pl * pt.Tf * t.inv_phi;
-    qf[0] += -w_of<R>(0) * p.rho * (-R(1.5) * uu * c.inv_phi);
+    const RH jT = t.inv_cs2 * pt.Tf * t.inv_phi;
+    const R uu15 = R(1.5) * uu * c.inv_phi;
+    qf[0] += -w_of<R>(0) * p.rho * -uu15;
     if (QT == 9) {
         qg[0] += (Hb - pt.H) - RH(5) / RH(9) * t.c_fref * dTg;
-        qh[0] += (c.c_pm - R(5) / R(9) * c.c_mref) * dTh;
+        qh[0] += (R(1) - R(5) / R(9) * c.c_mref) * dTh;
     } else {
         qg[0] += (Hb - pt.H) - t.varpi * t.c_fref * dTg;
-        qh[0] += (c.c_pm - c.varpi * c.c_mref) * dTh;
+        qh[0] += (R(1) - c.varpi * c.c_mref) * dTh;
     }
+    // the moving directions by opposite pairs (1, 3), (2, 4), (5, 7), (6, 8)
+    const int fwd[4] = {1, 2, 5, 6}, bwd[4] = {3, 4, 7, 8};
+    const R along[4] = {p.ux, p.uy, p.ux + p.uy, p.uy - p.ux};
 #pragma unroll
-    for (int i = 1; i < 9; ++i) {
-        const R eu = R(ex_of(i)) * p.ux + R(ey_of(i)) * p.uy;
+    for (int k = 0; k < 4; ++k) {
+        const int i = fwd[k], j = bwd[k];
+        const R eu = along[k];
         // f^eq(rho, 0) - f^eq(rho, u) from Eq. (27)
-        qf[i] += -w_of<R>(i) * p.rho * (R(3) * eu + R(4.5) * eu * eu * c.inv_phi - R(1.5) * uu * c.inv_phi);
+        const R e3 = R(3) * eu, e45 = R(4.5) * eu * eu * c.inv_phi, wr = -w_of<R>(i) * p.rho;
+        qf[i] += wr * (e3 + e45 - uu15);
+        qf[j] += wr * (e45 - e3 - uu15);
         if (i < QT) {
             const RH wg = QT == 9 ? w_of<RH>(i) : RH(0.25) * t.varpi;
             const R wh = QT == 9 ? w_of<R>(i) : R(0.25) * c.varpi;
-            qg[i] += wg * (t.c_fref * dTg - jT * (RH)eu);
-            qh[i] += wh * c.c_mref * dTh;
+            const RH cT = t.c_fref * dTg, ju = jT * (RH)eu;
+            const R hw = wh * c.c_mref * dTh;
+            qg[i] += wg * (cT - ju);
+            qg[j] += wg * (cT + ju);
+            qh[i] += hw;
+            qh[j] += hw;
         }
     }
 }
@@ -828,9 +994,14 @@ LBM_HD void reconstruct_wall(const CavityConst<R> &c, int x, int y, R qf[9], RH 
 // Wall classification and the node whose populations a node pulls: its own
 // neighbourhood, or its interior partner's for a wall node (inward normal
 // neighbour, diagonal at corners).
+enum { NODE_WALL = 1, NODE_NEAR_X = 2, NODE_NEAR_Y = 4, NODE_OWNED = 8 };
 struct NodeGeom {
-    bool wall, near_x, near_y;
+    int kind;  // NODE_WALL; NODE_NEAR_*: an interior node next to a vertical / horizontal wall
     int sx, sy;
+    LBM_HD bool wall() const { return kind & NODE_WALL; }
+    LBM_HD bool near_x() const { return kind & NODE_NEAR_X; }
+    LBM_HD bool near_y() const { return kind & NODE_NEAR_Y; }
+    LBM_HD bool near_wall() const { return kind & (NODE_NEAR_X | NODE_NEAR_Y); }
 };
 
 template <typename R>
@@ -839,15 +1010,16 @@ LBM_HD NodeGeom geometry(const CavityConst<R> &c, int x, int y, bool pull) {
     const int nx = c.nx, ny = c.ny;
     const bool vwall = !c.periodic && (x == 0 || x == nx - 1);
     const bool hwall = (y == 0 || y == ny - 1);
-    g.wall = vwall || hwall;
+    const bool wall = vwall || hwall;
     g.sx = x;
     g.sy = y;
-    if (pull && g.wall) {
+    if (pull && wall) {
         if (!c.periodic) g.sx = (x == 0) ? 1 : ((x == nx - 1) ? nx - 2 : x);
         g.sy = (y == 0) ? 1 : ((y == ny - 1) ? ny - 2 : y);
     }
-    g.near_x = !g.wall && !c.periodic && (x == 1 || x == nx - 2);
-    g.near_y = !g.wall && (y == 1 || y == ny - 2);
+    g.kind = wall ? NODE_WALL
+                  : (!c.periodic && (x == 1 || x == nx - 2) ? NODE_NEAR_X : 0) |
+                        (y == 1 || y == ny - 2 ? NODE_NEAR_Y : 0);
     return g;
 }
 
@@ -890,9 +1062,15 @@ struct AnyBand {
     LBM_HD FarRef row(int y) const { return (*this)(0, y); }
     LBM_HD static FarRef at_row(FarRef r, int x) { return FarRef{r.rel + x, r.jump}; }
 };
+// Band of row y: a multiplication by the rounded-up reciprocal 2^32 /
+// band_rows, one too large at most.
 template <typename R>
-LBM_HD BandOrigin band_origin(const CavityConst<R> &c, int y) {  // from the band of row y
-    const int ba = y / c.band_rows;
+LBM_HD int band_of(const CavityConst<R> &c, int y) {
+    const uint32_t b = (uint32_t)(((uint64_t)(uint32_t)y * c.band_recip) >> 32);
+    return (int)(b * (uint32_t)c.band_rows > (uint32_t)y ? b - 1 : b);
+}
+template <typename R>
+LBM_HD BandOrigin band_origin(const CavityConst<R> &c, int ba) {  // from band ba
     return BandOrigin{ba * c.band_rows, (ba + 1) * c.band_rows, c.pitch, (uint32_t)c.band_bytes};
 }
 template <typename R>
@@ -911,31 +1089,15 @@ LBM_HD int64_t flat_index(const CavityConst<R> &c, int x, int y) {
 }
 
 // Offsets of the node's post-streaming populations: pulled from the
-// neighbours (Eqs. 15, 33, 44), or read in place for the initial state.
-// src is the band block addr is relative to.
-template <class Lay, typename R, typename RH, bool PULL, class A>
-LBM_HD void gather_at(const CavityConst<R> &c, const void *src, const NodeGeom &g, int x, int y, A addr,
-                      R qf[9], RH qg[9], R qh[9]) {
+// neighbours (Eqs. 15, 33, 44), or read in place for the initial state, from
+// a whole state buffer.
+template <class Lay, typename R, typename RH, bool PULL>
+LBM_HD void gather(const CavityConst<R> &c, const void *buf, const NodeGeom &g, int x, int y, R qf[9], RH qg[9],
+                   R qh[9]) {
+    const void *src = band_block(c, buf, 0);
+    const AnyBand addr = any_band(c);
     const int nx = c.nx;
     const int64_t stride = c.band_nodes;
-    if (PULL && !c.periodic) {
-        // no wrap: the three rows the pulls read are resolved to their bands
-        // once, and each pull is an offset within its row
-        const auto row_up = addr.row(g.sy + 1), row_mid = addr.row(g.sy), row_down = addr.row(g.sy - 1);
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            const auto k = A::at_row(ey_of(i) > 0 ? row_down : (ey_of(i) < 0 ? row_up : row_mid), g.sx - ex_of(i));
-            qf[i] = Lay::template load<R>(src, stride, 0, i, k, c);
-            if (i < Lay::QT) {
-                qg[i] = Lay::template load<RH>(src, stride, 1, i, k, c);
-                qh[i] = Lay::template load<R>(src, stride, 2, i, k, c);
-            } else {
-                qg[i] = RH(0);
-                qh[i] = R(0);
-            }
-        }
-        return;
-    }
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
         int px = x, py = y;
@@ -956,18 +1118,145 @@ LBM_HD void gather_at(const CavityConst<R> &c, const void *src, const NodeGeom &
     }
 }
 
-// From a whole state buffer.
-template <class Lay, typename R, typename RH, bool PULL>
-LBM_HD void gather(const CavityConst<R> &c, const void *buf, const NodeGeom &g, int x, int y, R qf[9],
-                   RH qg[9], R qh[9]) {
-    gather_at<Lay, R, RH, PULL>(c, band_block(c, buf, 0), g, x, y, any_band(c), qf, qg, qh);
+// One workgroup's view of a state buffer: the rows it reads or writes lie in
+// the bands ba and ba + 1 of its cavity (org).  flat: they lie in band ba
+// alone and nothing wraps, so a pull's place is the node's own plus a
+// uniform distance.
+struct View {
+    BandOrigin org;
+    uint32_t stride;
+    int nx;
+    bool flat, periodic;
+};
+template <typename R>
+LBM_HD View view_of(const CavityConst<R> &c, int ba, int last_row) {
+    const BandOrigin org = band_origin(c, ba);
+    return View{org, (uint32_t)c.band_nodes, c.nx, !c.periodic && last_row < org.y_next, c.periodic != 0};
 }
 
-// Energy and mass carried by direction i of the given offsets (FP64);
-// energy moves only along the thermal lattice's links.
+// The node pulled along direction i by the node whose neighbourhood is at
+// (sx, sy).  In a flat view every pull has one vector offset: the row is a
+// uniform shift (planes that pull from the row below are never the first,
+// so the sum stays positive) and the column a constant.
+template <int I>
+LBM_HD Pull pull_of(const View &v, int sx, int sy, bool flat) {
+    if (flat)
+        return Pull{-ey_of(I) * v.org.pitch, (uint32_t)((sy - v.org.y_first) * v.org.pitch + sx - 1),
+                    (uint32_t)(1 - ex_of(I)), 0u};
+    int px = sx - ex_of(I);
+    if (v.periodic) px = px < 0 ? px + v.nx : (px >= v.nx ? px - v.nx : px);
+    const NodeRef k = v.org(px, sy - ey_of(I));
+    return Pull{0, k.rel, 0u, k.jump};
+}
+template <class Lay, typename R, typename RH, bool PULL, bool FLAT, int I = 0>
+LBM_HD void pull_all(const NodeConst<R, RH> &n, Blocks b, const View &v, const NodeGeom &g, R qf[9], RH qg[9],
+                     R qh[9]) {
+    if constexpr (I < 9) {
+        const NodeRef own = PULL ? NodeRef{0u, 0u} : v.org(g.sx, g.sy);
+        const Pull p = PULL ? pull_of<I>(v, g.sx, g.sy, FLAT) : Pull{0, own.rel, 0u, own.jump};
+        qf[I] = Lay::template pull<R>(b, v.stride, 0, I, p, n);
+        if constexpr (I < Lay::QT) {
+            qg[I] = Lay::template pull<RH>(b, v.stride, 1, I, p, n);
+            qh[I] = Lay::template pull<R>(b, v.stride, 2, I, p, n);
+        } else {
+            qg[I] = RH(0);
+            qh[I] = R(0);
+        }
+        pull_all<Lay, R, RH, PULL, FLAT, I + 1>(n, b, v, g, qf, qg, qh);
+    }
+}
+// The same offsets as gather(), within a workgroup's blocks.
+template <class Lay, typename R, typename RH, bool PULL>
+LBM_HD void gather_view(const NodeConst<R, RH> &n, Blocks b, const View &v, const NodeGeom &g, R qf[9], RH qg[9],
+                        R qh[9]) {
+    if (PULL && v.flat) pull_all<Lay, R, RH, PULL, true>(n, b, v, g, qf, qg, qh);
+    else pull_all<Lay, R, RH, PULL, false>(n, b, v, g, qf, qg, qh);
+}
+
+// Energy and mass carried by the three links of a node's side towards one of
+// its walls (FP64): the axis link and the two diagonals a and b, in that
+// order.  q(f, i) selects the population; energy moves only along the
+// thermal lattice's links (g_ref, h_ref: alike on all axes and all
+// diagonals).
+struct LinkSum {
+    double E, M;
+};
+template <int QT, bool OUT, typename R>
+LBM_HD void add_link(const CavityConst<R> &c, bool diag, double qf, double qg, double qh, bool use, LinkSum &s) {
+    const int i = diag ? 5 : 1;
+    const double e = i < QT ? c.we * (c.g_ref[i] + qg) + c.wm * (c.h_ref[i] + qh) : 0.0;
+    const double m = w_of<double>(i) + qf;
+    s.E += use ? (OUT ? -e : e) : 0.0;
+    s.M += use ? (OUT ? -m : m) : 0.0;
+}
+// The links between node (x, y), next to a vertical (X) or horizontal wall,
+// and that wall.  low: the left or bottom wall.  Populations leave (OUT)
+// along the directions that point at the wall and enter along their
+// opposites; a diagonal between a corner-adjacent node and a vertical wall
+// counts for that wall (skip_lo: the node is next to the left wall, skip_hi:
+// the right one).
+template <int QT, bool X, bool OUT, typename R, typename RH>
+LBM_HD void wall_links(const CavityConst<R> &c, bool low, bool skip_lo, bool skip_hi, const R qf[9], const RH qg[9],
+                       const R qh[9], LinkSum &s) {
+    // directions with positive (p) and negative (n) component along the axis
+    using RG = typename MomentType<R, RH>::T;  // moving populations are held in it
+    constexpr int p[3] = {X ? 1 : 2, 5, X ? 8 : 6}, n[3] = {X ? 3 : 4, X ? 6 : 7, X ? 7 : 8};
+    const bool pos = low != OUT;
+#pragma unroll
+    for (int k = 0; k < 3; ++k) {
+        // horizontal walls: the diagonals 5, 8 (entering 5, 8 from, leaving 6,
+        // 7 to, the left; and so on) that belong to a vertical wall
+        bool use = true;
+        if (!X && k == 1) use = low ? !skip_lo : !skip_hi;
+        if (!X && k == 2) use = low ? !skip_hi : !skip_lo;
+        add_link<QT, OUT>(c, k > 0, (double)(pos ? qf[p[k]] : qf[n[k]]),
+                          (double)(pos ? (RG)qg[p[k]] : (RG)qg[n[k]]), (double)(pos ? qh[p[k]] : qh[n[k]]), use, s);
+    }
+}
+
+// Where the tallies of the nodes next to a wall are kept, energy and mass of
+// one slot each: column() of a node next to the left or right wall by its
+// row, row() of one next to the bottom or top wall by its column.
+// CavityTally: the cavity's own, in global memory.
+template <typename R>
+struct CavityTally {
+    double *acc;
+    const CavityConst<R> &c;
+    LBM_HD double *column(bool left, int y) const { return acc + 2 * (c.acc0 + (left ? y : c.ny + y)); }
+    LBM_HD double *row(bool bottom, int x) const { return acc + 2 * (c.acc0 + 2 * c.ny + (bottom ? x : c.nx + x)); }
+    LBM_HD void add(const double *from, double *to, LinkSum s) const {
+        to[0] = from[0] + s.E;
+        to[1] = from[1] + s.M;
+    }
+    LBM_HD void add_column(bool left, int y, LinkSum s) const { add(column(left, y), column(left, y), s); }
+    LBM_HD void add_row(bool bottom, int x, LinkSum s) const { add(row(bottom, x), row(bottom, x), s); }
+};
+// TileTally: a tile's copy in LDS (TH left, TH right, TW bottom, TW top) for
+// the updates of one launch; the last one adds to the copy and writes the
+// cavity's (LAST).  Adding in global memory in each update put a round trip
+// to memory into every update of the tiles at the walls, which in a small
+// cavity set the launch's duration: with the links summed by selects instead
+// of a branch per direction, 256^2 FP32_H64 went from 5.3 to 4.5 us a step.
+template <int TW, int TH, bool LAST, typename R>
+struct TileTally {
+    static constexpr int N = 4 * (TW + TH);  // doubles
+    CavityTally<R> all;
+    double *lds;
+    int x0, y0;
+    LBM_HD double *column(bool left, int y) const { return lds + 2 * ((left ? 0 : TH) + y - y0); }
+    LBM_HD double *row(bool bottom, int x) const { return lds + 2 * (2 * TH + (bottom ? 0 : TW) + x - x0); }
+    LBM_HD void add_column(bool left, int y, LinkSum s) const {
+        all.add(column(left, y), LAST ? all.column(left, y) : column(left, y), s);
+    }
+    LBM_HD void add_row(bool bottom, int x, LinkSum s) const {
+        all.add(row(bottom, x), LAST ? all.row(bottom, x) : row(bottom, x), s);
+    }
+};
+
+// Energy and mass carried by direction i of the given offsets (FP64).
 template <int QT, typename R, typename RH>
-LBM_HD void link_content(const CavityConst<R> &c, int i, const R qf[9], const RH qg[9], const R qh[9],
-                         double &e, double &m) {
+LBM_HD void link_content(const CavityConst<R> &c, int i, const R qf[9], const RH qg[9], const R qh[9], double &e,
+                         double &m) {
     e = i < QT ? c.we * (c.g_ref[i] + (double)qg[i]) + c.wm * (c.h_ref[i] + (double)qh[i]) : 0.0;
     m = (double)w_of<double>(i) + (double)qf[i];
 }
@@ -977,117 +1266,109 @@ LBM_HD void link_content(const CavityConst<R> &c, int i, const R qf[9], const RH
 // reconstruction, macroscopic values, the three collisions and the
 // interstitial sources.  On return q* hold the post-collision offsets and
 // m, th the values the split layout stores as bases; the result is the
-// new PCM source Sr_f.
-template <int QT, typename R, typename RH, bool PULL>
-LBM_HD RH update_node(const CavityConst<R> &c, const NodeGeom &g, int x, int y, R qf[9], RH qg[9], R qh[9],
-                      R sr_prev, bool tally, double *__restrict__ acc, Thermo<RH> &th, Macro<R> &m) {
-    const int nx = c.nx, ny = c.ny;
+// new PCM source Sr_f.  edge (uniform over the workgroup): some node of the
+// workgroup may be a wall node or next to one; without it the wall code is
+// passed by a scalar branch.
+template <int QT, typename R, typename RH, bool PULL, class Tally>
+LBM_HD RH update_node(const CavityConst<R> &c, const NodeConst<R, RH> &n, bool edge, const NodeGeom &g, int x, int y,
+                      R qf[9], RH qg[9], R qh[9], R sr_prev, bool tally, Tally acc, Thermo<RH> &th,
+                      Macro<R> &m) {
     // Wall tallies: an interior node next to a wall owns one slot per wall it
-    // touches (x: the vertical wall, y: the horizontal one).
-    double xE = 0.0, xM = 0.0, yE = 0.0, yM = 0.0;
-    if (PULL && tally && (g.near_x || g.near_y)) {
+    // touches (x: the vertical wall, y: the horizontal one).  Set and read
+    // under the same conditions only.
+    LinkSum sx, sy;
+    if (edge) {
         // inflow: populations pulled from wall nodes (post-collision of the
         // previous step)
-#pragma unroll
-        for (int i = 1; i < 9; ++i) {
-            const int px = x - ex_of(i), py = y - ey_of(i);
-            const bool onx = !c.periodic && (px == 0 || px == nx - 1);
-            const bool ony = (py == 0 || py == ny - 1);
-            if (onx || ony) {
-                double e, mm;
-                link_content<QT>(c, i, qf, qg, qh, e, mm);
-                if (onx) {
-                    xE += e;
-                    xM += mm;
-                } else {
-                    yE += e;
-                    yM += mm;
-                }
-            }
+        if (tally && g.near_x()) {
+            sx = LinkSum{0.0, 0.0};
+            if (PULL) wall_links<QT, true, false>(c, x == 1, false, false, qf, qg, qh, sx);
         }
+        if (tally && g.near_y()) {
+            sy = LinkSum{0.0, 0.0};
+            if (PULL)
+                wall_links<QT, false, false>(c, y == 1, g.near_x() && x == 1, g.near_x() && x != 1, qf, qg, qh, sy);
+        }
+        if (PULL && g.wall()) reconstruct_wall<QT>(c, n, x, y, qf, qg, qh);
     }
-
-    if (PULL && g.wall) reconstruct_wall<QT>(c, x, y, qf, qg, qh);
 
     Moments<R, RH> mo;
     field_moments<QT>(qf, qg, qh, mo);
-    macros_of<QT>(c, mo, th, m);
-    collide_flow(c, m, mo.f, qf);
+    macros_of(n, mo, th, m);
+    collide_flow(n, m, mo.f, qf);
     // Eqs. (36), (47) with the backward difference of Remark III.
-    const RH srf = (RH)c.hv_f * ((RH)m.Tm - th.Tf);
-    const R srm = c.hv_m * (m.Tf - m.Tm);
-    const R srm_prev = -c.sr_ratio * sr_prev;
-    const RH S_pcm = srf + RH(0.5) * (srf - (RH)sr_prev);
-    const R S_metal = srm + R(0.5) * (srm - srm_prev);
+    const RH srf = n.hv_f * ((RH)m.Tm - th.Tf);
+    const R srm = n.hv_m * (m.Tf - m.Tm);
+    const R srm_prev = -n.sr_ratio * sr_prev;
+    const RH S_pcm = fma_of(RH(0.5), srf - (RH)sr_prev, srf);
+    const R S_metal = fma_of(R(0.5), srm - srm_prev, srm);
     if (QT == 9) {
-        collide_pcm(c, th, m, S_pcm, mo.g, mo.rest, qg);
-        collide_metal(c, m, S_metal, mo.h, qh);
+        collide_pcm(n, th, m, S_pcm, mo.g, mo.rest, qg);
+        collide_metal(n, m, S_metal, mo.h, qh);
     } else {
-        collide_pcm5(c, th, m, S_pcm, mo.g, mo.rest, qg);
-        collide_metal5(c, m, S_metal, mo.h, qh);
+        collide_pcm5(n, th, m, S_pcm, mo.g, mo.rest, qg);
+        collide_metal5(n, m, S_metal, mo.h, qh);
     }
 
-    if (tally && (g.near_x || g.near_y)) {
+    if (edge) {
         // outflow: post-collision populations aimed at wall nodes
-#pragma unroll
-        for (int i = 1; i < 9; ++i) {
-            const int tx = x + ex_of(i), ty = y + ey_of(i);
-            const bool onx = !c.periodic && (tx == 0 || tx == nx - 1);
-            const bool ony = (ty == 0 || ty == ny - 1);
-            if (onx || ony) {
-                double e, mm;
-                link_content<QT>(c, i, qf, qg, qh, e, mm);
-                if (onx) {
-                    xE -= e;
-                    xM -= mm;
-                } else {
-                    yE -= e;
-                    yM -= mm;
-                }
-            }
+        if (tally && g.near_x()) {
+            wall_links<QT, true, true>(c, x == 1, false, false, qf, qg, qh, sx);
+            acc.add_column(x == 1, y, sx);
         }
-        if (g.near_x) {
-            const int64_t slot = c.acc0 + (x == 1 ? y : ny + y);
-            acc[2 * slot] += xE;
-            acc[2 * slot + 1] += xM;
-        }
-        if (g.near_y) {
-            const int64_t slot = c.acc0 + 2 * ny + (y == 1 ? x : nx + x);
-            acc[2 * slot] += yE;
-            acc[2 * slot + 1] += yM;
+        if (tally && g.near_y()) {
+            wall_links<QT, false, true>(c, y == 1, g.near_x() && x == 1, g.near_x() && x != 1, qf, qg, qh, sy);
+            acc.add_row(y == 1, x, sy);
         }
     }
     return srf;
 }
 
-// One node's full time step; addr places the node and its neighbours
-// relative to the band blocks src and dst.
-template <class Lay, typename R, typename RH, bool PULL, class A>
-LBM_HD void step_node_at(const CavityConst<R> &c, const void *src, void *dst, const R *__restrict__ sr_src,
-                         R *__restrict__ sr_dst, double *__restrict__ acc, int x, int y, A addr) {
-    const NodeGeom g = geometry(c, x, y, PULL);
-    R qf[9], qh[9];
-    RH qg[9];
-    gather_at<Lay, R, RH, PULL>(c, src, g, x, y, addr, qf, qg, qh);
-    const auto k = addr(x, y);
-    const int64_t kf = flat_index(c, x, y);
-    Thermo<RH> th;
-    Macro<R> m;
-    const RH srf = update_node<Lay::QT, R, RH, PULL>(c, g, x, y, qf, qg, qh, sr_src[kf], true, acc, th, m);
-    const ThermalConst<RH> &t = thermal<RH>(c);
-    const int64_t stride = c.band_nodes;
-    Lay::template store<R>(dst, stride, 0, qf, m.drho, k, c);
-    Lay::template store<RH>(dst, stride, 1, qg, t.c_fref * (th.Tf - t.T_ref), k, c);
-    Lay::template store<R>(dst, stride, 2, qh, c.c_mref * m.dTm, k, c);
-    sr_dst[kf] = (R)srf;
-}
-
-// The same on whole state buffers.
+// One node's full time step on whole state buffers.
 template <class Lay, typename R, typename RH, bool PULL>
 LBM_HD void step_node(const CavityConst<R> &c, const void *src, void *dst, const R *__restrict__ sr_src,
                       R *__restrict__ sr_dst, double *__restrict__ acc, int x, int y) {
-    step_node_at<Lay, R, RH, PULL>(c, band_block(c, src, 0), band_block(c, dst, 0), sr_src, sr_dst, acc, x, y,
-                                   any_band(c));
+    const NodeConst<R, RH> &n = node_const_of<RH>(c);
+    const NodeGeom g = geometry(c, x, y, PULL);
+    R qf[9], qh[9];
+    RH qg[9];
+    gather<Lay, R, RH, PULL>(c, src, g, x, y, qf, qg, qh);
+    const int64_t kf = flat_index(c, x, y);
+    Thermo<RH> th;
+    Macro<R> m;
+    const RH srf = update_node<Lay::QT, R, RH, PULL>(c, n, true, g, x, y, qf, qg, qh, sr_src[kf], true,
+                                                          CavityTally<R>{acc, c}, th, m);
+    const ThermalConst<RH> &t = thermal<RH>(c);
+    const FarRef k = any_band(c)(x, y);
+    void *blk = band_block(c, dst, 0);
+    const int64_t stride = c.band_nodes;
+    Lay::template store<R>(blk, stride, 0, qf, m.drho, k, c);
+    Lay::template store<RH>(blk, stride, 1, qg, t.c_fref * (th.Tf - t.T_ref), k, c);
+    Lay::template store<R>(blk, stride, 2, qh, c.c_mref * m.dTm, k, c);
+    sr_dst[kf] = (R)srf;
+}
+
+// The same within a workgroup's view of the buffers (src and dst are the
+// blocks of the view's first band); edge as for update_node.
+template <class Lay, typename R, typename RH, bool PULL>
+LBM_HD void step_node_view(const CavityConst<R> &c, const NodeConst<R, RH> &n, bool edge, Blocks src, Blocks dst,
+                           const View &v, const R *__restrict__ sr_src, R *__restrict__ sr_dst,
+                           double *__restrict__ acc, int x, int y) {
+    NodeGeom g{0, x, y};
+    if (edge) g = geometry(c, x, y, PULL);
+    R qf[9], qh[9];
+    RH qg[9];
+    gather_view<Lay, R, RH, PULL>(n, src, v, g, qf, qg, qh);
+    const int64_t kf = flat_index(c, x, y);
+    Thermo<RH> th;
+    Macro<R> m;
+    const RH srf = update_node<Lay::QT, R, RH, PULL>(c, n, edge, g, x, y, qf, qg, qh, sr_src[kf], true,
+                                                          CavityTally<R>{acc, c}, th, m);
+    const NodeRef k = v.org(x, y);
+    Lay::template put<R>(dst, v.stride, 0, qf, m.drho, k, n);
+    Lay::template put<RH>(dst, v.stride, 1, qg, n.cf_base * (th.Tf - n.Tf_ref), k, n);
+    Lay::template put<R>(dst, v.stride, 2, qh, n.cm_base * m.dTm, k, n);
+    sr_dst[kf] = (R)srf;
 }
 
 // ---------------------------------------------------------------------------
@@ -1130,17 +1411,18 @@ template <class Lay>
 struct LdsCodec;
 template <class E, bool SCALED, int QT_>
 struct LdsCodec<Plain<E, SCALED, QT_>> {
+    using R = decltype(E::dec(typename E::T()));  // arithmetic type of the kernels
     using T = typename E::T;
     using C = decltype(E::dec(T()));
     static constexpr int QT = QT_;
     static constexpr size_t bytes(int nslot) { return (size_t)(9 + 2 * QT) * nslot * sizeof(T); }
     LBM_HD static int plane(int f, int i) { return f == 0 ? i : 9 + (f - 1) * QT + i; }
-    template <typename V, typename R>
-    LBM_HD static void put1(void *lds, int nslot, int f, int i, int slot, V v, const CavityConst<R> &c) {
+    template <typename V, class S>
+    LBM_HD static void put1(void *lds, int nslot, int f, int i, int slot, V v, const S &c) {
         ((T *)lds)[plane(f, i) * nslot + slot] = E::enc((C)(SCALED ? v * (V)c.scale[f] : v));
     }
-    template <typename R, typename RH>
-    LBM_HD static void put_node(void *lds, int nslot, int slot, const CavityConst<R> &c, const R qf[9],
+    template <typename R, typename RH, class S>
+    LBM_HD static void put_node(void *lds, int nslot, int slot, const S &c, const R qf[9],
                                 const RH qg[9], const R qh[9], R bf, RH bg, R bh) {
         (void)bf;
         (void)bg;
@@ -1154,14 +1436,15 @@ struct LdsCodec<Plain<E, SCALED, QT_>> {
             }
         }
     }
-    template <typename V, typename R>
-    LBM_HD static V get(const void *lds, int nslot, int f, int i, int slot, const CavityConst<R> &c) {
+    template <typename V, class S>
+    LBM_HD static V get(const void *lds, int nslot, int f, int i, int slot, const S &c) {
         const V v = (V)E::dec(((const T *)lds)[plane(f, i) * nslot + slot]);
         return SCALED ? v * (V)c.inv_scale[f] : v;
     }
 };
 template <int QT_>
 struct LdsCodec<PlainH64<QT_>> {
+    using R = float;
     static constexpr int QT = QT_;
     static constexpr int NF32 = PlainH64<QT_>::NF32;
     // FP32 planes, then the FP64 rest enthalpy plane (8-byte aligned)
@@ -1172,13 +1455,13 @@ struct LdsCodec<PlainH64<QT_>> {
         if (f == 1 && i == 0) ((double *)((char *)lds + f64_offset(nslot)))[slot] = (double)v;
         else ((float *)lds)[PlainH64<QT_>::plane(f, i) * nslot + slot] = (float)v;
     }
-    template <typename V, typename R>
-    LBM_HD static void put1(void *lds, int nslot, int f, int i, int slot, V v, const CavityConst<R> &c) {
+    template <typename V, class S>
+    LBM_HD static void put1(void *lds, int nslot, int f, int i, int slot, V v, const S &c) {
         (void)c;
         put1(lds, nslot, f, i, slot, v);
     }
-    template <typename R, typename RH>
-    LBM_HD static void put_node(void *lds, int nslot, int slot, const CavityConst<R> &c, const R qf[9],
+    template <typename R, typename RH, class S>
+    LBM_HD static void put_node(void *lds, int nslot, int slot, const S &c, const R qf[9],
                                 const RH qg[9], const R qh[9], R bf, RH bg, R bh) {
         (void)c;
         (void)bf;
@@ -1193,8 +1476,8 @@ struct LdsCodec<PlainH64<QT_>> {
             }
         }
     }
-    template <typename V, typename R>
-    LBM_HD static V get(const void *lds, int nslot, int f, int i, int slot, const CavityConst<R> &c) {
+    template <typename V, class S>
+    LBM_HD static V get(const void *lds, int nslot, int f, int i, int slot, const S &c) {
         (void)c;
         if (f == 1 && i == 0) return (V)((const double *)((const char *)lds + f64_offset(nslot)))[slot];
         return (V)((const float *)lds)[PlainH64<QT_>::plane(f, i) * nslot + slot];
@@ -1204,11 +1487,12 @@ struct LdsCodec<PlainH64<QT_>> {
 // eight 16-bit remainders from the base's rest equilibrium.
 template <class ER>
 struct LdsCodec<SplitT<ER>> {
+    using R = float;
     static constexpr int QT = 9;
     static constexpr size_t bytes(int nslot) { return (size_t)nslot * (6 * 4 + 24 * 2); }
-    template <typename V, typename R>
+    template <typename V, class S>
     LBM_HD static void put_field(void *lds, int nslot, int f, int slot, const V q[9], V beta,
-                                 const CavityConst<R> &c) {
+                                 const S &c) {
         float *P = (float *)lds;
         uint16_t *Qp = (uint16_t *)(P + 6 * nslot);
         const float b = (float)split_base<V>(beta);
@@ -1218,15 +1502,15 @@ struct LdsCodec<SplitT<ER>> {
         for (int i = 1; i < 9; ++i)
             Qp[(8 * f + i - 1) * nslot + slot] = ER::enc(split_rem<V>(i, q[i], (V)b, (V)c.scale[f]));
     }
-    template <typename R, typename RH>
-    LBM_HD static void put_node(void *lds, int nslot, int slot, const CavityConst<R> &c, const R qf[9],
+    template <typename R, typename RH, class S>
+    LBM_HD static void put_node(void *lds, int nslot, int slot, const S &c, const R qf[9],
                                 const RH qg[9], const R qh[9], R bf, RH bg, R bh) {
         put_field(lds, nslot, 0, slot, qf, bf, c);
         put_field(lds, nslot, 1, slot, qg, bg, c);
         put_field(lds, nslot, 2, slot, qh, bh, c);
     }
-    template <typename V, typename R>
-    LBM_HD static V get(const void *lds, int nslot, int f, int i, int slot, const CavityConst<R> &c) {
+    template <typename V, class S>
+    LBM_HD static V get(const void *lds, int nslot, int f, int i, int slot, const S &c) {
         const float *P = (const float *)lds;
         if (i == 0) return (V)P[(2 * f) * nslot + slot];
         const V b = (V)P[(2 * f + 1) * nslot + slot];
@@ -1283,6 +1567,7 @@ struct IsSplitLayout<SplitT<ER>> {
 template <class Lay, int TW, int TH, int K>
 struct StepKShape {
     static constexpr int QT = Lay::QT;
+    static constexpr int TILE_W = TW;
     static constexpr int RING = K - 1;          // ring of the first update
     static constexpr int LW = TW + 2 * RING;    // thread map pitch of the first update
     static constexpr int NFIRST = LW * (TH + 2 * RING);  // threads of the first update
@@ -1301,46 +1586,94 @@ struct StepKShape {
     static constexpr int BP = BW;  // row pitch of the staged bases
     static constexpr int NBASE = STAGE_BASE ? BP * BH : 0;   // base plane stride
     static constexpr size_t BASE_BYTES = (size_t)3 * NBASE * sizeof(float);
+    // LDS of a workgroup, and the workgroups of NT threads a CU holds (160
+    // KiB, 32 waves).  The wall tallies move into LDS where that leaves as
+    // many workgroups per CU as without them (all forms but D2Q5 FP32).
+    using R = typename Codec::R;
+    static constexpr size_t total_lds(bool tally) {
+        return LDS_BYTES + NSLOT * sizeof(R) + BASE_BYTES + (tally ? 32 * (TW + TH) : 0);
+    }
+    static constexpr int NT = (NFIRST + 63) / 64 * 64;
+    static constexpr int per_cu(bool tally) {
+        const int a = (int)(160 * 1024 / ((total_lds(tally) + 511) / 512 * 512)), b = 32 / (NT / 64);
+        return a < b ? a : b;
+    }
+    static constexpr bool TILE_TALLY = per_cu(true) == per_cu(false);
     static_assert(TH + 2 * K <= LBM_MIN_BAND_ROWS, "a tile's rows must span at most two bands");
 };
 
 // Global accesses of a tile go through 32-bit offsets from the block of the
 // band of the first row any update touches, y0 - K (the first update's ring
 // and its pulls), clipped to the cavity: at most TH + 2K <= LBM_MIN_BAND_ROWS
-// rows, so at most two bands.
-template <typename R, int K>
-LBM_HD int tile_first_row(const CavityConst<R> &c, const Tile2 &tl) {
-    (void)c;
-    return tl.y0 >= K ? tl.y0 - K : 0;
+// rows, so at most two bands.  edge: some node of the first update's region
+// is a wall node, next to a wall or outside the cavity, or the tile is
+// narrower than TW; a tile without it runs no wall code and no per-node
+// bounds checks (at 8192^2, 99% of the tiles).
+template <typename R>
+struct TileView {
+    View v;
+    Tile2 tl;
+    int ny, yb;        // first row
+    int64_t block;     // byte offset of the block of the first row's band in a state buffer
+    int64_t flat_row;  // flat index of the first row
+    bool edge;
+    const CavityConst<R> &c;
+};
+template <class Sh, typename R>
+LBM_HD TileView<R> tile_view(const CavityConst<R> &c, Tile2 tl) {
+    constexpr int K = Sh::RING + 1, M = Sh::RING + 2;
+    const int yb = tl.y0 >= K ? tl.y0 - K : 0, last = tl.y0 + tl.h - 1 + K;
+    const int ba = band_of(c, yb);
+    const View v = view_of(c, ba, last < c.ny ? last : c.ny - 1);
+    const bool edge = c.periodic || tl.w < Sh::TILE_W || tl.x0 < M || tl.x0 + tl.w > c.nx - M || tl.y0 < M ||
+                      tl.y0 + tl.h > c.ny - M;
+    TileView<R> t{v, tl, c.ny, yb, c.pop_off + (int64_t)ba * c.band_bytes, c.node0 + (int64_t)yb * c.nx, edge, c};
+    resident(t.v.org.y_first), resident(t.v.org.y_next), resident(t.v.org.pitch), resident(t.v.org.band_bytes);
+    resident(t.v.stride), resident(t.v.nx), resident(t.tl.x0), resident(t.tl.y0), resident(t.tl.w), resident(t.tl.h);
+    resident(t.yb), resident(t.block), resident(t.flat_row);
+    return t;
+}
+template <class T, typename R>
+LBM_HD T tally_of(const CavityTally<R> &all, double *lds, const TileView<R> &tv) {
+    if constexpr (std::is_same<T, CavityTally<R>>::value) return all;
+    else return T{all, lds, tv.tl.x0, tv.tl.y0};
+}
+template <typename T>
+LBM_HD Blocks blocks_at(T *buf, int64_t byte) {
+    return blocks_of((const char *)buf + byte);
 }
 
-// LDS slot of the node at unwrapped (x, y) of a tile's K-step sweep.
-template <class Sh>
-LBM_HD int lds_slot(const Tile2 &tl, int x, int y) {
-    return (y - (tl.y0 - Sh::WR)) * Sh::WW + (x - (tl.x0 - Sh::WR));
+// t / P and t % P of a thread index t < 1024.
+template <int P>
+LBM_HD int div_by(int t) {
+    static_assert(P >= 1 && P < 1024, "t times the rounding of 2^20 / P stays below 2^20");
+    return (int)(((uint32_t)t * (uint32_t)(((1 << 20) + P - 1) / P)) >> 20);
+}
+template <int P>
+LBM_HD int mod_by(int t) {
+    return t - div_by<P>(t) * P;
 }
 
-// Push placement: population i of the node at unwrapped (x, y) goes to the
-// slot of x + e_i if that lies in the window; Sr_f to the node's own slot.
+// Push placement: population i of the node at window position (wx, wy) goes
+// to the slot of x + e_i if that lies in the window; Sr_f to the node's own.
 template <class Sh, typename R, typename RH>
-LBM_HD void lds_push(const CavityConst<R> &c, const Tile2 &tl, int x, int y, void *lds_q, R *lds_sr, const R qf[9],
+LBM_HD void lds_push(const NodeConst<R, RH> &n, int wx, int wy, void *lds_q, R *lds_sr, const R qf[9],
                      const RH qg[9], const R qh[9], RH srf) {
     using Cd = typename Sh::Codec;
-    const int wx = x - (tl.x0 - Sh::WR), wy = y - (tl.y0 - Sh::WR);
+    const int own = wy * Sh::WW + wx;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        const int dx = wx + ex_of(i), dy = wy + ey_of(i);
-        if (dx >= 0 && dx < Sh::WW && dy >= 0 && dy < Sh::WH) {
-            const int sl = dy * Sh::WW + dx;
+        if ((unsigned)(wx + ex_of(i)) < (unsigned)Sh::WW && (unsigned)(wy + ey_of(i)) < (unsigned)Sh::WH) {
+            const int sl = own + ey_of(i) * Sh::WW + ex_of(i);
             LBM_HOST_CHECK(sl >= 0 && sl < Sh::NSLOT);
-            Cd::put1(lds_q, Sh::NSLOT, 0, i, sl, qf[i], c);
+            Cd::put1(lds_q, Sh::NSLOT, 0, i, sl, qf[i], n);
             if (i < Sh::QT) {
-                Cd::put1(lds_q, Sh::NSLOT, 1, i, sl, qg[i], c);
-                Cd::put1(lds_q, Sh::NSLOT, 2, i, sl, qh[i], c);
+                Cd::put1(lds_q, Sh::NSLOT, 1, i, sl, qg[i], n);
+                Cd::put1(lds_q, Sh::NSLOT, 2, i, sl, qh[i], n);
             }
         }
     }
-    if (wx >= 0 && wx < Sh::WW && wy >= 0 && wy < Sh::WH) lds_sr[wy * Sh::WW + wx] = (R)srf;
+    if ((unsigned)wx < (unsigned)Sh::WW && (unsigned)wy < (unsigned)Sh::WH) lds_sr[own] = (R)srf;
 }
 
 // Split layouts, before the first update: thread t (of NT) copies the
@@ -1349,57 +1682,51 @@ LBM_HD void lds_push(const CavityConst<R> &c, const Tile2 &tl, int x, int y, voi
 // nodes outside the cavity are skipped, nothing reads them) into three LDS
 // planes of NBASE.
 template <class Lay, typename R, int TW, int TH, int K, int NT>
-LBM_HD void stepk_stage_bases(const CavityConst<R> &c, const Tile2 &tl, const void *src, float *lds_b, int t) {
+LBM_HD void stepk_stage_bases(const TileView<R> &tv, const void *src, float *lds_b, int t) {
     using Sh = StepKShape<Lay, TW, TH, K>;
     static_assert(Sh::STAGE_BASE, "split layouts only");
-    const int yb = tile_first_row<R, K>(c, tl);
-    const BandOrigin org = band_origin(c, yb);
-    const void *blk = band_block(c, src, yb / c.band_rows);
-    const int64_t stride = c.band_nodes;
+    const Tile2 &tl = tv.tl;
+    const Blocks blk = blocks_at(src, tv.block);
     for (int q = t; q < Sh::BP * (tl.h + 2 * K); q += NT) {
         const int bx = q % Sh::BP;
         if (bx >= tl.w + 2 * K) continue;
         const int x = tl.x0 - K + bx, y = tl.y0 - K + q / Sh::BP;  // unwrapped
-        if (y < 0 || y >= c.ny) continue;
+        if (y < 0 || y >= tv.ny) continue;
         int xx = x;
-        if (c.periodic) xx = x < 0 ? x + c.nx : (x >= c.nx ? x - c.nx : x);
-        else if (x < 0 || x >= c.nx) continue;
-        LBM_HOST_CHECK(xx >= 0 && xx < c.nx && q < Sh::NBASE);
-        LBM_HOST_CHECK(y >= yb && y < yb + TH + 2 * K && y < org.y_next + c.band_rows);
-        const NodeRef k = org(xx, y);
+        if (tv.v.periodic) xx = x < 0 ? x + tv.v.nx : (x >= tv.v.nx ? x - tv.v.nx : x);
+        else if (x < 0 || x >= tv.v.nx) continue;
+        LBM_HOST_CHECK(xx >= 0 && xx < tv.v.nx && q < Sh::NBASE);
+        LBM_HOST_CHECK(y >= tv.yb && y < tv.yb + TH + 2 * K && y < tv.v.org.y_next + tv.c.band_rows);
+        const NodeRef k = tv.v.org(xx, y);
 #pragma unroll
-        for (int f = 0; f < 3; ++f) lds_b[f * Sh::NBASE + q] = Lay::load_base(blk, stride, f, k);
+        for (int f = 0; f < 3; ++f)
+            lds_b[f * Sh::NBASE + q] = Lay::pull_base(blk, tv.v.stride, f, Pull{0, k.rel, 0u, k.jump});
     }
 }
 
 // Split layouts, first update: the pulls of the node at unwrapped column x
 // (wrapped xx) or of its wall partner, with the pulled nodes' bases from
-// the staged LDS copy; the same values as gather_at.
-template <class Lay, typename R, typename RH, int TW, int TH, int K>
-LBM_HD void gather_staged(const CavityConst<R> &c, const Tile2 &tl, const void *blk, const NodeGeom &g, int x,
-                          int xx, const BandOrigin &org, const float *lds_b, R qf[9], RH qg[9], R qh[9]) {
-    using Sh = StepKShape<Lay, TW, TH, K>;
-    const int64_t stride = c.band_nodes;
-    const int px = x + (g.sx - xx);  // partner column, unwrapped
-    const NodeRef rows[3] = {org.row(g.sy - 1), org.row(g.sy), org.row(g.sy + 1)};
-#pragma unroll
-    for (int i = 0; i < 9; ++i) {
-        int sx = g.sx - ex_of(i);
-        if (c.periodic) sx = sx < 0 ? sx + c.nx : (sx >= c.nx ? sx - c.nx : sx);
-        const NodeRef k = BandOrigin::at_row(rows[1 - ey_of(i)], sx);
-        if (i == 0) {
-            qf[0] = Lay::template load<R>(blk, stride, 0, 0, k, c);
-            qg[0] = Lay::template load<RH>(blk, stride, 1, 0, k, c);
-            qh[0] = Lay::template load<R>(blk, stride, 2, 0, k, c);
-            continue;
+// the staged LDS copy; the same values as gather_view.
+template <class Sh, class Lay, bool FLAT, typename R, typename RH, int I = 0>
+LBM_HD void pull_staged(const NodeConst<R, RH> &n, const Tile2 &tl, Blocks b, const View &v, const NodeGeom &g, int px,
+                        const float *lds_b, R qf[9], RH qg[9], R qh[9]) {
+    if constexpr (I < 9) {
+        constexpr int K = Sh::RING + 1;
+        const Pull p = pull_of<I>(v, g.sx, g.sy, FLAT);
+        if constexpr (I == 0) {
+            qf[0] = Lay::template pull<R>(b, v.stride, 0, 0, p, n);
+            qg[0] = Lay::template pull<RH>(b, v.stride, 1, 0, p, n);
+            qh[0] = Lay::template pull<R>(b, v.stride, 2, 0, p, n);
+        } else {
+            const int bi = (g.sy - ey_of(I) - (tl.y0 - K)) * Sh::BP + (px - ex_of(I) - (tl.x0 - K));
+            LBM_HOST_CHECK(px - ex_of(I) - (tl.x0 - K) >= 0 && px - ex_of(I) - (tl.x0 - K) < tl.w + 2 * K);
+            LBM_HOST_CHECK(g.sy - ey_of(I) - (tl.y0 - K) >= 0 && g.sy - ey_of(I) - (tl.y0 - K) < tl.h + 2 * K);
+            LBM_HOST_CHECK(bi >= 0 && bi < Sh::NBASE);
+            qf[I] = Lay::template pull_moving<R>(b, v.stride, 0, I, p, (R)lds_b[bi], n);
+            qg[I] = Lay::template pull_moving<RH>(b, v.stride, 1, I, p, (RH)lds_b[Sh::NBASE + bi], n);
+            qh[I] = Lay::template pull_moving<R>(b, v.stride, 2, I, p, (R)lds_b[2 * Sh::NBASE + bi], n);
         }
-        const int bi = (g.sy - ey_of(i) - (tl.y0 - K)) * Sh::BP + (px - ex_of(i) - (tl.x0 - K));
-        LBM_HOST_CHECK(px - ex_of(i) - (tl.x0 - K) >= 0 && px - ex_of(i) - (tl.x0 - K) < tl.w + 2 * K);
-        LBM_HOST_CHECK(g.sy - ey_of(i) - (tl.y0 - K) >= 0 && g.sy - ey_of(i) - (tl.y0 - K) < tl.h + 2 * K);
-        LBM_HOST_CHECK(bi >= 0 && bi < Sh::NBASE);
-        qf[i] = Lay::template load_moving<R>(blk, stride, 0, i, k, (R)lds_b[bi], c);
-        qg[i] = Lay::template load_moving<RH>(blk, stride, 1, i, k, (RH)lds_b[Sh::NBASE + bi], c);
-        qh[i] = Lay::template load_moving<R>(blk, stride, 2, i, k, (R)lds_b[2 * Sh::NBASE + bi], c);
+        pull_staged<Sh, Lay, FLAT, R, RH, I + 1>(n, tl, b, v, g, px, lds_b, qf, qg, qh);
     }
 }
 
@@ -1407,93 +1734,97 @@ LBM_HD void gather_staged(const CavityConst<R> &c, const Tile2 &tl, const void *
 // decode divides by a constant; columns beyond w + 2 RING idle).  Reads the
 // global state (split layouts: with the bases staged in lds_b), writes the
 // slot's post-collision populations and Sr_f to LDS.
-template <class Lay, typename R, typename RH, int TW, int TH, int K>
-LBM_HD void stepk_first(const CavityConst<R> &c, const Tile2 &tl, const void *src,
-                        const R *__restrict__ sr_src, double *__restrict__ acc, void *lds_q, R *lds_sr,
+template <class Lay, typename R, typename RH, int TW, int TH, int K, class Tally>
+LBM_HD void stepk_first(const TileView<R> &tv, const NodeConst<R, RH> &n, const void *src,
+                        const R *__restrict__ sr_src, Tally acc, void *lds_q, R *lds_sr,
                         const float *lds_b, int s) {
     using Sh = StepKShape<Lay, TW, TH, K>;
     constexpr int LW = Sh::LW, RG = Sh::RING;
+    const CavityConst<R> &c = tv.c;
+    const Tile2 &tl = tv.tl;
     LBM_HOST_CHECK(s >= 0 && s < LW * (tl.h + 2 * RG) && s < Sh::NFIRST);
-    const int lx = s % LW, ly = s / LW;
-    if (lx >= tl.w + 2 * RG) return;
+    const int lx = mod_by<LW>(s), ly = div_by<LW>(s);
     const int x = tl.x0 - RG + lx, y = tl.y0 - RG + ly;  // unwrapped
-    if (y < 0 || y >= c.ny) return;
     int xx = x;
-    if (c.periodic) xx = x < 0 ? x + c.nx : (x >= c.nx ? x - c.nx : x);
-    else if (x < 0 || x >= c.nx) return;
+    NodeGeom g{0, x, y};
+    if (tv.edge) {
+        if (lx >= tl.w + 2 * RG) return;
+        if (y < 0 || y >= c.ny) return;
+        if (c.periodic) xx = x < 0 ? x + c.nx : (x >= c.nx ? x - c.nx : x);
+        else if (x < 0 || x >= c.nx) return;
+        g = geometry(c, xx, y, true);
+        if (x >= tl.x0 && x < tl.x0 + tl.w && y >= tl.y0 && y < tl.y0 + tl.h) g.kind |= NODE_OWNED;
+    }
     LBM_HOST_CHECK(xx >= 0 && xx < c.nx);
-    const bool owned = x >= tl.x0 && x < tl.x0 + tl.w && y >= tl.y0 && y < tl.y0 + tl.h;
-    const NodeGeom g = geometry(c, xx, y, true);
-    const int yb = tile_first_row<R, K>(c, tl);
-    const BandOrigin org = band_origin(c, yb);
-    LBM_HOST_CHECK(g.sy - 1 >= yb && g.sy + 1 < yb + TH + 2 * K);
-    LBM_HOST_CHECK(g.sy + 1 < org.y_next + c.band_rows);
+    LBM_HOST_CHECK(tv.edge || (x >= 2 && x <= c.nx - 3 && y >= 2 && y <= c.ny - 3));
+    LBM_HOST_CHECK(g.sy - 1 >= tv.yb && g.sy + 1 < tv.yb + TH + 2 * K);
+    LBM_HOST_CHECK(g.sy + 1 < tv.v.org.y_next + (tv.v.flat ? 0 : c.band_rows));
+    const Blocks b = blocks_at(src, tv.block);
     R qf[9], qh[9];
     RH qg[9];
-    if constexpr (Sh::STAGE_BASE)
-        gather_staged<Lay, R, RH, TW, TH, K>(c, tl, band_block(c, src, yb / c.band_rows), g, x, xx, org, lds_b, qf,
-                                              qg, qh);
-    else
-        gather_at<Lay, R, RH, true>(c, band_block(c, src, yb / c.band_rows), g, xx, y, org, qf, qg, qh);
+    LinkSum ax, ay;  // the tallies so far, read with the populations
+    const bool tx = tv.edge && (g.kind & NODE_OWNED) && g.near_x(), ty = tv.edge && (g.kind & NODE_OWNED) && g.near_y();
+    if constexpr (!std::is_same<Tally, CavityTally<R>>::value) {
+        if (tx) ax = LinkSum{acc.all.column(x == 1, y)[0], acc.all.column(x == 1, y)[1]};
+        if (ty) ay = LinkSum{acc.all.row(y == 1, x)[0], acc.all.row(y == 1, x)[1]};
+    }
+    if constexpr (Sh::STAGE_BASE) {
+        const int px = x + (g.sx - xx);  // partner column, unwrapped
+        if (tv.v.flat) pull_staged<Sh, Lay, true, R, RH>(n, tl, b, tv.v, g, px, lds_b, qf, qg, qh);
+        else pull_staged<Sh, Lay, false, R, RH>(n, tl, b, tv.v, g, px, lds_b, qf, qg, qh);
+    } else {
+        gather_view<Lay, R, RH, true>(n, b, tv.v, g, qf, qg, qh);
+    }
     (void)lds_b;
+    if constexpr (!std::is_same<Tally, CavityTally<R>>::value) {
+        if (tx) acc.column(x == 1, y)[0] = ax.E, acc.column(x == 1, y)[1] = ax.M;
+        if (ty) acc.row(y == 1, x)[0] = ay.E, acc.row(y == 1, x)[1] = ay.M;
+    }
     Thermo<RH> th;
     Macro<R> m;
-    const R sr_prev = sr_src[flat_index(c, xx, y)];
-    const RH srf = update_node<Sh::QT, R, RH, true>(c, g, xx, y, qf, qg, qh, sr_prev, owned, acc, th, m);
+    const R sr_prev = ld_block<R>(blocks_at(sr_src + tv.flat_row, 0), 0, (uint32_t)((y - tv.yb) * tv.v.nx + xx) * sizeof(R), 0);
+    const RH srf =
+        update_node<Sh::QT, R, RH, true>(c, n, tv.edge, g, xx, y, qf, qg, qh, sr_prev, g.kind & NODE_OWNED, acc, th, m);
     if constexpr (Sh::PUSH) {
-        lds_push<Sh, R, RH>(c, tl, x, y, lds_q, lds_sr, qf, qg, qh, srf);
+        lds_push<Sh, R, RH>(n, lx - RG + Sh::WR, ly - RG + Sh::WR, lds_q, lds_sr, qf, qg, qh, srf);
     } else {
-        const ThermalConst<RH> &t = thermal<RH>(c);
-        Sh::Codec::put_node(lds_q, Sh::NSLOT, s, c, qf, qg, qh, m.drho, t.c_fref * (th.Tf - t.T_ref),
-                            c.c_mref * m.dTm);
+        Sh::Codec::put_node(lds_q, Sh::NSLOT, s, n, qf, qg, qh, m.drho, n.cf_base * (th.Tf - n.Tf_ref),
+                            n.cm_base * m.dTm);
         lds_sr[s] = (R)srf;
     }
 }
 
-// A node's pulls from LDS: the slots of the neighbours of the node (or of
-// its wall partner), in unwrapped coordinates.  x is the node's unwrapped
-// column, xx the wrapped one.
+// A node's pulls from LDS; slot is that of the node or of its wall partner.
 template <class Sh, typename R, typename RH>
-LBM_HD void lds_gather(const CavityConst<R> &c, const Tile2 &tl, const NodeGeom &g, int x, int xx, int h_region,
-                       const void *lds_q, R qf[9], RH qg[9], R qh[9]) {
+LBM_HD void lds_gather(const NodeConst<R, RH> &n, int slot, const void *lds_q, R qf[9], RH qg[9], R qh[9]) {
     using Cd = typename Sh::Codec;
-    const int px = x + (g.sx - xx);  // partner column, unwrapped
-    if constexpr (Sh::PUSH) {
-        // every pull of the node (or of its partner) sits in its own slot
-        const int sl = lds_slot<Sh>(tl, px, g.sy);
-        LBM_HOST_CHECK(px - (tl.x0 - Sh::WR) >= 0 && px - (tl.x0 - Sh::WR) < Sh::WW);
-        LBM_HOST_CHECK(g.sy - (tl.y0 - Sh::WR) >= 0 && g.sy - (tl.y0 - Sh::WR) < Sh::WH);
-        LBM_HOST_CHECK(sl >= 0 && sl < Sh::NSLOT);
-        (void)h_region;
-#pragma unroll
-        for (int i = 0; i < 9; ++i) {
-            qf[i] = Cd::template get<R>(lds_q, Sh::NSLOT, 0, i, sl, c);
-            if (i < Sh::QT) {
-                qg[i] = Cd::template get<RH>(lds_q, Sh::NSLOT, 1, i, sl, c);
-                qh[i] = Cd::template get<R>(lds_q, Sh::NSLOT, 2, i, sl, c);
-            } else {
-                qg[i] = RH(0);
-                qh[i] = R(0);
-            }
-        }
-        return;
-    }
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
-        const int sl = lds_slot<Sh>(tl, px - ex_of(i), g.sy - ey_of(i));
-        LBM_HOST_CHECK(px - ex_of(i) - (tl.x0 - Sh::RING) >= 0 && px - ex_of(i) - (tl.x0 - Sh::RING) < Sh::LW);
-        LBM_HOST_CHECK(g.sy - ey_of(i) - (tl.y0 - Sh::RING) >= 0 &&
-                       g.sy - ey_of(i) - (tl.y0 - Sh::RING) < h_region);
+        // push placement: every pull of a node sits in its own slot
+        const int sl = Sh::PUSH ? slot : slot - ey_of(i) * Sh::WW - ex_of(i);
         LBM_HOST_CHECK(sl >= 0 && sl < Sh::NSLOT);
-        qf[i] = Cd::template get<R>(lds_q, Sh::NSLOT, 0, i, sl, c);
+        qf[i] = Cd::template get<R>(lds_q, Sh::NSLOT, 0, i, sl, n);
         if (i < Sh::QT) {
-            qg[i] = Cd::template get<RH>(lds_q, Sh::NSLOT, 1, i, sl, c);
-            qh[i] = Cd::template get<R>(lds_q, Sh::NSLOT, 2, i, sl, c);
+            qg[i] = Cd::template get<RH>(lds_q, Sh::NSLOT, 1, i, sl, n);
+            qh[i] = Cd::template get<R>(lds_q, Sh::NSLOT, 2, i, sl, n);
         } else {
             qg[i] = RH(0);
             qh[i] = R(0);
         }
     }
+}
+// The slot a node pulls through: its own, or its wall partner's (edge tiles).
+// x is the node's unwrapped column, xx the wrapped one.
+template <class Sh>
+LBM_HD int pull_slot(const Tile2 &tl, const NodeGeom &g, int x, int xx, int own, int y) {
+    const int slot = own + (g.sy - y) * Sh::WW + (g.sx - xx);
+    const int wx = x + (g.sx - xx) - (tl.x0 - Sh::WR), wy = g.sy - (tl.y0 - Sh::WR);
+    (void)wx;
+    (void)wy;
+    // the partner itself (push), or its neighbours too (pull), lie in the window
+    LBM_HOST_CHECK(wx >= (Sh::PUSH ? 0 : 1) && wx < Sh::WW - (Sh::PUSH ? 0 : 1));
+    LBM_HOST_CHECK(wy >= (Sh::PUSH ? 0 : 1) && wy < tl.h + 2 * Sh::WR - (Sh::PUSH ? 0 : 1));
+    return slot;
 }
 
 // A middle update of ring j (1 <= j <= K - 2), split at the barrier that
@@ -1502,79 +1833,124 @@ LBM_HD void lds_gather(const CavityConst<R> &c, const Tile2 &tl, const NodeGeom 
 // node and writes its own slot.
 template <typename R, typename RH>
 struct MidNode {
-    int x, xx, y, slot;
-    bool owned;
+    int lx, ly, xx, y, slot;
     NodeGeom g;
     R qf[9], qh[9], sr_prev;
     RH qg[9];
 };
-template <class Lay, typename R, typename RH, int TW, int TH, int K>
-LBM_HD bool stepk_mid_load(const CavityConst<R> &c, const Tile2 &tl, int j, const void *lds_q, const R *lds_sr,
-                           int t, MidNode<R, RH> &n) {
+template <class Lay, typename R, typename RH, int TW, int TH, int K, int J>
+LBM_HD bool stepk_mid_load(const TileView<R> &tv, const NodeConst<R, RH> &n, const void *lds_q, const R *lds_sr, int t,
+                           MidNode<R, RH> &q) {
     using Sh = StepKShape<Lay, TW, TH, K>;
-    const int pw = TW + 2 * j;  // pitch of ring j's thread map
-    const int lx = t % pw, ly = t / pw;
-    if (lx >= tl.w + 2 * j || ly >= tl.h + 2 * j) return false;
-    n.x = tl.x0 - j + lx;
-    n.y = tl.y0 - j + ly;  // unwrapped
-    if (n.y < 0 || n.y >= c.ny) return false;
-    n.xx = n.x;
-    if (c.periodic) n.xx = n.x < 0 ? n.x + c.nx : (n.x >= c.nx ? n.x - c.nx : n.x);
-    else if (n.x < 0 || n.x >= c.nx) return false;
-    LBM_HOST_CHECK(n.xx >= 0 && n.xx < c.nx);
-    n.owned = n.x >= tl.x0 && n.x < tl.x0 + tl.w && n.y >= tl.y0 && n.y < tl.y0 + tl.h;
-    n.g = geometry(c, n.xx, n.y, true);
-    n.slot = lds_slot<Sh>(tl, n.x, n.y);
-    LBM_HOST_CHECK(n.slot >= 0 && n.slot < Sh::NSLOT);
-    lds_gather<Sh, R, RH>(c, tl, n.g, n.x, n.xx, tl.h + 2 * Sh::RING, lds_q, n.qf, n.qg, n.qh);
-    n.sr_prev = lds_sr[n.slot];
+    constexpr int P = TW + 2 * J;  // pitch of ring J's thread map
+    const CavityConst<R> &c = tv.c;
+    const Tile2 &tl = tv.tl;
+    q.lx = mod_by<P>(t);
+    q.ly = div_by<P>(t);
+    const int x = tl.x0 - J + q.lx, y = tl.y0 - J + q.ly;  // unwrapped
+    q.xx = x;
+    q.y = y;
+    q.g = NodeGeom{0, x, y};
+    q.slot = P == Sh::WW ? t : (q.ly + Sh::WR - J) * Sh::WW + q.lx + Sh::WR - J;
+    int from = q.slot;
+    if (tv.edge) {
+        if (q.lx >= tl.w + 2 * J) return false;
+        if (y < 0 || y >= c.ny) return false;
+        if (c.periodic) q.xx = x < 0 ? x + c.nx : (x >= c.nx ? x - c.nx : x);
+        else if (x < 0 || x >= c.nx) return false;
+        q.g = geometry(c, q.xx, y, true);
+        if (x >= tl.x0 && x < tl.x0 + tl.w && y >= tl.y0 && y < tl.y0 + tl.h) q.g.kind |= NODE_OWNED;
+        from = pull_slot<Sh>(tl, q.g, x, q.xx, q.slot, y);
+    }
+    LBM_HOST_CHECK(q.ly < tl.h + 2 * J && q.xx >= 0 && q.xx < c.nx);
+    LBM_HOST_CHECK(q.slot >= 0 && q.slot < Sh::NSLOT);
+    lds_gather<Sh, R, RH>(n, from, lds_q, q.qf, q.qg, q.qh);
+    q.sr_prev = lds_sr[q.slot];
     return true;
 }
-template <class Lay, typename R, typename RH, int TW, int TH, int K>
-LBM_HD void stepk_mid_store(const CavityConst<R> &c, const Tile2 &tl, double *__restrict__ acc, void *lds_q,
-                            R *lds_sr, MidNode<R, RH> &n) {
+template <class Lay, typename R, typename RH, int TW, int TH, int K, int J, class Tally>
+LBM_HD void stepk_mid_store(const TileView<R> &tv, const NodeConst<R, RH> &n, Tally acc, void *lds_q,
+                            R *lds_sr, MidNode<R, RH> &q) {
     using Sh = StepKShape<Lay, TW, TH, K>;
     Thermo<RH> th;
     Macro<R> m;
-    const RH srf = update_node<Sh::QT, R, RH, true>(c, n.g, n.xx, n.y, n.qf, n.qg, n.qh, n.sr_prev, n.owned, acc,
-                                                   th, m);
+    const RH srf = update_node<Sh::QT, R, RH, true>(tv.c, n, tv.edge, q.g, q.xx, q.y, q.qf, q.qg, q.qh, q.sr_prev,
+                                                   q.g.kind & NODE_OWNED, acc, th, m);
     if constexpr (Sh::PUSH) {
-        lds_push<Sh, R, RH>(c, tl, n.x, n.y, lds_q, lds_sr, n.qf, n.qg, n.qh, srf);
+        lds_push<Sh, R, RH>(n, q.lx - J + Sh::WR, q.ly - J + Sh::WR, lds_q, lds_sr, q.qf, q.qg, q.qh, srf);
     } else {
-        const ThermalConst<RH> &t = thermal<RH>(c);
-        Sh::Codec::put_node(lds_q, Sh::NSLOT, n.slot, c, n.qf, n.qg, n.qh, m.drho, t.c_fref * (th.Tf - t.T_ref),
-                            c.c_mref * m.dTm);
-        lds_sr[n.slot] = (R)srf;
+        Sh::Codec::put_node(lds_q, Sh::NSLOT, q.slot, n, q.qf, q.qg, q.qh, m.drho, n.cf_base * (th.Tf - n.Tf_ref),
+                            n.cm_base * m.dTm);
+        lds_sr[q.slot] = (R)srf;
     }
 }
 
-// Last update: node n of the tile (row-major with pitch TW; columns beyond
+// Last update: node s of the tile (row-major with pitch TW; columns beyond
 // w idle).  Pulls from LDS, writes the global state.
-template <class Lay, typename R, typename RH, int TW, int TH, int K>
-LBM_HD void stepk_last(const CavityConst<R> &c, const Tile2 &tl, void *dst, R *__restrict__ sr_dst,
-                       double *__restrict__ acc, const void *lds_q, const R *lds_sr, int n) {
+template <class Lay, typename R, typename RH, int TW, int TH, int K, class Tally>
+LBM_HD void stepk_last(const TileView<R> &tv, const NodeConst<R, RH> &n, void *dst,
+                       R *__restrict__ sr_dst, Tally acc, const void *lds_q, const R *lds_sr, int s) {
     using Sh = StepKShape<Lay, TW, TH, K>;
-    LBM_HOST_CHECK(n >= 0 && n < TW * tl.h);
-    if (n % TW >= tl.w) return;
-    const int x = tl.x0 + n % TW, y = tl.y0 + n / TW;
+    const CavityConst<R> &c = tv.c;
+    const Tile2 &tl = tv.tl;
+    LBM_HOST_CHECK(s >= 0 && s < TW * tl.h);
+    const int lx = mod_by<TW>(s), ly = div_by<TW>(s);
+    const int x = tl.x0 + lx, y = tl.y0 + ly;
+    const int own = (ly + Sh::WR) * Sh::WW + lx + Sh::WR;
+    int from = own;
+    NodeGeom g{0, x, y};
+    if (tv.edge) {
+        if (lx >= tl.w) return;
+        g = geometry(c, x, y, true);
+        from = pull_slot<Sh>(tl, g, x, x, own, y);
+    }
     LBM_HOST_CHECK(x >= 0 && x < c.nx && y >= 0 && y < c.ny);
-    const NodeGeom g = geometry(c, x, y, true);
     R qf[9], qh[9];
     RH qg[9];
-    lds_gather<Sh, R, RH>(c, tl, g, x, x, tl.h + 2 * Sh::RING, lds_q, qf, qg, qh);
-    const int self = lds_slot<Sh>(tl, x, y);
-    const int yb = tile_first_row<R, K>(c, tl);
-    const NodeRef k = band_origin(c, yb)(x, y);
-    void *blk = band_block(c, dst, yb / c.band_rows);
+    lds_gather<Sh, R, RH>(n, from, lds_q, qf, qg, qh);
     Thermo<RH> th;
     Macro<R> m;
-    const RH srf = update_node<Sh::QT, R, RH, true>(c, g, x, y, qf, qg, qh, lds_sr[self], true, acc, th, m);
-    const ThermalConst<RH> &t = thermal<RH>(c);
-    const int64_t stride = c.band_nodes;
-    Lay::template store<R>(blk, stride, 0, qf, m.drho, k, c);
-    Lay::template store<RH>(blk, stride, 1, qg, t.c_fref * (th.Tf - t.T_ref), k, c);
-    Lay::template store<R>(blk, stride, 2, qh, c.c_mref * m.dTm, k, c);
-    sr_dst[flat_index(c, x, y)] = (R)srf;
+    const RH srf =
+        update_node<Sh::QT, R, RH, true>(c, n, tv.edge, g, x, y, qf, qg, qh, lds_sr[own], true, acc, th, m);
+    const NodeRef k = tv.v.org(x, y);
+    const Blocks b = blocks_at(dst, tv.block);
+    Lay::template put<R>(b, tv.v.stride, 0, qf, m.drho, k, n);
+    Lay::template put<RH>(b, tv.v.stride, 1, qg, n.cf_base * (th.Tf - n.Tf_ref), k, n);
+    Lay::template put<R>(b, tv.v.stride, 2, qh, n.cm_base * m.dTm, k, n);
+    *(R *)((char *)(sr_dst + tv.flat_row) + (uint32_t)((y - tv.yb) * tv.v.nx + x) * (uint32_t)sizeof(R)) = (R)srf;
+}
+
+// The same from the cavity's table and a tile (host builds).
+template <class Lay, typename R, int TW, int TH, int K, int NT>
+LBM_HD void stepk_stage_bases(const CavityConst<R> &c, const Tile2 &tl, const void *src, float *lds_b, int t) {
+    stepk_stage_bases<Lay, R, TW, TH, K, NT>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl), src, lds_b, t);
+}
+template <class Lay, typename R, typename RH, int TW, int TH, int K>
+LBM_HD void stepk_first(const CavityConst<R> &c, const Tile2 &tl, const void *src, const R *__restrict__ sr_src,
+                        double *__restrict__ acc, void *lds_q, R *lds_sr, const float *lds_b, int s) {
+    stepk_first<Lay, R, RH, TW, TH, K>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl), node_const_of<RH>(c), src, sr_src,
+                                       CavityTally<R>{acc, c}, lds_q, lds_sr, lds_b, s);
+}
+template <class Lay, typename R, typename RH, int TW, int TH, int K>
+LBM_HD bool stepk_mid_load(const CavityConst<R> &c, const Tile2 &tl, int j, const void *lds_q, const R *lds_sr, int t,
+                           MidNode<R, RH> &q) {
+    static_assert(K <= 3, "one middle update");
+    LBM_HOST_CHECK(j == 1);
+    (void)j;
+    return stepk_mid_load<Lay, R, RH, TW, TH, K, 1>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl),
+                                                    node_const_of<RH>(c), lds_q, lds_sr, t, q);
+}
+template <class Lay, typename R, typename RH, int TW, int TH, int K>
+LBM_HD void stepk_mid_store(const CavityConst<R> &c, const Tile2 &tl, double *__restrict__ acc, void *lds_q, R *lds_sr,
+                            MidNode<R, RH> &q) {
+    stepk_mid_store<Lay, R, RH, TW, TH, K, 1>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl), node_const_of<RH>(c), CavityTally<R>{acc, c},
+                                              lds_q, lds_sr, q);
+}
+template <class Lay, typename R, typename RH, int TW, int TH, int K>
+LBM_HD void stepk_last(const CavityConst<R> &c, const Tile2 &tl, void *dst, R *__restrict__ sr_dst,
+                       double *__restrict__ acc, const void *lds_q, const R *lds_sr, int s) {
+    stepk_last<Lay, R, RH, TW, TH, K>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl), node_const_of<RH>(c), dst, sr_dst,
+                                      CavityTally<R>{acc, c}, lds_q, lds_sr, s);
 }
 
 // Macroscopic fields of one node (post-streaming state) plus its
@@ -1593,7 +1969,7 @@ LBM_HD void macro_node(const CavityConst<R> &c, const void *src, bool raw, int x
     for (int i = 0; i < 9; ++i)
         finite = finite && isfinite(qf[i]) && (i >= Lay::QT || (isfinite(qg[i]) && isfinite(qh[i])));
     // inflow of the last step through the wall links (not yet tallied)
-    if (!raw && !g.wall) {
+    if (!raw && !g.wall()) {
 #pragma unroll
         for (int i = 1; i < 9; ++i) {
             const int px = x - ex_of(i), py = y - ey_of(i);
@@ -1614,7 +1990,8 @@ LBM_HD void macro_node(const CavityConst<R> &c, const void *src, bool raw, int x
             }
         }
     }
-    if (!raw && g.wall) reconstruct_wall<Lay::QT>(c, x, y, qf, qg, qh);
+    const NodeConst<R, RH> &n = node_const_of<RH>(c);
+    if (!raw && g.wall()) reconstruct_wall<Lay::QT>(c, n, x, y, qf, qg, qh);
     double sg = 0.0, sh = 0.0, sf = 0.0;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {
@@ -1626,7 +2003,7 @@ LBM_HD void macro_node(const CavityConst<R> &c, const void *src, bool raw, int x
     }
     Thermo<RH> th;
     Macro<R> m;
-    macros<Lay::QT>(c, qf, qg, qh, th, m);
+    macros<Lay::QT>(n, qf, qg, qh, th, m);
     out[0] = (double)m.ux;
     out[1] = (double)m.uy;
     out[2] = (double)th.Tf;
@@ -1634,7 +2011,7 @@ LBM_HD void macro_node(const CavityConst<R> &c, const void *src, bool raw, int x
     out[4] = (double)th.fl;
     out[5] = (double)m.rho;
     if (!finite) v[P_NF] = 1.0;
-    if (!g.wall) {
+    if (!g.wall()) {
         v[P_FL] = (double)th.fl;
         // phi rho_l H + (1-phi) rho_m c_pm T_m and rho, from the offsets
         v[P_E] = c.we * sg + c.wm * sh;
@@ -1656,12 +2033,12 @@ LBM_HD void init_node(const CavityConst<R> &c, void *dst, R *sr, int x, int y, d
     if (w >= 0) Tf = Tm = t.T_wall[w];
     // inverse of Eq. (38) (a tie at the solidus goes to the solid branch)
     double H;
-    if (Tf <= t.T_fs) H = Tf / t.inv_cps;
-    else if (Tf >= t.T_fl) H = (Tf - t.T_fl) / t.inv_cpl + t.H_fl;
+    if (Tf <= t.T_fs) H = Tf;
+    else if (Tf >= t.T_fl) H = (Tf - t.T_fl) + t.H_fl;
     else H = t.H_fs + (Tf - t.T_fs) / (t.T_fl - t.T_fs) * (t.H_fl - t.H_fs);
     const double dT = Tf - t.T_ref, dTm = Tm - t.T_ref;
     const double dH = H - t.H_ref;
-    const double cf = t.c_fref, cm = c.c_mref, cpm = c.c_pm;
+    const double cf = t.c_fref, cm = c.c_mref;
     // equilibria at rest, Eqs. (40), (49) / Eqs. (B3), (B5): the moving
     // weights are w_i (D2Q9) or varpi/4 (D2Q5), the rest one takes the rest
     const int QT = Lay::QT;
@@ -1673,7 +2050,7 @@ LBM_HD void init_node(const CavityConst<R> &c, void *dst, R *sr, int x, int y, d
         const double wi = QT == 9 ? w_of<double>(i) : 0.25 * t.varpi;
         qf[i] = R(0);
         qg[i] = (RH)(i == 0 ? dH - wrest * cf * dT : wi * cf * dT);
-        qh[i] = (R)(i == 0 ? (cpm - wrest * cm) * dTm : wi * cm * dTm);
+        qh[i] = (R)(i == 0 ? (1.0 - wrest * cm) * dTm : wi * cm * dTm);
     }
     const FarRef k = any_band(c)(x, y);
     void *blk = band_block(c, dst, 0);
@@ -1681,7 +2058,7 @@ LBM_HD void init_node(const CavityConst<R> &c, void *dst, R *sr, int x, int y, d
     Lay::template store<R>(blk, stride, 0, qf, R(0), k, c);
     Lay::template store<RH>(blk, stride, 1, qg, (RH)(cf * dT), k, c);
     Lay::template store<R>(blk, stride, 2, qh, (R)(cm * dTm), k, c);
-    sr[flat_index(c, x, y)] = (R)((double)c.hv_f * (Tm - Tf));
+    sr[flat_index(c, x, y)] = (R)(c.hv_f * (Tm - Tf));
 }
 
 }  // namespace lbm

@@ -192,7 +192,8 @@ inline lbm_status map_params(const lbm_params &p, lbm_precision prec, Lattice &l
     const double ze = p.zeta_e > 0 ? p.zeta_e : 2.0 - za;
     l.zeta_a = za;
     l.eta_a = ea;
-    const double s[9] = {1.0, 1.1, 1.1, 1.0, 1.2, 1.0, 1.2, s_v, s_v};
+    double s[9];
+    for (int k = 0; k < 9; ++k) s[k] = k < 7 ? kFlowRate[k] : s_v;
     double zt[9], et[9];
     if (p.thermal_collision == 1) {
         for (int k = 0; k < 9; ++k) {
@@ -269,17 +270,8 @@ ThermalConst<T> make_thermal(const Lattice &l) {
     t.H_fl = (T)l.H_fl;
     t.T_fs = (T)l.T_fs;
     t.T_fl = (T)l.T_fl;
-    t.inv_dH = (T)(1.0 / (l.H_fl - l.H_fs));
-    t.dT_band = (T)(l.T_fl - l.T_fs);
-    t.inv_cps = (T)(1.0 / l.c_ps);
-    t.inv_cpl = (T)(1.0 / l.c_pl);
-    t.c_pl = (T)l.c_pl;
     t.c_fref = (T)l.c_fref;
     t.inv_phi = (T)(1.0 / l.phi);
-    for (int k = 0; k < 9; ++k) {
-        t.zA[k] = (T)((1.0 - l.zeta[k]) * thermal_factor(l, k));
-        t.zB[k] = (T)(l.zeta[k] * thermal_factor(l, k));
-    }
     t.varpi = (T)l.varpi;
     t.inv_cs2 = (T)(l.qt == 9 ? 3.0 : 2.0 / l.varpi);
     t.T_ref = (T)l.T_ref;
@@ -289,6 +281,79 @@ ThermalConst<T> make_thermal(const Lattice &l) {
         t.H_wall[w] = (T)enthalpy_of(l, l.wall_T[w]);
     }
     return t;
+}
+
+template <typename R, typename RH>
+NodeConst<R, RH> make_node_const(const Lattice &l) {
+    using RG = typename NodeConst<R, RH>::RG;
+    NodeConst<R, RH> n;
+    std::memset(&n, 0, sizeof(n));
+    n.H_ref = (RH)l.H_ref;
+    n.H_fs = (RH)l.H_fs;
+    n.H_fl = (RH)l.H_fl;
+    n.T_fs = (RH)l.T_fs;
+    n.T_fl = (RH)l.T_fl;
+    n.inv_dH = (RH)(1.0 / (l.H_fl - l.H_fs));
+    n.dT_band = (RH)(l.T_fl - l.T_fs);
+    n.Tf_ref = (RH)l.T_ref;
+    const double hvf = l.h_v / (l.phi * l.rho_l), hvm = l.h_v / ((1.0 - l.phi) * l.rho_m);
+    n.hv_f = (RH)(R)hvf;
+    n.hv_m = (R)hvm;
+    n.sr_ratio = (R)((l.phi * l.rho_l) / ((1.0 - l.phi) * l.rho_m));
+    n.gbeta = (R)l.gbeta;
+    n.T0 = (R)l.T0;
+    n.px = l.gaxis == 0 ? (R)l.phi : R(0);
+    n.py = l.gaxis == 1 ? (R)l.phi : R(0);
+    n.inv_phi = (R)(1.0 / l.phi);
+    const double dl = l.phi * l.nu_f / l.K;              // phi nu_f / K
+    const double dq = l.phi * l.F_phi / std::sqrt(l.K);  // phi F_phi / sqrt(K)
+    const double l0 = 0.5 * (1.0 + 0.5 * dl);            // Eq. (25)
+    n.drag_lin = (R)dl;
+    n.drag_quad = (R)dq;
+    n.l0 = (R)l0;
+    n.l0sq = (R)(l0 * l0);
+    n.l1 = (R)(0.5 * dq);
+    n.fA7 = (R)((1.0 - l.s[7]) * row_norm(7));
+    n.fB7 = (R)(l.s[7] * row_norm(7));
+    n.fC7 = (R)((1.0 - 0.5 * l.s[7]) * row_norm(7));
+    const double *e = l.eta, *z = l.zeta;
+    auto g = [&](int k) { return thermal_factor(l, k); };
+    n.T_ref = (R)l.T_ref;
+    n.mA0 = (R)((1.0 - e[0]) * g(0));
+    n.mB0 = (R)(e[0] * g(0));
+    n.mA1 = (R)((1.0 - e[1]) * g(1));
+    n.mB1 = (R)(e[1] * g(1));
+    n.mA3 = (R)((1.0 - e[3]) * g(3));
+    n.mB3 = (R)(e[3] * g(3));
+    n.mA4 = (R)((1.0 - e[4]) * g(4));
+    n.mA7 = (R)((1.0 - e[7]) * g(7));
+    n.zA1 = (RG)((1.0 - z[1]) * g(1));
+    n.zB1 = (RG)(z[1] * g(1));
+    n.zA3 = (RG)((1.0 - z[3]) * g(3));
+    n.zB3 = (RG)(z[3] * g(3));
+    n.zA4 = (RG)((1.0 - z[4]) * g(4));
+    n.zB4 = (RG)(z[4] * g(4));
+    n.zA7 = (RG)((1.0 - z[7]) * g(7));
+    const RG cf = (RG)l.c_fref, vg = (RG)l.varpi;
+    const R cm = (R)l.c_mref, vr = (R)l.varpi;
+    if (l.qt == 9) {
+        n.ge1 = RG(2) * cf;
+        n.ge2 = RG(3) * cf;
+        n.me1 = R(-4) + R(2) * cm;
+        n.me2 = R(4) - R(3) * cm;
+    } else {
+        n.ge1 = vg * cf;
+        n.me1 = vr * cm;
+        n.w4 = vr * R(0.25);
+    }
+    n.cf_base = (RH)l.c_fref;
+    n.cm_base = (R)l.c_mref;
+    n.bounce_back = l.solid;
+    for (int f = 0; f < 3; ++f) {
+        n.scale[f] = (R)std::ldexp(1.0, l.scale_exp[f]);
+        n.inv_scale[f] = (R)std::ldexp(1.0, -l.scale_exp[f]);
+    }
+    return n;
 }
 
 // Banded placement of one cavity's populations in a state buffer.
@@ -326,51 +391,29 @@ CavityConst<R> make_const(const Lattice &l, int64_t node0, int64_t acc0, const B
     c.nx = l.nx;
     c.ny = l.ny;
     c.periodic = l.periodic;
-    c.gaxis = l.gaxis;
     c.node0 = node0;
     c.acc0 = acc0;
     c.band_rows = bd.rows;
+    c.band_recip = (uint32_t)((((uint64_t)1 << 32) + bd.rows - 1) / bd.rows);
     c.pitch = bd.pitch;
     c.band_nodes = bd.nodes;
     c.band_bytes = bd.bytes;
     c.pop_off = bd.off;
-    c.phi = (R)l.phi;
     c.inv_phi = (R)(1.0 / l.phi);
-    c.inv_cpm = (R)(1.0 / l.c_pm);
-    c.c_pm = (R)l.c_pm;
     c.c_mref = (R)l.c_mref;
-    for (int k = 0; k < 9; ++k) {
-        c.fA[k] = (R)((1.0 - l.s[k]) * row_norm(k));
-        c.fB[k] = (R)(l.s[k] * row_norm(k));
-        c.fC[k] = (R)((1.0 - 0.5 * l.s[k]) * row_norm(k));
-        c.mA[k] = (R)((1.0 - l.eta[k]) * thermal_factor(l, k));
-        c.mB[k] = (R)(l.eta[k] * thermal_factor(l, k));
-    }
-    c.gbeta = (R)l.gbeta;
-    c.T0 = (R)l.T0;
-    const double dl = l.phi * l.nu_f / l.K;             // phi nu_f / K
-    const double dq = l.phi * l.F_phi / std::sqrt(l.K);  // phi F_phi / sqrt(K)
-    c.drag_lin = (R)dl;
-    c.drag_quad = (R)dq;
-    const double l0 = 0.5 * (1.0 + 0.5 * dl);          // Eq. (25)
-    c.l0 = (R)l0;
-    c.l0sq = (R)(l0 * l0);
-    c.l1 = (R)(0.5 * dq);
-    const double hvf = l.h_v / (l.phi * l.rho_l), hvm = l.h_v / ((1.0 - l.phi) * l.rho_m);
-    c.hv_f = (R)hvf;
-    c.hv_m = (R)hvm;
-    c.sr_ratio = (R)((l.phi * l.rho_l) / ((1.0 - l.phi) * l.rho_m));
+    c.hv_f = (double)(R)(l.h_v / (l.phi * l.rho_l));
     c.T_ref = (R)l.T_ref;
     c.varpi = (R)l.varpi;
     for (int w = 0; w < 4; ++w) {
         c.T_wall[w] = (R)l.wall_T[w];
         c.wall_iso[w] = l.wall_type[w] == 1 ? 1 : 0;
     }
-    c.bounce_back = l.solid;
     for (int f = 0; f < 3; ++f) {
         c.scale[f] = (R)std::ldexp(1.0, l.scale_exp[f]);
         c.inv_scale[f] = (R)std::ldexp(1.0, -l.scale_exp[f]);
     }
+    c.nr = make_node_const<R, R>(l);
+    c.nd = make_node_const<R, double>(l);
     c.tf = make_thermal<float>(l);
     c.td = make_thermal<double>(l);
     c.we = l.phi * l.rho_l;
