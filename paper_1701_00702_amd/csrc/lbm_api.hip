@@ -369,6 +369,7 @@ Step2Launch stepk_args(lbm_handle *h, int k, int src_buf, double *acc, const lbm
     L.shape = h->shapek[k];
     const int nt = h->ntk[k];
     L.grid = lc.persistent > 0 ? std::min(nt, h->n_cu * lc.persistent) : nt;
+    L.n_cu = h->n_cu;
     L.xcd_remap = lc.xcd_remap;
     L.src = h->pop(src_buf);
     L.dst = h->pop(1 - src_buf);

@@ -163,7 +163,7 @@ struct Step2Launch {
     int storage;
     int steps;  // K: 2 or 3 steps per launch
     int shape;  // tile shape index (0 default; see stepk_tile)
-    int grid, xcd_remap;
+    int grid, xcd_remap, n_cu;
     const void *src;
     void *dst;
     const void *sr_src;

@@ -189,6 +189,71 @@ hipError_t launch_step(const StepLaunch &L, hipStream_t s) {
 // four workgroups share a CU, whose waves overlap one tile's loads with
 // another's arithmetic.  Two-step tiles first.
 // ---------------------------------------------------------------------------
+// Brings the rows a tile will be the first to read into the XCD's L2: item q
+// of NP planes of elements of ES bytes from byte `plane0` on (stride nodes
+// apart), TH rows each, one load per 128-byte line.  v receives the loads.
+template <int ES, int NP, int TW, int TH, int NT, int N>
+__device__ __forceinline__ void touch_lines(Blocks b, const BandOrigin &org, uint32_t stride, uint32_t plane0, int x0,
+                                            int x1, int y0, int y1, int t, uint32_t (&v)[N]) {
+    constexpr int EL = 128 / ES, LINES = (TW + EL - 1) / EL;  // elements per line, lines per row
+    static_assert(N * NT >= NP * TH * LINES, "one load per item");
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int q = t + k * NT, line = q % LINES, row = (q / LINES) % TH, p = q / (LINES * TH);
+        const int x = x0 + line * EL, y = y0 + row;
+        v[k] = 0;
+        if (p < NP && x < x1 && y < y1) {
+            const NodeRef r = org(x, y);
+            v[k] = ld_block<uint32_t>(b, plane0, ((p * stride + r.rel) * ES + r.jump) & ~3u, 0);
+        }
+    }
+}
+template <int N>
+__device__ __forceinline__ void wait_lines(uint32_t (&v)[N]) {
+#pragma unroll
+    for (int k = 0; k < N; ++k) asm volatile("" : : "v"(v[k]));
+}
+// What a tile will be the first to read of its state: its columns of the
+// rows from K below its own first (the tile before it in its column has read
+// those up to there) to K beyond its last.  Run by threads t of NT that have
+// no node in the last update: without it the first update's pulls come from
+// HBM and hold the workgroup for about a quarter of its life with little to
+// overlap (the waves of a tile load together, three tiles share a CU).
+// Measured with the strip order of the tiles (cavity_tiles2), 8192^2, three
+// steps per launch: FP32_H64 46.5 -> 51.3 GLUPS, FP32 48.1 -> 52.8, D2Q5 FP32
+// 72.0 -> 75.0, F16_SPLIT (4096^2) 44.4 -> 49.0.
+template <class Lay, typename R, int TW, int TH, int K, int NT>
+__device__ __forceinline__ void stepk_prefetch(const CavityConst<R> &c, const Tile2 &tl, const void *src,
+                                               const R *__restrict__ sr_src, int t) {
+    const int y0 = tl.y0 ? tl.y0 + K : 0, end = tl.y0 + tl.h + K, y1 = end < c.ny ? end : c.ny;
+    if (y0 >= y1) return;
+    const int ba = band_of(c, y0);
+    const BandOrigin org = band_origin(c, ba);
+    const Blocks b = blocks_at(src, c.pop_off + (int64_t)ba * c.band_bytes);
+    const uint32_t stride = (uint32_t)c.band_nodes;
+    const int x1 = tl.x0 + tl.w;
+    constexpr int TR = TH + K;  // rows of a first tile
+    auto n = [](int es, int planes) { return (planes * TR * ((TW * es + 127) / 128) + NT - 1) / NT; };
+    if constexpr (IsSplitLayout<Lay>::value) {
+        uint32_t v[n(4, 6)], w[n(2, 24)];
+        touch_lines<4, 6, TW, TR, NT>(b, org, stride, 0, tl.x0, x1, y0, y1, t, v);
+        touch_lines<2, 24, TW, TR, NT>(b, org, stride, 24 * stride, tl.x0, x1, y0, y1, t, w);
+        wait_lines(v);
+        wait_lines(w);
+    } else if constexpr (std::is_same<Lay, PlainH64<Lay::QT>>::value) {
+        uint32_t v[n(4, 8 + 2 * Lay::QT)], w[n(8, 1)];
+        touch_lines<4, 8 + 2 * Lay::QT, TW, TR, NT>(b, org, stride, 0, tl.x0, x1, y0, y1, t, v);
+        touch_lines<8, 1, TW, TR, NT>(b, org, stride, (8 + 2 * Lay::QT) * 4 * stride, tl.x0, x1, y0, y1, t, w);
+        wait_lines(v);
+        wait_lines(w);
+    } else {
+        constexpr int es = (int)sizeof(typename Lay::T), np = 9 + 2 * Lay::QT;
+        uint32_t v[n(es, np)];
+        touch_lines<es, np, TW, TR, NT>(b, org, stride, 0, tl.x0, x1, y0, y1, t, v);
+        wait_lines(v);
+    }
+}
+
 // One tile per workgroup, or (LOOP) a grid-stride walk over the tiles for
 // the persistent launch.  Without the loop nothing in the tile's code is
 // loop-invariant, so the compiler does not keep the 27 plane addresses live
@@ -197,7 +262,8 @@ template <class Lay, typename R, typename RH, int TW, int TH, int NT, int K>
 __device__ __forceinline__ void stepk_advance(const void *__restrict__ src, void *__restrict__ dst,
                                               const R *__restrict__ sr_src, R *__restrict__ sr_dst,
                                               double *__restrict__ acc, const CavityConst<R> *__restrict__ cav,
-                                              const Tile2 &tl, void *lds_q, R *lds_sr, float *lds_b, double *lds_t) {
+                                              const Tile2 *__restrict__ tiles, const Tile2 &tl, void *lds_q, R *lds_sr,
+                                              float *lds_b, double *lds_t, int next) {
     using Sh = StepKShape<Lay, TW, TH, K>;
     const CavityConst<R> &c = cav[tl.cav];
     const TileView<R> tv = tile_view<Sh>(c, tl);
@@ -224,7 +290,13 @@ __device__ __forceinline__ void stepk_advance(const void *__restrict__ src, void
         if (act) stepk_mid_store<Lay, R, RH, TW, TH, K, 1>(tv, n, tally, lds_q, lds_sr, q);
         __syncthreads();
     }
+    constexpr int BUSY = (TW * TH + 63) / 64 * 64;
     if (s < TW * tv.tl.h) stepk_last<Lay, R, RH, TW, TH, K>(tv, n, dst, sr_dst, last, lds_q, lds_sr, s);
+    if constexpr (NT > BUSY)
+        if (s >= BUSY && next >= 0) {
+            const Tile2 &tn = tiles[next];
+            stepk_prefetch<Lay, R, TW, TH, K, NT - BUSY>(cav[tn.cav], tn, src, sr_src, s - BUSY);
+        }
 }
 
 // Waves per SIMD a multi-step kernel is built for: as many workgroups per
@@ -255,12 +327,21 @@ constexpr int stepk_wpe() {
     return ((LBM_WPE_MASK >> ST) & 1) ? stepk_waves_per_eu<Lay, R, TW, TH, NT, K>() : 1;
 }
 
+// The tile that starts about when tile b's workgroup ends: `ahead` tiles on
+// among those of its XCD (remap_block gives each XCD a run of grid / 8).
+__device__ __forceinline__ int next_tile(int b, int ntiles, int grid, int ahead) {
+    const int per = grid >> 3;
+    if (ahead <= 0 || b >= per * 8) return -1;
+    const int n = b + ahead;
+    return n < ntiles && n < (b / per + 1) * per ? n : -1;
+}
+
 template <class Lay, typename R, typename RH, int TW, int TH, int NT, int K, bool LOOP, int WPE>
 __global__ __launch_bounds__(NT, WPE) void stepk_kernel(const void *__restrict__ src, void *__restrict__ dst,
                                                    const R *__restrict__ sr_src,
                                                    R *__restrict__ sr_dst, double *__restrict__ acc,
                                                    const CavityConst<R> *__restrict__ cav,
-                                                   const Tile2 *__restrict__ tiles, int ntiles, int xcd_remap) {
+                                                   const Tile2 *__restrict__ tiles, int ntiles, int xcd_remap, int ahead) {
     using Sh = StepKShape<Lay, TW, TH, K>;
     static_assert(Sh::LDS_BYTES + Sh::NSLOT * sizeof(R) + Sh::BASE_BYTES <= 65536, "tile exceeds 64 KiB of LDS");
     static_assert(NT >= Sh::NFIRST && NT % 64 == 0, "one thread per node of the first update");
@@ -271,13 +352,13 @@ __global__ __launch_bounds__(NT, WPE) void stepk_kernel(const void *__restrict__
     const int b = remap_block(blockIdx.x, gridDim.x, xcd_remap);
     if (!LOOP) {
         if (b < ntiles)
-            stepk_advance<Lay, R, RH, TW, TH, NT, K>(src, dst, sr_src, sr_dst, acc, cav, tiles[b], lds_q, lds_sr,
-                                                     lds_b, lds_t);
+            stepk_advance<Lay, R, RH, TW, TH, NT, K>(src, dst, sr_src, sr_dst, acc, cav, tiles, tiles[b], lds_q,
+                                                     lds_sr, lds_b, lds_t, next_tile(b, ntiles, gridDim.x, ahead));
         return;
     }
     for (int t = b; t < ntiles; t += gridDim.x) {
-        stepk_advance<Lay, R, RH, TW, TH, NT, K>(src, dst, sr_src, sr_dst, acc, cav, tiles[t], lds_q, lds_sr, lds_b,
-                                                 lds_t);
+        stepk_advance<Lay, R, RH, TW, TH, NT, K>(src, dst, sr_src, sr_dst, acc, cav, tiles, tiles[t], lds_q, lds_sr,
+                                                 lds_b, lds_t, -1);
         __syncthreads();  // the next tile reuses the LDS
     }
 }
@@ -288,18 +369,30 @@ static hipError_t launch_stepk_i(const Step2Launch &L, hipStream_t s) {
     using R = typename LayoutOf<ST>::R;
     using RH = typename LayoutOf<ST>::RH;
     using Tl = StepKTileI<ST, K, I>;
+    using Sh = StepKShape<Lay, Tl::TW, Tl::TH, K>;
+    // How many tiles on, among its XCD's, the tile lies that a workgroup
+    // fetches for: about the tile that starts when it ends.  Of the 32 CUs'
+    // 96 tiles (three per CU) 80 was best (64: 48.8 GLUPS, 80: 51.3, 96: 49.7,
+    // 104: 49.6), of 128 tiles 88 to 96.  Two-step launches are bound by HBM
+    // and lose to it (FP32_H64 39.2 -> 37.6 GLUPS, FP64 21.2 -> 19.2).
+    // Launches of fewer than three rounds of tiles have little to fetch for and
+    // some lose (D2Q5 FP32 1001x613, 1.9 rounds: 11.7 -> 12.1 us a step; 2.6
+    // and 3.1 rounds: even; 4.3 rounds, FP32_H64 1024^2: 25.2 -> 24.6).
+    const int per_xcd = L.n_cu / 8, wgs = Sh::per_cu(Sh::TILE_TALLY);
+    const bool fetch = K == 3 && sizeof(R) == 4 && L.xcd_remap && L.ntiles / (wgs * L.n_cu) >= 3;
+    const int ahead = fetch ? per_xcd + wgs * per_xcd / 2 : 0;
     if (L.grid >= L.ntiles) {
         hipLaunchKernelGGL((stepk_kernel<Lay, R, RH, Tl::TW, Tl::TH, Tl::NT, K, false,
                                          stepk_wpe<ST, Lay, R, Tl::TW, Tl::TH, Tl::NT, K>()>),
                            dim3(L.grid), dim3(Tl::NT),
                            0, s, L.src, L.dst, (const R *)L.sr_src, (R *)L.sr_dst, L.acc,
-                           (const CavityConst<R> *)L.cav, L.tiles, L.ntiles, L.xcd_remap);
+                           (const CavityConst<R> *)L.cav, L.tiles, L.ntiles, L.xcd_remap, ahead);
     } else {
         // persistent grids exist for the default shape only
         if constexpr (I == 0)
             hipLaunchKernelGGL((stepk_kernel<Lay, R, RH, Tl::TW, Tl::TH, Tl::NT, K, true, 1>), dim3(L.grid),
                                dim3(Tl::NT), 0, s, L.src, L.dst, (const R *)L.sr_src, (R *)L.sr_dst, L.acc,
-                               (const CavityConst<R> *)L.cav, L.tiles, L.ntiles, L.xcd_remap);
+                               (const CavityConst<R> *)L.cav, L.tiles, L.ntiles, L.xcd_remap, 0);
         else
             return hipErrorInvalidValue;
     }
