@@ -21,6 +21,7 @@
 #include "../../include/lbmpcm.h"
 #include "lbm_internal.h"
 #include "lbm_plan.h"
+#include "lbm_tiles.h"
 
 using namespace lbm;
 
@@ -116,6 +117,10 @@ struct Plan {
     // the tile shapes (0: not available for this storage)
     int64_t tilesk[4] = {0, 0, 0, 0};
     size_t off_tilesk[4] = {0, 0, 0, 0};
+    // deep launches: tile shape (-1: the handle takes none), tiles, most steps
+    int deep = -1, deep_k = 0;
+    int64_t deep_tiles = 0;
+    size_t off_deep = 0;
     size_t off_pop[2], off_sr[2], off_acc, off_accs, off_cav, off_tiles, off_fields, off_part, off_tf,
         off_tm, off_fl, off_out, total;
 };
@@ -124,6 +129,24 @@ struct Plan {
 // host and device in runs of whole rows of at most this many nodes, so the
 // staging area stays a small part of the memory however large a cavity is.
 constexpr int64_t kStageNodes = (int64_t)1 << 22;
+
+// The deep tile shape of a handle: the first that leaves at most a tile per
+// CU (kDeepTiles).  Periodic problems, whose rings may wrap more than once,
+// and the 16-bit forms have none.
+void choose_deep(const lbm_params *p, int n, Plan &pl) {
+    for (int c = 0; c < n; ++c)
+        if (p[c].bc_x == 1) return;
+    int tw, th, k;
+    for (int shape = 0; deep_tile(pl.st, shape, &tw, &th, &k); ++shape) {
+        int64_t count = 0;
+        for (int c = 0; c < n; ++c) count += count_tiles2(p[c].nx, p[c].ny, tw, th);
+        if (count > kDeepTiles) continue;
+        pl.deep = shape;
+        pl.deep_k = k;
+        pl.deep_tiles = count;
+        return;
+    }
+}
 
 lbm_status make_plan(const lbm_params *p, int n, lbm_precision prec, Plan &pl) {
     if (!p) return fail(LBM_EINVAL, "params is NULL");
@@ -200,6 +223,9 @@ lbm_status make_plan(const lbm_params *p, int n, lbm_precision prec, Plan &pl) {
         pl.off_tilesk[k] = off;
         off = align256(off + (size_t)pl.tilesk[k] * sizeof(Tile2));
     }
+    choose_deep(p, n, pl);
+    pl.off_deep = off;
+    off = align256(off + (size_t)pl.deep_tiles * sizeof(Tile2));
     pl.stage_nodes = std::max<int64_t>(std::min(pl.max_nodes, kStageNodes), pl.max_nx);
     pl.off_fields = off;
     off = align256(off + (size_t)6 * pl.stage_nodes * sizeof(double));
@@ -248,6 +274,12 @@ struct lbm_handle {
     hipGraph_t gsrc[2] = {nullptr, nullptr};
     hipGraphExec_t graphk[4][2] = {};  // K-step launches, K = 2, 3
     hipGraph_t gsrck[4][2] = {};
+    // the launch shape is the library's own choice (lc: the K-step part of
+    // it): deep launches, where the handle has them
+    bool own_shape = true;
+    lbm_launch_config own_lc{};
+    hipGraphExec_t graphd[2] = {nullptr, nullptr};
+    hipGraph_t gsrcd[2] = {nullptr, nullptr};
 
     void *pop(int b) { return ws + pl.off_pop[b]; }
     void *sr(int b) { return ws + pl.off_sr[b]; }
@@ -255,6 +287,8 @@ struct lbm_handle {
     double *acc_scratch() { return (double *)(ws + pl.off_accs); }
     void *cav() { return ws + pl.off_cav; }
     Tile *dtiles() { return (Tile *)(ws + pl.off_tiles); }
+    Tile2 *dtilesd() { return (Tile2 *)(ws + pl.off_deep); }
+    bool deep() const { return own_shape && pl.deep >= 0; }
     Tile2 *dtilesk(int k) { return (Tile2 *)(ws + pl.off_tilesk[k]); }
     double *fields() { return (double *)(ws + pl.off_fields); }
     double *dout() { return (double *)(ws + pl.off_out); }
@@ -273,6 +307,10 @@ void drop_graphs(lbm_handle *h) {
         if (h->gsrc[b]) (void)hipGraphDestroy(h->gsrc[b]);
         h->graph[b] = nullptr;
         h->gsrc[b] = nullptr;
+        if (h->graphd[b]) (void)hipGraphExecDestroy(h->graphd[b]);
+        if (h->gsrcd[b]) (void)hipGraphDestroy(h->gsrcd[b]);
+        h->graphd[b] = nullptr;
+        h->gsrcd[b] = nullptr;
         for (int k = 2; k <= 3; ++k) {
             if (h->graphk[k][b]) (void)hipGraphExecDestroy(h->graphk[k][b]);
             if (h->gsrck[k][b]) (void)hipGraphDestroy(h->gsrck[k][b]);
@@ -309,6 +347,18 @@ lbm_status tables_for(lbm_handle *h, const lbm_launch_config &lc) {
             if (s != LBM_OK) return s;
         }
     }
+    return LBM_OK;
+}
+
+// Tile table of the deep launches.
+lbm_status build_tilesd(lbm_handle *h) {
+    int tw, th, k;
+    if (h->pl.deep < 0 || !deep_tile(h->st, h->pl.deep, &tw, &th, &k)) return LBM_OK;
+    std::vector<Tile2> t;
+    for (int c = 0; c < h->n; ++c) cavity_tiles2(c, h->params[c].nx, h->params[c].ny, tw, th, t);
+    if ((int64_t)t.size() != h->pl.deep_tiles) return fail(LBM_EINVAL, "deep tile table overflow");
+    HIP_TRY(hipMemcpyAsync(h->dtilesd(), t.data(), t.size() * sizeof(Tile2), hipMemcpyHostToDevice, h->stream));
+    HIP_TRY(hipStreamSynchronize(h->stream));
     return LBM_OK;
 }
 
@@ -382,6 +432,22 @@ Step2Launch stepk_args(lbm_handle *h, int k, int src_buf, double *acc, const lbm
     return L;
 }
 
+DeepLaunch deep_args(lbm_handle *h, int k, int src_buf, double *acc) {
+    DeepLaunch L;
+    L.storage = h->st;
+    L.shape = h->pl.deep;
+    L.steps = k;
+    L.src = h->pop(src_buf);
+    L.dst = h->pop(1 - src_buf);
+    L.sr_src = h->sr(src_buf);
+    L.sr_dst = h->sr(1 - src_buf);
+    L.acc = acc;
+    L.cav = h->cav();
+    L.tiles = h->dtilesd();
+    L.ntiles = (int)h->pl.deep_tiles;
+    return L;
+}
+
 StepLaunch step_args(lbm_handle *h, int pull, int src_buf, double *acc, int tile0, int ntiles,
                      const lbm_launch_config &lc) {
     StepLaunch L;
@@ -408,14 +474,17 @@ lbm_status launch_one(lbm_handle *h, hipStream_t s, int pull, int src_buf) {
     return LBM_OK;
 }
 
-// Graph of graph_chunk launches of K steps each (K = 1: the one-step kernel).
-lbm_status build_graph(lbm_handle *h, int parity, int kk) {
+// Graph of graph_chunk launches of K steps each (K = 1: the one-step kernel;
+// deep: deep launches of K steps).
+lbm_status build_graph(lbm_handle *h, int parity, int kk, bool deep = false) {
     if (!h->cap) HIP_TRY(hipStreamCreateWithFlags(&h->cap, hipStreamNonBlocking));
     HIP_TRY(hipStreamBeginCapture(h->cap, hipStreamCaptureModeThreadLocal));
     int b = parity;
     for (int k = 0; k < h->graph_chunk; ++k) {
         hipError_t e;
-        if (kk > 1) {
+        if (deep) {
+            e = launch_deep(deep_args(h, kk, b, h->acc()), h->cap);
+        } else if (kk > 1) {
             Step2Launch L = stepk_args(h, kk, b, h->acc(), h->lc);
             e = launch_stepk(L, h->cap);
         } else {
@@ -430,8 +499,8 @@ lbm_status build_graph(lbm_handle *h, int parity, int kk) {
         }
         b ^= 1;
     }
-    hipGraph_t *src = kk > 1 ? &h->gsrck[kk][parity] : &h->gsrc[parity];
-    hipGraphExec_t *ex = kk > 1 ? &h->graphk[kk][parity] : &h->graph[parity];
+    hipGraph_t *src = deep ? &h->gsrcd[parity] : (kk > 1 ? &h->gsrck[kk][parity] : &h->gsrc[parity]);
+    hipGraphExec_t *ex = deep ? &h->graphd[parity] : (kk > 1 ? &h->graphk[kk][parity] : &h->graph[parity]);
     HIP_TRY(hipStreamEndCapture(h->cap, src));
     HIP_TRY(hipGraphInstantiate(ex, *src, nullptr, nullptr, 0));
     return LBM_OK;
@@ -443,6 +512,12 @@ lbm_status build_graph(lbm_handle *h, int parity, int kk) {
 lbm_status prepare_graphs(lbm_handle *h) {
     const int kk = h->lc.steps_per_launch;
     for (int parity = 0; parity < 2; ++parity) {
+        if (h->deep()) {
+            if (h->graphd[parity]) continue;
+            lbm_status s = build_graph(h, parity, h->pl.deep_k, true);
+            if (s != LBM_OK) return s;
+            continue;
+        }
         if (kk > 1 ? h->graphk[kk][parity] : h->graph[parity]) continue;
         lbm_status s = build_graph(h, parity, kk);
         if (s != LBM_OK) return s;
@@ -573,9 +648,12 @@ lbm_status setup(lbm_handle *h) {
     // By default the most steps per launch the form has (measured faster
     // for every cavity size and batch, the rows being padded to 64 nodes).
     h->lc.steps_per_launch = h->pl.tilesk[3] > 0 ? 3 : (h->pl.tilesk[2] > 0 ? 2 : 1);
+    h->own_lc = h->lc;
     lbm_status s = build_tiles(h, h->lc);
     if (s != LBM_OK) return s;
     s = tables_for(h, h->lc);
+    if (s != LBM_OK) return s;
+    s = build_tilesd(h);
     if (s != LBM_OK) return s;
     h->E0.assign(h->n, 0.0);
     h->M0.assign(h->n, 0.0);
@@ -708,6 +786,33 @@ extern "C" lbm_status lbm_step(lbm_handle *h, int64_t n) {
         h->cur ^= 1;
         h->step += 1;
         n -= 1;
+    }
+    if (h->deep()) {
+        const int K = h->pl.deep_k;
+        while (n >= (int64_t)K * h->graph_chunk) {
+            if (!h->graphd[h->cur]) {
+                lbm_status s = build_graph(h, h->cur, K, true);
+                if (s != LBM_OK) return s;
+            }
+            HIP_TRY(hipGraphLaunch(h->graphd[h->cur], h->stream));
+            if (h->graph_chunk & 1) h->cur ^= 1;
+            h->step += (int64_t)K * h->graph_chunk;
+            n -= (int64_t)K * h->graph_chunk;
+        }
+        while (n >= 2) {
+            const int k = (int)std::min<int64_t>(n, K);
+            HIP_TRY(launch_deep(deep_args(h, k, h->cur, h->acc()), h->stream));
+            h->cur ^= 1;
+            h->step += k;
+            n -= k;
+        }
+        if (n == 1) {
+            lbm_status s = launch_one(h, h->stream, 1, h->cur);
+            if (s != LBM_OK) return s;
+            h->cur ^= 1;
+            h->step += 1;
+        }
+        return LBM_OK;
     }
     const int kk = h->lc.steps_per_launch;
     if (kk > 1) {
@@ -940,6 +1045,22 @@ extern "C" lbm_status lbm_get_launch(const lbm_handle *h, lbm_launch_config *out
     return LBM_OK;
 }
 
+namespace {
+// Launch shape lc from here on; own: the library's choice, with deep launches
+// where the handle has them.
+lbm_status apply_shape(lbm_handle *h, const lbm_launch_config &lc, bool own) {
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    lbm_status s = build_tiles(h, lc);
+    if (s != LBM_OK) return s;
+    s = tables_for(h, lc);
+    if (s != LBM_OK) return s;
+    h->lc = reported(h, lc);
+    h->own_shape = own;
+    drop_graphs(h);
+    return prepare_graphs(h);
+}
+}  // namespace
+
 extern "C" lbm_status lbm_set_launch(lbm_handle *h, const lbm_launch_config *cfg) {
     if (!h || !cfg) return fail(LBM_EINVAL, "NULL argument");
     if (!valid_launch(*cfg, h->pl))
@@ -947,14 +1068,7 @@ extern "C" lbm_status lbm_set_launch(lbm_handle *h, const lbm_launch_config *cfg
                     "unsupported launch shape block=%d npt=%d xcd=%d persistent=%d steps=%d tile_shape=%d",
                     cfg->block, cfg->nodes_per_thread, cfg->xcd_remap, cfg->persistent, cfg->steps_per_launch,
                     cfg->tile_shape);
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    lbm_status s = build_tiles(h, *cfg);
-    if (s != LBM_OK) return s;
-    s = tables_for(h, *cfg);
-    if (s != LBM_OK) return s;
-    h->lc = reported(h, *cfg);
-    drop_graphs(h);
-    return prepare_graphs(h);
+    return apply_shape(h, *cfg, false);
 }
 
 namespace {
@@ -975,7 +1089,7 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
                                    lbm_launch_config *chosen) {
     if (!h) return fail(LBM_EINVAL, "handle is NULL");
     if (steps < 1) return fail(LBM_EINVAL, "steps_per_trial must be >= 1");
-    const std::string key = tune_key(h);
+    const std::string key = tune_key(h), own_key = key + ":own";
     if (cache_path) {
         FILE *f = fopen(cache_path, "r");
         if (f) {
@@ -984,9 +1098,9 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
             std::memset(&lc, 0, sizeof(lc));
             while (fscanf(f, "%255s %d %d %d %d %d %d", k, &lc.block, &lc.nodes_per_thread, &lc.xcd_remap,
                           &lc.persistent, &lc.steps_per_launch, &lc.tile_shape) == 7) {
-                if (key == k && valid_launch(lc, h->pl)) {
+                if ((key == k || own_key == k) && valid_launch(lc, h->pl)) {
                     fclose(f);
-                    lbm_status s = lbm_set_launch(h, &lc);
+                    lbm_status s = apply_shape(h, lc, own_key == k);
                     if (s == LBM_OK && chosen) *chosen = h->lc;
                     return s;
                 }
@@ -1004,6 +1118,8 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
     lbm_launch_config best = h->lc;
     float best_ms = 1e30f;
     const lbm_launch_config saved = h->lc;
+    const bool saved_own = h->own_shape;
+    bool best_own = false;
     // Every trial reads the live buffer and writes only the other buffer and
     // scratch tallies; times are per step.
     auto trial = [&](const lbm_launch_config &lc, float *ms_per_step) -> lbm_status {
@@ -1034,7 +1150,7 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
         const std::string msg = g_err;
         (void)hipEventDestroy(e0);
         (void)hipEventDestroy(e1);
-        (void)lbm_set_launch(h, &saved);
+        (void)apply_shape(h, saved, saved_own);
         return fail(s, "%s", msg.c_str());
     };
     for (int b : blocks)
@@ -1069,17 +1185,33 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
                     }
                 }
     }
+    // deep launches, with the library's own shape for the rest
+    if (h->pl.deep >= 0) {
+        const DeepLaunch L = deep_args(h, h->pl.deep_k, h->cur, h->acc_scratch());
+        hipError_t e = launch_deep(L, h->stream);
+        if (e == hipSuccess) e = hipEventRecord(e0, h->stream);
+        for (int k = 0; k < steps && e == hipSuccess; ++k) e = launch_deep(L, h->stream);
+        if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
+        if (e == hipSuccess) e = hipEventSynchronize(e1);
+        float ms = 0;
+        if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
+        if (e != hipSuccess) return abandon(fail(LBM_EDEVICE, "deep launch: %s", hipGetErrorString(e)));
+        if (ms / (float)(steps * h->pl.deep_k) < best_ms) {
+            best = h->own_lc;
+            best_own = true;
+        }
+    }
     (void)hipEventDestroy(e0);
     (void)hipEventDestroy(e1);
     // The trials wrote the inactive buffer; when the live state is the raw
     // initial state the inactive buffer is not part of the state either.
-    lbm_status s = lbm_set_launch(h, &best);
+    lbm_status s = apply_shape(h, best, best_own);
     if (s != LBM_OK) return s;
     if (chosen) *chosen = h->lc;
     if (cache_path) {
         FILE *f = fopen(cache_path, "a");
         if (f) {
-            fprintf(f, "%s %d %d %d %d %d %d\n", key.c_str(), best.block, best.nodes_per_thread, best.xcd_remap,
+            fprintf(f, "%s %d %d %d %d %d %d\n", (best_own ? own_key : key).c_str(), best.block, best.nodes_per_thread, best.xcd_remap,
                     best.persistent, best.steps_per_launch, best.tile_shape);
             fclose(f);
         }

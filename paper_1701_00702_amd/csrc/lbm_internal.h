@@ -174,6 +174,20 @@ struct Step2Launch {
     int ntiles;
 };
 
+// Deep launches: up to K steps of a few tiles.
+struct DeepLaunch {
+    int storage;
+    int shape, steps;
+    const void *src;
+    void *dst;
+    const void *sr_src;
+    void *sr_dst;
+    double *acc;
+    const void *cav;
+    const Tile2 *tiles;
+    int ntiles;
+};
+
 // Macroscopic fields of rows [y0, y0 + rows) of one cavity.
 struct MacroLaunch {
     int storage;
@@ -248,6 +262,9 @@ bool stepk_supported(int storage, int k);  // K steps per launch (K = 2, 3)
 // when it does not exist.
 #define LBM_TILE_SHAPES 3
 void stepk_tile(int storage, int k, int shape, int *tw, int *th);
+hipError_t launch_deep(const DeepLaunch &L, hipStream_t s);
+// Tile and most steps of deep shape `shape`; false when there is none.
+bool deep_tile(int storage, int shape, int *tw, int *th, int *k);
 hipError_t launch_macro(const MacroLaunch &L, int nx, int ny, hipStream_t s);
 hipError_t launch_diag(const DiagLaunch &L, int nx, int ny, hipStream_t s);
 hipError_t launch_diag_nodes(const DiagNodeLaunch &L, int nx, int ny, hipStream_t s);

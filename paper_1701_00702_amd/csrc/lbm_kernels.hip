@@ -268,9 +268,9 @@ __device__ __forceinline__ void stepk_advance(const void *__restrict__ src, void
     const CavityConst<R> &c = cav[tl.cav];
     const TileView<R> tv = tile_view<Sh>(c, tl);
     const NodeConst<R, RH> &n = node_const<Lay, RH>(c);
-    using InTile = typename std::conditional<Sh::TILE_TALLY, TileTally<TW, TH, false, R>, CavityTally<R>>::type;
-    using InLast = typename std::conditional<Sh::TILE_TALLY, TileTally<TW, TH, true, R>, CavityTally<R>>::type;
-    const CavityTally<R> all{acc, c};
+    using InTile = typename std::conditional<Sh::TILE_TALLY, TileTally<TW, TH, false, R>, CavityTally<double, R>>::type;
+    using InLast = typename std::conditional<Sh::TILE_TALLY, TileTally<TW, TH, true, R>, CavityTally<double, R>>::type;
+    const CavityTally<double, R> all{acc, c};
     const InTile tally = tally_of<InTile>(all, lds_t, tv);
     const InLast last = tally_of<InLast>(all, lds_t, tv);
     // NT >= NFIRST: each thread advances at most one node per update
@@ -479,6 +479,83 @@ hipError_t launch_stepk(const Step2Launch &L, hipStream_t s) {
         case ST_BF16S: return launch_stepk_s<ST_BF16S, 2>(L, s);
         default: return hipErrorInvalidValue;
     }
+}
+
+// ---------------------------------------------------------------------------
+// Deep launches (k <= K steps, one tile per workgroup, one workgroup per CU).
+// Bound by the latency of one wave's chain of instructions: at 64^2 (FP32_H64,
+// 8x8 tiles) an update takes 1720 cycles of a wave, 3400 where it holds wall
+// nodes, and 1000 to 1300 for the exchange through LDS.  The constants stay
+// in vector registers, which one workgroup per CU leaves plenty of.
+// ---------------------------------------------------------------------------
+template <class Lay, typename R, typename RH, int TW, int TH, int K>
+__global__ __launch_bounds__((DeepShape<Lay, TW, TH, K>::NT)) void deep_kernel(
+    const void *__restrict__ src, void *__restrict__ dst, const R *__restrict__ sr_src, R *__restrict__ sr_dst,
+    double *__restrict__ acc, const CavityConst<R> *__restrict__ cav, const Tile2 *__restrict__ tiles, int k) {
+    using Sh = DeepShape<Lay, TW, TH, K>;
+    __shared__ __align__(16) unsigned char lds_q[Sh::LDS_BYTES];
+    const Tile2 &tl = tiles[blockIdx.x];
+    const CavityConst<R> &c = cav[tl.cav];
+    const TileView<R> tv = tile_view<Sh>(c, tl);
+    NodeConst<R, RH> n = node_const_of<RH>(c);
+    reside<Lay, true>(n);
+    DeepNode<R, RH> q;
+    deep_load<Sh, Lay, R, RH>(tv, n, src, sr_src, acc, k, (int)threadIdx.x, q);
+    for (int left = k - 1;; --left) {
+        const bool act = deep_update<Sh, R, RH>(tv, n, left, q);
+        if (left == 0) break;
+        __syncthreads();  // every pull of this update is in registers
+        if (act) deep_put<Sh, R, RH>(n, lds_q, (int)threadIdx.x, q);
+        __syncthreads();
+        deep_pull<Sh, R, RH>(n, lds_q, left - 1, q);
+    }
+    deep_store<Sh, Lay, R, RH>(tv, n, dst, sr_dst, acc, q);
+}
+
+template <int ST, int I>
+static hipError_t launch_deep_i(const DeepLaunch &L, hipStream_t s) {
+    using Lay = typename LayoutOf<ST>::L;
+    using R = typename LayoutOf<ST>::R;
+    using RH = typename LayoutOf<ST>::RH;
+    constexpr DeepDims d = deep_dims(ST, I);
+    if (L.steps < 2 || L.steps > d.k) return hipErrorInvalidValue;
+    hipLaunchKernelGGL((deep_kernel<Lay, R, RH, d.tw, d.th, d.k>), dim3(L.ntiles),
+                       dim3(DeepShape<Lay, d.tw, d.th, d.k>::NT), 0, s, L.src, L.dst, (const R *)L.sr_src,
+                       (R *)L.sr_dst, L.acc, (const CavityConst<R> *)L.cav, L.tiles, L.steps);
+    return hipGetLastError();
+}
+
+template <int ST>
+static hipError_t launch_deep_s(const DeepLaunch &L, hipStream_t s) {
+    switch (L.shape) {
+        case 0: return launch_deep_i<ST, 0>(L, s);
+        case 1: return launch_deep_i<ST, 1>(L, s);
+        case 2: return launch_deep_i<ST, 2>(L, s);
+        case 3: return launch_deep_i<ST, 3>(L, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+hipError_t launch_deep(const DeepLaunch &L, hipStream_t s) {
+    if (L.ntiles < 1) return hipErrorInvalidValue;
+    switch (L.storage) {
+        case ST_F64: return launch_deep_s<ST_F64>(L, s);
+        case ST_F32: return launch_deep_s<ST_F32>(L, s);
+        case ST_F32H: return launch_deep_s<ST_F32H>(L, s);
+        case ST5_F64: return launch_deep_s<ST5_F64>(L, s);
+        case ST5_F32: return launch_deep_s<ST5_F32>(L, s);
+        case ST5_F32H: return launch_deep_s<ST5_F32H>(L, s);
+        default: return hipErrorInvalidValue;
+    }
+}
+
+bool deep_tile(int storage, int shape, int *tw, int *th, int *k) {
+    if (!deep_available(storage) || shape < 0 || shape >= kDeepShapes) return false;
+    const DeepDims d = deep_dims(storage, shape);
+    *tw = d.tw;
+    *th = d.th;
+    *k = d.k;
+    return true;
 }
 
 // ---------------------------------------------------------------------------

@@ -113,15 +113,39 @@ LBM_HD const NodeConst<R, RH> &node_const_of(const CavityConst<R> &c) {
     else return c.nd;
 }
 
-// A workgroup-uniform value kept in a scalar register from here on: the
-// empty asm keeps the compiler from loading it again at each use.
-template <typename T>
+// A value kept in a register from here on: the empty asm keeps the compiler
+// from loading it again at each use.  Scalar registers (workgroup-uniform
+// values only), or vector ones.
+template <bool VECTOR = false, typename T>
 LBM_HD void resident(T &v) {
 #if defined(__HIP_DEVICE_COMPILE__)
-    asm volatile("" : "+s"(v));
+    if constexpr (VECTOR) asm volatile("" : "+v"(v));
+    else asm volatile("" : "+s"(v));
 #else
     (void)v;
 #endif
+}
+template <class Lay, bool VECTOR, class N>
+LBM_HD void reside(N &n) {
+    constexpr bool V = VECTOR;
+    resident<V>(n.H_ref), resident<V>(n.H_fs), resident<V>(n.H_fl), resident<V>(n.T_fs), resident<V>(n.T_fl);
+    resident<V>(n.inv_dH), resident<V>(n.dT_band), resident<V>(n.Tf_ref), resident<V>(n.hv_f);
+    resident<V>(n.gbeta), resident<V>(n.T0), resident<V>(n.px), resident<V>(n.py);
+    resident<V>(n.inv_phi), resident<V>(n.drag_lin), resident<V>(n.drag_quad), resident<V>(n.l0), resident<V>(n.l0sq);
+    resident<V>(n.l1), resident<V>(n.fA7), resident<V>(n.fB7), resident<V>(n.fC7);
+    resident<V>(n.hv_m), resident<V>(n.sr_ratio);
+    resident<V>(n.T_ref), resident<V>(n.mA0), resident<V>(n.mB0), resident<V>(n.mA1), resident<V>(n.mA3);
+    resident<V>(n.me1), resident<V>(n.zA1), resident<V>(n.zB1), resident<V>(n.zA3), resident<V>(n.zB3);
+    resident<V>(n.ge1);
+    resident(n.bounce_back);
+    if constexpr (Lay::QT == 9) {
+        resident<V>(n.mB1), resident<V>(n.mA4), resident<V>(n.mA7), resident<V>(n.me2);
+        resident<V>(n.zA4), resident<V>(n.zB4), resident<V>(n.zA7), resident<V>(n.ge2);
+    } else {
+        resident<V>(n.mB3), resident<V>(n.w4);
+    }
+    if constexpr (Lay::SCALED)
+        for (int f = 0; f < 3; ++f) resident<V>(n.scale[f]), resident<V>(n.inv_scale[f]);
 }
 
 // The constants of the node update for the step kernels.  With FP32
@@ -140,27 +164,7 @@ LBM_HD const NodeConst<double, RH> &node_const(const CavityConst<double> &c) {
 template <class Lay, typename RH>
 LBM_HD NodeConst<float, RH> node_const(const CavityConst<float> &c) {
     NodeConst<float, RH> n = node_const_of<RH>(c);
-#if defined(__HIP_DEVICE_COMPILE__)
-    {
-        constexpr bool q9 = Lay::QT == 9;
-        resident(n.H_ref), resident(n.H_fs), resident(n.H_fl), resident(n.T_fs), resident(n.T_fl);
-        resident(n.inv_dH), resident(n.dT_band), resident(n.Tf_ref), resident(n.hv_f);
-        resident(n.gbeta), resident(n.T0), resident(n.px), resident(n.py);
-        resident(n.inv_phi), resident(n.drag_lin), resident(n.drag_quad), resident(n.l0), resident(n.l0sq);
-        resident(n.l1), resident(n.fA7), resident(n.fB7), resident(n.fC7), resident(n.hv_m), resident(n.sr_ratio);
-        resident(n.T_ref), resident(n.mA0), resident(n.mB0), resident(n.mA1), resident(n.mA3), resident(n.me1);
-        resident(n.zA1), resident(n.zB1), resident(n.zA3), resident(n.zB3), resident(n.ge1);
-        resident(n.bounce_back);
-        if constexpr (q9) {
-            resident(n.mB1), resident(n.mA4), resident(n.mA7), resident(n.me2);
-            resident(n.zA4), resident(n.zB4), resident(n.zA7), resident(n.ge2);
-        } else {
-            resident(n.mB3), resident(n.w4);
-        }
-        if constexpr (Lay::SCALED)
-            for (int f = 0; f < 3; ++f) resident(n.scale[f]), resident(n.inv_scale[f]);
-    }
-#endif
+    reside<Lay, false>(n);
     return n;
 }
 
@@ -929,43 +933,56 @@ LBM_HD int thermal_wall(const CavityConst<R> &c, int x, int y) {
     return -1;
 }
 
-// Non-equilibrium extrapolation for wall node (x, y), applied in place to
-// the partner's pulled offsets (Eq. 52 with wall velocity 0; thermal
-// analogues with the isothermal or zero-gradient wall values).
-template <int QT, typename R, typename RH>
-LBM_HD void reconstruct_wall(const CavityConst<R> &c, const NodeConst<R, RH> &n, int x, int y, R qf[9], RH qg[9],
-                             R qh[9]) {
+// What the reconstruction of a wall node reads: the values of the isothermal
+// wall it lies on (a vertical one before a horizontal one; iso false: it
+// takes its partner's), selected from uniform values rather than loaded per
+// lane, and constants of the enthalpy and metal fields.
+template <typename R, typename RH>
+struct WallNode {
+    bool iso;
+    RH Tb, Hb, c_fref, inv_phi, inv_cs2, varpi;
+    R Tmb, c_mref, varpi_m;
+};
+template <typename RH, typename R>
+LBM_HD WallNode<R, RH> wall_node(const CavityConst<R> &c, int x, int y) {
     const ThermalConst<RH> &t = thermal<RH>(c);
+    WallNode<R, RH> w{false, RH(0), RH(0), t.c_fref, t.inv_phi, t.inv_cs2, t.varpi, R(0), c.c_mref, c.varpi};
+    const bool on[4] = {!c.periodic && x == 0, !c.periodic && x == c.nx - 1, y == 0, y == c.ny - 1};
+#pragma unroll
+    for (int k = 3; k >= 0; --k)
+        if (c.wall_iso[k]) {
+            w.iso = on[k] || w.iso;
+            w.Tb = on[k] ? t.T_wall[k] : w.Tb;
+            w.Hb = on[k] ? t.H_wall[k] : w.Hb;
+            w.Tmb = on[k] ? c.T_wall[k] : w.Tmb;
+        }
+    return w;
+}
+
+// Non-equilibrium extrapolation for a wall node, applied in place to the
+// partner's pulled offsets (Eq. 52 with wall velocity 0; thermal analogues
+// with the isothermal or zero-gradient wall values).
+template <int QT, typename R, typename RH>
+LBM_HD void reconstruct_wall(const WallNode<R, RH> &w, const NodeConst<R, RH> &n, R qf[9], RH qg[9], R qh[9]) {
     Thermo<RH> pt;
     Macro<R> p;
     macros<QT>(n, qf, qg, qh, pt, p);
-    // the wall values: the partner's (adiabatic), or those of the isothermal
-    // wall the node lies on (a vertical one before a horizontal one), taken by
-    // selects from uniform values rather than loaded per lane
-    RH Tb = pt.Tf, Hb = pt.H;
-    R Tmb = p.Tm;
-    const bool on[4] = {!c.periodic && x == 0, !c.periodic && x == c.nx - 1, y == 0, y == c.ny - 1};
-#pragma unroll
-    for (int w = 3; w >= 0; --w)
-        if (c.wall_iso[w]) {
-            Tb = on[w] ? t.T_wall[w] : Tb;
-            Hb = on[w] ? t.H_wall[w] : Hb;
-            Tmb = on[w] ? c.T_wall[w] : Tmb;
-        }
+    const RH Tb = w.iso ? w.Tb : pt.Tf, Hb = w.iso ? w.Hb : pt.H;
+    const R Tmb = w.iso ? w.Tmb : p.Tm;
     const R uu = p.ux * p.ux + p.uy * p.uy;
     const RH dTg = Tb - pt.Tf;
     const R dTh = Tmb - p.Tm;
     // g^eq(H_b, T_b, 0) - g^eq(H, T, u) from Eq. (40) / Eq. (B3); h likewise
     // from Eq. (49) / Eq. (B5)
-    const RH jT = t.inv_cs2 * pt.Tf * t.inv_phi;
-    const R uu15 = R(1.5) * uu * c.inv_phi;
+    const RH jT = w.inv_cs2 * pt.Tf * w.inv_phi;
+    const R uu15 = R(1.5) * uu * n.inv_phi;
     qf[0] += -w_of<R>(0) * p.rho * -uu15;
     if (QT == 9) {
-        qg[0] += (Hb - pt.H) - RH(5) / RH(9) * t.c_fref * dTg;
-        qh[0] += (R(1) - R(5) / R(9) * c.c_mref) * dTh;
+        qg[0] += (Hb - pt.H) - RH(5) / RH(9) * w.c_fref * dTg;
+        qh[0] += (R(1) - R(5) / R(9) * w.c_mref) * dTh;
     } else {
-        qg[0] += (Hb - pt.H) - t.varpi * t.c_fref * dTg;
-        qh[0] += (R(1) - c.varpi * c.c_mref) * dTh;
+        qg[0] += (Hb - pt.H) - w.varpi * w.c_fref * dTg;
+        qh[0] += (R(1) - w.varpi_m * w.c_mref) * dTh;
     }
     // the moving directions by opposite pairs (1, 3), (2, 4), (5, 7), (6, 8)
     const int fwd[4] = {1, 2, 5, 6}, bwd[4] = {3, 4, 7, 8};
@@ -975,14 +992,14 @@ LBM_HD void reconstruct_wall(const CavityConst<R> &c, const NodeConst<R, RH> &n,
         const int i = fwd[k], j = bwd[k];
         const R eu = along[k];
         // f^eq(rho, 0) - f^eq(rho, u) from Eq. (27)
-        const R e3 = R(3) * eu, e45 = R(4.5) * eu * eu * c.inv_phi, wr = -w_of<R>(i) * p.rho;
+        const R e3 = R(3) * eu, e45 = R(4.5) * eu * eu * n.inv_phi, wr = -w_of<R>(i) * p.rho;
         qf[i] += wr * (e3 + e45 - uu15);
         qf[j] += wr * (e45 - e3 - uu15);
         if (i < QT) {
-            const RH wg = QT == 9 ? w_of<RH>(i) : RH(0.25) * t.varpi;
-            const R wh = QT == 9 ? w_of<R>(i) : R(0.25) * c.varpi;
-            const RH cT = t.c_fref * dTg, ju = jT * (RH)eu;
-            const R hw = wh * c.c_mref * dTh;
+            const RH wg = QT == 9 ? w_of<RH>(i) : RH(0.25) * w.varpi;
+            const R wh = QT == 9 ? w_of<R>(i) : R(0.25) * w.varpi_m;
+            const RH cT = w.c_fref * dTg, ju = jT * (RH)eu;
+            const R hw = wh * w.c_mref * dTh;
             qg[i] += wg * (cT - ju);
             qg[j] += wg * (cT + ju);
             qh[i] += hw;
@@ -1173,57 +1190,74 @@ LBM_HD void gather_view(const NodeConst<R, RH> &n, Blocks b, const View &v, cons
     else pull_all<Lay, R, RH, PULL, false>(n, b, v, g, qf, qg, qh);
 }
 
-// Energy and mass carried by the three links of a node's side towards one of
-// its walls (FP64): the axis link and the two diagonals a and b, in that
-// order.  q(f, i) selects the population; energy moves only along the
-// thermal lattice's links (g_ref, h_ref: alike on all axes and all
-// diagonals).
+// Energy and mass carried by the three links between node (x, y), next to a
+// vertical (X) or horizontal wall, and that wall, as offsets from what the
+// reference state would carry (FP64): a step's inflow and outflow run over
+// the same links, so their references cancel.  low: the left or bottom wall.
+// Populations leave (OUT) along the directions that point at the wall and
+// enter along their opposites; a diagonal between a corner-adjacent node and
+// a vertical wall counts for that wall (skip_lo: the node is next to the left
+// wall, skip_hi: the right one); energy moves only along the thermal
+// lattice's links.
 struct LinkSum {
     double E, M;
 };
-template <int QT, bool OUT, typename R>
-LBM_HD void add_link(const CavityConst<R> &c, bool diag, double qf, double qg, double qh, bool use, LinkSum &s) {
-    const int i = diag ? 5 : 1;
-    const double e = i < QT ? c.we * (c.g_ref[i] + qg) + c.wm * (c.h_ref[i] + qh) : 0.0;
-    const double m = w_of<double>(i) + qf;
-    s.E += use ? (OUT ? -e : e) : 0.0;
-    s.M += use ? (OUT ? -m : m) : 0.0;
-}
-// The links between node (x, y), next to a vertical (X) or horizontal wall,
-// and that wall.  low: the left or bottom wall.  Populations leave (OUT)
-// along the directions that point at the wall and enter along their
-// opposites; a diagonal between a corner-adjacent node and a vertical wall
-// counts for that wall (skip_lo: the node is next to the left wall, skip_hi:
-// the right one).
-template <int QT, bool X, bool OUT, typename R, typename RH>
-LBM_HD void wall_links(const CavityConst<R> &c, bool low, bool skip_lo, bool skip_hi, const R qf[9], const RH qg[9],
-                       const R qh[9], LinkSum &s) {
-    // directions with positive (p) and negative (n) component along the axis
+// Constants of walls and tallies, read from the cavity's table where needed.
+template <typename R, typename RH>
+struct TableWalls {
+    const CavityConst<R> &c;
+    LBM_HD WallNode<R, RH> node(int x, int y) const { return wall_node<RH>(c, x, y); }
+    LBM_HD double we() const { return c.we; }
+    LBM_HD double wm() const { return c.wm; }
+};
+template <int QT, bool X, bool OUT, class Walls, typename R, typename RH>
+LBM_HD LinkSum wall_links(const Walls &walls, bool low, bool skip_lo, bool skip_hi, const R qf[9], const RH qg[9],
+                          const R qh[9]) {
     using RG = typename MomentType<R, RH>::T;  // moving populations are held in it
+    // directions with positive (p) and negative (n) component along the axis:
+    // the axis, then the two diagonals
     constexpr int p[3] = {X ? 1 : 2, 5, X ? 8 : 6}, n[3] = {X ? 3 : 4, X ? 6 : 7, X ? 7 : 8};
     const bool pos = low != OUT;
+    double f = 0.0, g = 0.0, h = 0.0;
 #pragma unroll
     for (int k = 0; k < 3; ++k) {
-        // horizontal walls: the diagonals 5, 8 (entering 5, 8 from, leaving 6,
-        // 7 to, the left; and so on) that belong to a vertical wall
-        bool use = true;
-        if (!X && k == 1) use = low ? !skip_lo : !skip_hi;
-        if (!X && k == 2) use = low ? !skip_hi : !skip_lo;
-        add_link<QT, OUT>(c, k > 0, (double)(pos ? qf[p[k]] : qf[n[k]]),
-                          (double)(pos ? (RG)qg[p[k]] : (RG)qg[n[k]]), (double)(pos ? qh[p[k]] : qh[n[k]]), use, s);
+        R af = pos ? qf[p[k]] : qf[n[k]], ah = pos ? qh[p[k]] : qh[n[k]];
+        RG ag = pos ? (RG)qg[p[k]] : (RG)qg[n[k]];
+        if (!X && k > 0) {
+            // horizontal walls: the diagonals 5 and 7 cross the left wall's
+            // column from below and the right one's from above, 6 and 8 the
+            // other way round
+            const bool skip = (k == 1) == low ? skip_lo : skip_hi;
+            af = skip ? R(0) : af;
+            ag = skip ? RG(0) : ag;
+            ah = skip ? R(0) : ah;
+        }
+        f += (double)af;
+        if (k == 0 || QT == 9) {
+            g += (double)ag;
+            h += (double)ah;
+        }
     }
+    return LinkSum{fma_of(walls.we(), g, walls.wm() * h), f};
+}
+// What the reference state carries along those links.
+template <int QT, typename R>
+LBM_HD LinkSum wall_reference(const CavityConst<R> &c, bool skip_lo, bool skip_hi) {
+    const double diag = 2.0 - (skip_lo ? 1.0 : 0.0) - (skip_hi ? 1.0 : 0.0), dt = QT == 9 ? diag : 0.0;
+    return LinkSum{c.we * (c.g_ref[1] + dt * c.g_ref[5]) + c.wm * (c.h_ref[1] + dt * c.h_ref[5]),
+                   w_of<double>(1) + diag * w_of<double>(5)};
 }
 
 // Where the tallies of the nodes next to a wall are kept, energy and mass of
 // one slot each: column() of a node next to the left or right wall by its
 // row, row() of one next to the bottom or top wall by its column.
 // CavityTally: the cavity's own, in global memory.
-template <typename R>
+template <typename T, typename R>
 struct CavityTally {
-    double *acc;
+    T *acc;
     const CavityConst<R> &c;
-    LBM_HD double *column(bool left, int y) const { return acc + 2 * (c.acc0 + (left ? y : c.ny + y)); }
-    LBM_HD double *row(bool bottom, int x) const { return acc + 2 * (c.acc0 + 2 * c.ny + (bottom ? x : c.nx + x)); }
+    LBM_HD T *column(bool left, int y) const { return acc + 2 * (c.acc0 + (left ? y : c.ny + y)); }
+    LBM_HD T *row(bool bottom, int x) const { return acc + 2 * (c.acc0 + 2 * c.ny + (bottom ? x : c.nx + x)); }
     LBM_HD void add(const double *from, double *to, LinkSum s) const {
         to[0] = from[0] + s.E;
         to[1] = from[1] + s.M;
@@ -1240,7 +1274,7 @@ struct CavityTally {
 template <int TW, int TH, bool LAST, typename R>
 struct TileTally {
     static constexpr int N = 4 * (TW + TH);  // doubles
-    CavityTally<R> all;
+    CavityTally<double, R> all;
     double *lds;
     int x0, y0;
     LBM_HD double *column(bool left, int y) const { return lds + 2 * ((left ? 0 : TH) + y - y0); }
@@ -1269,27 +1303,35 @@ LBM_HD void link_content(const CavityConst<R> &c, int i, const R qf[9], const RH
 // new PCM source Sr_f.  edge (uniform over the workgroup): some node of the
 // workgroup may be a wall node or next to one; without it the wall code is
 // passed by a scalar branch.
-template <int QT, typename R, typename RH, bool PULL, class Tally>
-LBM_HD RH update_node(const CavityConst<R> &c, const NodeConst<R, RH> &n, bool edge, const NodeGeom &g, int x, int y,
-                      R qf[9], RH qg[9], R qh[9], R sr_prev, bool tally, Tally acc, Thermo<RH> &th,
-                      Macro<R> &m) {
+template <int QT, typename R, typename RH, bool PULL, class Walls, class Tally>
+LBM_HD RH update_node(const Walls &walls, const NodeConst<R, RH> &n, bool edge, const NodeGeom &g, int x, int y,
+                      R qf[9], RH qg[9], R qh[9], R sr_prev, bool tally, Tally acc, Thermo<RH> &th, Macro<R> &m) {
     // Wall tallies: an interior node next to a wall owns one slot per wall it
     // touches (x: the vertical wall, y: the horizontal one).  Set and read
     // under the same conditions only.
     LinkSum sx, sy;
+    const bool lo = edge && g.near_x() && x == 1, hi = edge && g.near_x() && x != 1;
     if (edge) {
         // inflow: populations pulled from wall nodes (post-collision of the
-        // previous step)
+        // previous step; the first step has none, and counts the outflow's
+        // reference)
         if (tally && g.near_x()) {
-            sx = LinkSum{0.0, 0.0};
-            if (PULL) wall_links<QT, true, false>(c, x == 1, false, false, qf, qg, qh, sx);
+            if constexpr (PULL) {
+                sx = wall_links<QT, true, false>(walls, lo, false, false, qf, qg, qh);
+            } else {
+                sx = wall_reference<QT>(walls.c, false, false);
+                sx = LinkSum{-sx.E, -sx.M};
+            }
         }
         if (tally && g.near_y()) {
-            sy = LinkSum{0.0, 0.0};
-            if (PULL)
-                wall_links<QT, false, false>(c, y == 1, g.near_x() && x == 1, g.near_x() && x != 1, qf, qg, qh, sy);
+            if constexpr (PULL) {
+                sy = wall_links<QT, false, false>(walls, y == 1, lo, hi, qf, qg, qh);
+            } else {
+                sy = wall_reference<QT>(walls.c, lo, hi);
+                sy = LinkSum{-sy.E, -sy.M};
+            }
         }
-        if (PULL && g.wall()) reconstruct_wall<QT>(c, n, x, y, qf, qg, qh);
+        if (PULL && g.wall()) reconstruct_wall<QT>(walls.node(x, y), n, qf, qg, qh);
     }
 
     Moments<R, RH> mo;
@@ -1313,12 +1355,12 @@ LBM_HD RH update_node(const CavityConst<R> &c, const NodeConst<R, RH> &n, bool e
     if (edge) {
         // outflow: post-collision populations aimed at wall nodes
         if (tally && g.near_x()) {
-            wall_links<QT, true, true>(c, x == 1, false, false, qf, qg, qh, sx);
-            acc.add_column(x == 1, y, sx);
+            const LinkSum o = wall_links<QT, true, true>(walls, lo, false, false, qf, qg, qh);
+            acc.add_column(lo, y, LinkSum{sx.E - o.E, sx.M - o.M});
         }
         if (tally && g.near_y()) {
-            wall_links<QT, false, true>(c, y == 1, g.near_x() && x == 1, g.near_x() && x != 1, qf, qg, qh, sy);
-            acc.add_row(y == 1, x, sy);
+            const LinkSum o = wall_links<QT, false, true>(walls, y == 1, lo, hi, qf, qg, qh);
+            acc.add_row(y == 1, x, LinkSum{sy.E - o.E, sy.M - o.M});
         }
     }
     return srf;
@@ -1336,8 +1378,8 @@ LBM_HD void step_node(const CavityConst<R> &c, const void *src, void *dst, const
     const int64_t kf = flat_index(c, x, y);
     Thermo<RH> th;
     Macro<R> m;
-    const RH srf = update_node<Lay::QT, R, RH, PULL>(c, n, true, g, x, y, qf, qg, qh, sr_src[kf], true,
-                                                          CavityTally<R>{acc, c}, th, m);
+    const RH srf = update_node<Lay::QT, R, RH, PULL>(TableWalls<R, RH>{c}, n, true, g, x, y, qf, qg, qh, sr_src[kf], true,
+                                                          CavityTally<double, R>{acc, c}, th, m);
     const ThermalConst<RH> &t = thermal<RH>(c);
     const FarRef k = any_band(c)(x, y);
     void *blk = band_block(c, dst, 0);
@@ -1362,8 +1404,8 @@ LBM_HD void step_node_view(const CavityConst<R> &c, const NodeConst<R, RH> &n, b
     const int64_t kf = flat_index(c, x, y);
     Thermo<RH> th;
     Macro<R> m;
-    const RH srf = update_node<Lay::QT, R, RH, PULL>(c, n, edge, g, x, y, qf, qg, qh, sr_src[kf], true,
-                                                          CavityTally<R>{acc, c}, th, m);
+    const RH srf = update_node<Lay::QT, R, RH, PULL>(TableWalls<R, RH>{c}, n, edge, g, x, y, qf, qg, qh, sr_src[kf], true,
+                                                          CavityTally<double, R>{acc, c}, th, m);
     const NodeRef k = v.org(x, y);
     Lay::template put<R>(dst, v.stride, 0, qf, m.drho, k, n);
     Lay::template put<RH>(dst, v.stride, 1, qg, n.cf_base * (th.Tf - n.Tf_ref), k, n);
@@ -1634,8 +1676,8 @@ LBM_HD TileView<R> tile_view(const CavityConst<R> &c, Tile2 tl) {
     return t;
 }
 template <class T, typename R>
-LBM_HD T tally_of(const CavityTally<R> &all, double *lds, const TileView<R> &tv) {
-    if constexpr (std::is_same<T, CavityTally<R>>::value) return all;
+LBM_HD T tally_of(const CavityTally<double, R> &all, double *lds, const TileView<R> &tv) {
+    if constexpr (std::is_same<T, CavityTally<double, R>>::value) return all;
     else return T{all, lds, tv.tl.x0, tv.tl.y0};
 }
 template <typename T>
@@ -1655,10 +1697,10 @@ LBM_HD int mod_by(int t) {
 }
 
 // Push placement: population i of the node at window position (wx, wy) goes
-// to the slot of x + e_i if that lies in the window; Sr_f to the node's own.
+// to the slot of x + e_i if that lies in the window.
 template <class Sh, typename R, typename RH>
-LBM_HD void lds_push(const NodeConst<R, RH> &n, int wx, int wy, void *lds_q, R *lds_sr, const R qf[9],
-                     const RH qg[9], const R qh[9], RH srf) {
+LBM_HD void lds_push(const NodeConst<R, RH> &n, int wx, int wy, void *lds_q, const R qf[9], const RH qg[9],
+                     const R qh[9]) {
     using Cd = typename Sh::Codec;
     const int own = wy * Sh::WW + wx;
 #pragma unroll
@@ -1673,7 +1715,13 @@ LBM_HD void lds_push(const NodeConst<R, RH> &n, int wx, int wy, void *lds_q, R *
             }
         }
     }
-    if ((unsigned)wx < (unsigned)Sh::WW && (unsigned)wy < (unsigned)Sh::WH) lds_sr[own] = (R)srf;
+}
+// The same, and Sr_f to the node's own slot.
+template <class Sh, typename R, typename RH>
+LBM_HD void lds_push(const NodeConst<R, RH> &n, int wx, int wy, void *lds_q, R *lds_sr, const R qf[9], const RH qg[9],
+                     const R qh[9], RH srf) {
+    lds_push<Sh, R, RH>(n, wx, wy, lds_q, qf, qg, qh);
+    if ((unsigned)wx < (unsigned)Sh::WW && (unsigned)wy < (unsigned)Sh::WH) lds_sr[wy * Sh::WW + wx] = (R)srf;
 }
 
 // Split layouts, before the first update: thread t (of NT) copies the
@@ -1764,7 +1812,7 @@ LBM_HD void stepk_first(const TileView<R> &tv, const NodeConst<R, RH> &n, const 
     RH qg[9];
     LinkSum ax, ay;  // the tallies so far, read with the populations
     const bool tx = tv.edge && (g.kind & NODE_OWNED) && g.near_x(), ty = tv.edge && (g.kind & NODE_OWNED) && g.near_y();
-    if constexpr (!std::is_same<Tally, CavityTally<R>>::value) {
+    if constexpr (!std::is_same<Tally, CavityTally<double, R>>::value) {
         if (tx) ax = LinkSum{acc.all.column(x == 1, y)[0], acc.all.column(x == 1, y)[1]};
         if (ty) ay = LinkSum{acc.all.row(y == 1, x)[0], acc.all.row(y == 1, x)[1]};
     }
@@ -1776,7 +1824,7 @@ LBM_HD void stepk_first(const TileView<R> &tv, const NodeConst<R, RH> &n, const 
         gather_view<Lay, R, RH, true>(n, b, tv.v, g, qf, qg, qh);
     }
     (void)lds_b;
-    if constexpr (!std::is_same<Tally, CavityTally<R>>::value) {
+    if constexpr (!std::is_same<Tally, CavityTally<double, R>>::value) {
         if (tx) acc.column(x == 1, y)[0] = ax.E, acc.column(x == 1, y)[1] = ax.M;
         if (ty) acc.row(y == 1, x)[0] = ay.E, acc.row(y == 1, x)[1] = ay.M;
     }
@@ -1784,7 +1832,7 @@ LBM_HD void stepk_first(const TileView<R> &tv, const NodeConst<R, RH> &n, const 
     Macro<R> m;
     const R sr_prev = ld_block<R>(blocks_at(sr_src + tv.flat_row, 0), 0, (uint32_t)((y - tv.yb) * tv.v.nx + xx) * sizeof(R), 0);
     const RH srf =
-        update_node<Sh::QT, R, RH, true>(c, n, tv.edge, g, xx, y, qf, qg, qh, sr_prev, g.kind & NODE_OWNED, acc, th, m);
+        update_node<Sh::QT, R, RH, true>(TableWalls<R, RH>{c}, n, tv.edge, g, xx, y, qf, qg, qh, sr_prev, g.kind & NODE_OWNED, acc, th, m);
     if constexpr (Sh::PUSH) {
         lds_push<Sh, R, RH>(n, lx - RG + Sh::WR, ly - RG + Sh::WR, lds_q, lds_sr, qf, qg, qh, srf);
     } else {
@@ -1874,7 +1922,7 @@ LBM_HD void stepk_mid_store(const TileView<R> &tv, const NodeConst<R, RH> &n, Ta
     using Sh = StepKShape<Lay, TW, TH, K>;
     Thermo<RH> th;
     Macro<R> m;
-    const RH srf = update_node<Sh::QT, R, RH, true>(tv.c, n, tv.edge, q.g, q.xx, q.y, q.qf, q.qg, q.qh, q.sr_prev,
+    const RH srf = update_node<Sh::QT, R, RH, true>(TableWalls<R, RH>{tv.c}, n, tv.edge, q.g, q.xx, q.y, q.qf, q.qg, q.qh, q.sr_prev,
                                                    q.g.kind & NODE_OWNED, acc, th, m);
     if constexpr (Sh::PUSH) {
         lds_push<Sh, R, RH>(n, q.lx - J + Sh::WR, q.ly - J + Sh::WR, lds_q, lds_sr, q.qf, q.qg, q.qh, srf);
@@ -1911,7 +1959,7 @@ LBM_HD void stepk_last(const TileView<R> &tv, const NodeConst<R, RH> &n, void *d
     Thermo<RH> th;
     Macro<R> m;
     const RH srf =
-        update_node<Sh::QT, R, RH, true>(c, n, tv.edge, g, x, y, qf, qg, qh, lds_sr[own], true, acc, th, m);
+        update_node<Sh::QT, R, RH, true>(TableWalls<R, RH>{c}, n, tv.edge, g, x, y, qf, qg, qh, lds_sr[own], true, acc, th, m);
     const NodeRef k = tv.v.org(x, y);
     const Blocks b = blocks_at(dst, tv.block);
     Lay::template put<R>(b, tv.v.stride, 0, qf, m.drho, k, n);
@@ -1929,7 +1977,7 @@ template <class Lay, typename R, typename RH, int TW, int TH, int K>
 LBM_HD void stepk_first(const CavityConst<R> &c, const Tile2 &tl, const void *src, const R *__restrict__ sr_src,
                         double *__restrict__ acc, void *lds_q, R *lds_sr, const float *lds_b, int s) {
     stepk_first<Lay, R, RH, TW, TH, K>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl), node_const_of<RH>(c), src, sr_src,
-                                       CavityTally<R>{acc, c}, lds_q, lds_sr, lds_b, s);
+                                       CavityTally<double, R>{acc, c}, lds_q, lds_sr, lds_b, s);
 }
 template <class Lay, typename R, typename RH, int TW, int TH, int K>
 LBM_HD bool stepk_mid_load(const CavityConst<R> &c, const Tile2 &tl, int j, const void *lds_q, const R *lds_sr, int t,
@@ -1943,14 +1991,158 @@ LBM_HD bool stepk_mid_load(const CavityConst<R> &c, const Tile2 &tl, int j, cons
 template <class Lay, typename R, typename RH, int TW, int TH, int K>
 LBM_HD void stepk_mid_store(const CavityConst<R> &c, const Tile2 &tl, double *__restrict__ acc, void *lds_q, R *lds_sr,
                             MidNode<R, RH> &q) {
-    stepk_mid_store<Lay, R, RH, TW, TH, K, 1>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl), node_const_of<RH>(c), CavityTally<R>{acc, c},
+    stepk_mid_store<Lay, R, RH, TW, TH, K, 1>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl), node_const_of<RH>(c), CavityTally<double, R>{acc, c},
                                               lds_q, lds_sr, q);
 }
 template <class Lay, typename R, typename RH, int TW, int TH, int K>
 LBM_HD void stepk_last(const CavityConst<R> &c, const Tile2 &tl, void *dst, R *__restrict__ sr_dst,
                        double *__restrict__ acc, const void *lds_q, const R *lds_sr, int s) {
     stepk_last<Lay, R, RH, TW, TH, K>(tile_view<StepKShape<Lay, TW, TH, K>>(c, tl), node_const_of<RH>(c), dst, sr_dst,
-                                      CavityTally<R>{acc, c}, lds_q, lds_sr, s);
+                                      CavityTally<double, R>{acc, c}, lds_q, lds_sr, s);
+}
+
+// ---------------------------------------------------------------------------
+// Deep launches: up to K steps per launch for cavities of so few tiles that a
+// launch's fixed cost and one tile's latency, not the GPU's throughput, set
+// the time.  One thread keeps one node of the tile's region (the tile and a
+// ring of K - 1) for the whole launch: its place, geometry, source and wall
+// tallies and the update's constants stay in registers, its populations pass
+// through LDS planes that cover the region (every node writes its own slot
+// and reads its neighbours'; a push, with its masked writes, took 1000 of an
+// update's 5700 cycles).  A launch of k <= K steps runs k updates, each of the
+// nodes at most as deep in the ring as updates are left; the steps are those
+// of the K-step kernels, so the bits are too.
+// ---------------------------------------------------------------------------
+template <class Lay, int TW, int TH, int K>
+struct DeepShape {
+    static constexpr int QT = Lay::QT, TILE_W = TW, RING = K - 1;
+    static constexpr int PW = TW + 2 * RING, PH = TH + 2 * RING;  // thread map: the region, row by row
+    static constexpr int NT = (PW * PH + 63) / 64 * 64;
+    static constexpr bool PUSH = false;
+    static constexpr int WR = RING, WW = PW, NSLOT = PW * PH;  // LDS window: a slot per node
+    using Codec = LdsCodec<Lay>;
+    static constexpr size_t LDS_BYTES = Codec::bytes(NSLOT);
+    static_assert(K >= 2 && NT <= 1024 && LDS_BYTES <= 160 * 1024, "one thread per node, one workgroup's LDS");
+    static_assert(TH + 2 * K <= LBM_MIN_BAND_ROWS, "a tile's rows must span at most two bands");
+};
+
+// A node's tallies so far, in registers.
+struct NodeTally {
+    LinkSum &x, &y;
+    LBM_HD void add_column(bool, int, LinkSum s) const { x = LinkSum{x.E + s.E, x.M + s.M}; }
+    LBM_HD void add_row(bool, int, LinkSum s) const { y = LinkSum{y.E + s.E, y.M + s.M}; }
+};
+
+// The walls' constants of one node, in registers.
+template <typename R, typename RH>
+struct KeptWalls {
+    WallNode<R, RH> wall;
+    double phi_l, phi_m;  // CavityConst::we, wm
+    LBM_HD const WallNode<R, RH> &node(int, int) const { return wall; }
+    LBM_HD double we() const { return phi_l; }
+    LBM_HD double wm() const { return phi_m; }
+};
+
+template <typename R, typename RH>
+struct DeepNode {
+    int from;      // slot it pulls through: its own, or its wall partner's
+    int depth;     // rings outside the tile (0: the tile's own); INT32_MAX: no node
+    int x, y;      // in the cavity
+    NodeGeom g;
+    R qf[9], qh[9], sr;
+    RH qg[9];
+    Thermo<RH> th;
+    Macro<R> m;
+    LinkSum tx, ty;
+    KeptWalls<R, RH> walls;
+};
+
+// Thread t's node, and its populations, source and tallies from global
+// memory if the first of k updates covers it.
+template <class Sh, class Lay, typename R, typename RH>
+LBM_HD void deep_load(const TileView<R> &tv, const NodeConst<R, RH> &n, const void *src, const R *__restrict__ sr_src,
+                      const double *__restrict__ acc, int k, int t, DeepNode<R, RH> &q) {
+    const CavityConst<R> &c = tv.c;
+    const Tile2 &tl = tv.tl;
+    const int lx = mod_by<Sh::PW>(t), ly = div_by<Sh::PW>(t);
+    const int x = tl.x0 - Sh::RING + lx, y = tl.y0 - Sh::RING + ly;  // unwrapped
+    const int ox = lx < Sh::RING ? Sh::RING - lx : lx - Sh::RING - tl.w + 1;
+    const int oy = ly < Sh::RING ? Sh::RING - ly : ly - Sh::RING - tl.h + 1;
+    q.depth = ox > oy ? (ox > 0 ? ox : 0) : (oy > 0 ? oy : 0);
+    q.x = x;
+    q.y = y;
+    q.g = NodeGeom{0, x, y};
+    q.from = t;
+    if (tv.edge) {
+        if (c.periodic) q.x = x < 0 ? x + c.nx : (x >= c.nx ? x - c.nx : x);
+        if (q.x < 0 || q.x >= c.nx || y < 0 || y >= c.ny) {
+            q.depth = INT32_MAX;
+        } else {
+            q.g = geometry(c, q.x, y, true);
+            if (q.depth == 0) q.g.kind |= NODE_OWNED;
+            q.from += (q.g.sy - y) * Sh::WW + (q.g.sx - q.x);
+        }
+    }
+    if (q.depth > k - 1) {
+        q.depth = INT32_MAX;
+        return;
+    }
+    LBM_HOST_CHECK(q.x >= 0 && q.x < c.nx && y >= 0 && y < c.ny);
+    LBM_HOST_CHECK(tv.edge || (x >= 2 && x <= c.nx - 3 && y >= 2 && y <= c.ny - 3));
+    LBM_HOST_CHECK(q.g.sy - 1 >= tv.yb && q.g.sy + 1 < tv.yb + LBM_MIN_BAND_ROWS);
+    LBM_HOST_CHECK(q.g.sy + 1 < tv.v.org.y_next + (tv.v.flat ? 0 : c.band_rows));
+    if (tv.edge) {
+        // read with the populations, for all updates
+        KeptWalls<R, RH> w{wall_node<RH>(c, q.x, y), c.we, c.wm};
+        resident<true>(w.wall.c_fref), resident<true>(w.wall.inv_phi), resident<true>(w.wall.inv_cs2);
+        resident<true>(w.wall.c_mref), resident<true>(w.phi_l), resident<true>(w.phi_m);
+        if constexpr (Lay::QT == 5) resident<true>(w.wall.varpi), resident<true>(w.wall.varpi_m);
+        q.walls = w;
+    }
+    if (tv.edge && (q.g.kind & NODE_OWNED)) {
+        const CavityTally<const double, R> a{acc, c};
+        if (q.g.near_x()) q.tx = LinkSum{a.column(x == 1, y)[0], a.column(x == 1, y)[1]};
+        if (q.g.near_y()) q.ty = LinkSum{a.row(y == 1, q.x)[0], a.row(y == 1, q.x)[1]};
+    }
+    gather_view<Lay, R, RH, true>(n, blocks_at(src, tv.block), tv.v, q.g, q.qf, q.qg, q.qh);
+    q.sr = ld_block<R>(blocks_at(sr_src + tv.flat_row, 0), 0, (uint32_t)((y - tv.yb) * tv.v.nx + q.x) * sizeof(R), 0);
+}
+// The update with `left` updates to follow it; true: the thread's node took part.
+template <class Sh, typename R, typename RH>
+LBM_HD bool deep_update(const TileView<R> &tv, const NodeConst<R, RH> &n, int left, DeepNode<R, RH> &q) {
+    if (q.depth > left) return false;
+    q.sr = (R)update_node<Sh::QT, R, RH, true>(q.walls, n, tv.edge, q.g, q.x, q.y, q.qf, q.qg, q.qh, q.sr,
+                                              q.g.kind & NODE_OWNED, NodeTally{q.tx, q.ty}, q.th, q.m);
+    return true;
+}
+// After a barrier, thread t's populations to its slot; after another, the
+// pulls of the next update, which `left` updates follow.
+template <class Sh, typename R, typename RH>
+LBM_HD void deep_put(const NodeConst<R, RH> &n, void *lds_q, int t, const DeepNode<R, RH> &q) {
+    Sh::Codec::put_node(lds_q, Sh::NSLOT, t, n, q.qf, q.qg, q.qh, q.m.drho, n.cf_base * (q.th.Tf - n.Tf_ref),
+                        n.cm_base * q.m.dTm);
+}
+template <class Sh, typename R, typename RH>
+LBM_HD void deep_pull(const NodeConst<R, RH> &n, const void *lds_q, int left, DeepNode<R, RH> &q) {
+    if (q.depth <= left) lds_gather<Sh, R, RH>(n, q.from, lds_q, q.qf, q.qg, q.qh);
+}
+// The tile's own nodes to global memory.
+template <class Sh, class Lay, typename R, typename RH>
+LBM_HD void deep_store(const TileView<R> &tv, const NodeConst<R, RH> &n, void *dst, R *__restrict__ sr_dst,
+                       double *__restrict__ acc, const DeepNode<R, RH> &q) {
+    if (q.depth != 0) return;
+    const CavityConst<R> &c = tv.c;
+    const NodeRef k = tv.v.org(q.x, q.y);
+    const Blocks b = blocks_at(dst, tv.block);
+    Lay::template put<R>(b, tv.v.stride, 0, q.qf, q.m.drho, k, n);
+    Lay::template put<RH>(b, tv.v.stride, 1, q.qg, n.cf_base * (q.th.Tf - n.Tf_ref), k, n);
+    Lay::template put<R>(b, tv.v.stride, 2, q.qh, n.cm_base * q.m.dTm, k, n);
+    *(R *)((char *)(sr_dst + tv.flat_row) + (uint32_t)((q.y - tv.yb) * tv.v.nx + q.x) * (uint32_t)sizeof(R)) = q.sr;
+    if (tv.edge) {
+        const CavityTally<double, R> a{acc, c};
+        if (q.g.near_x()) a.column(q.x == 1, q.y)[0] = q.tx.E, a.column(q.x == 1, q.y)[1] = q.tx.M;
+        if (q.g.near_y()) a.row(q.y == 1, q.x)[0] = q.ty.E, a.row(q.y == 1, q.x)[1] = q.ty.M;
+    }
 }
 
 // Macroscopic fields of one node (post-streaming state) plus its
@@ -1991,7 +2183,7 @@ LBM_HD void macro_node(const CavityConst<R> &c, const void *src, bool raw, int x
         }
     }
     const NodeConst<R, RH> &n = node_const_of<RH>(c);
-    if (!raw && g.wall()) reconstruct_wall<Lay::QT>(c, n, x, y, qf, qg, qh);
+    if (!raw && g.wall()) reconstruct_wall<Lay::QT>(wall_node<RH>(c, x, y), n, qf, qg, qh);
     double sg = 0.0, sh = 0.0, sf = 0.0;
 #pragma unroll
     for (int i = 0; i < 9; ++i) {

@@ -180,4 +180,31 @@ constexpr TileDims dims_of(int i) {
     return i == 0 ? TileDims{StepKTile<ST, K>::TW, StepKTile<ST, K>::TH} : alt_dims(ST, K, i);
 }
 
+// Deep launches: tiles of a handle that fits one per CU, and the most steps
+// of a launch.  Of the shapes that leave at most kDeepTiles tiles the first
+// (smallest) is taken: a launch's fixed part (2.4 us between launches, 0.5 for
+// its constants, 1.4 for the cold first loads, 0.5 for the stores) is shared
+// by its steps, and an update costs what its waves per SIMD make it, so
+// shapes trade steps for waves.  us a step against the K-step kernels, one
+// MI355X: FP32_H64 64^2 8x8x6 4.46 -> 2.73 (8x8x7 2.92, 12x12x6 3.14), 151^2
+// 12x12x6 4.46 -> 3.26, 200^2 16x12x6 4.5 -> 3.69, 256^2 16x16x5 4.45 -> 3.77
+// (x6 3.87, x4 4.21); FP64 64^2 8x8x5 5.86 -> 3.44 (x6 3.87, x4 3.83), 151^2
+// 16x8x4 5.41 -> 4.26 (x5 4.60), 200^2 16x12x4 6.18 -> 5.37, 256^2 16x16x4 7.17
+// -> 5.70; D2Q5 FP32 64^2 3.93 -> 2.13, 256^2 3.80 -> 2.82.  With two tiles on a
+// CU they lose (FP32_H64 300^2 16x16: 6.0 -> 7.7).
+constexpr int kDeepShapes = 4;
+constexpr int kDeepTiles = 256;  // the CUs of an MI355X
+struct DeepDims {
+    int tw, th, k;
+};
+constexpr bool deep_available(int st) {
+    return st == ST_F64 || st == ST_F32 || st == ST_F32H || st == ST5_F64 || st == ST5_F32 || st == ST5_F32H;
+}
+constexpr DeepDims deep_dims(int st, int i) {
+    const bool f64 = st == ST_F64 || st == ST5_F64;
+    const DeepDims wide[kDeepShapes] = {{8, 8, 5}, {16, 8, 4}, {16, 12, 4}, {16, 16, 4}};
+    const DeepDims narrow[kDeepShapes] = {{8, 8, 6}, {12, 12, 6}, {16, 12, 6}, {16, 16, 5}};
+    return f64 ? wide[i] : narrow[i];
+}
+
 }  // namespace lbm

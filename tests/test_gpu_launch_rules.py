@@ -47,3 +47,54 @@ def test_many_rounds_of_tiles_are_bitwise_single_steps(lbm, prec, qt, sizes):
     # over three rounds of tiles (fetching ahead), 50 and 53 tile columns (two strips), ragged edges
     ps = [_cavity(nx, ny, qt) for nx, ny in sizes]
     _same(_run(lbm, ps, prec, 20, 1), _run(lbm, ps, prec, 20))
+
+
+DEEP = {
+    "smallest": lambda q: [_cavity(4, 4, q)],
+    "thin": lambda q: [_cavity(5, 37, q)],
+    "256 smallest tiles": lambda q: [_cavity(128, 128, q)],
+    "one column more": lambda q: [_cavity(129, 128, q)],
+    "151": lambda q: [_cavity(151, 151, q)],
+    "193x191": lambda q: [_cavity(193, 191, q)],
+    "256 largest tiles": lambda q: [_cavity(256, 256, q)],
+    "not deep": lambda q: [_cavity(257, 256, q)],
+    "corner walls": lambda q: [dict(W.case_corner(100)[0], thermal_lattice=q)],
+    "bounce-back": lambda q: [dict(_cavity(41, 60, q), solid_treatment=1)],
+    "batch": lambda q: [_cavity(33, 70, q), _cavity(64, 48, q), _cavity(16, 16, q)],
+    "bands": lambda q: [dict(_cavity(70, 150, q), band_rows=34)],
+}
+
+
+@pytest.mark.parametrize("prec", ["f64", "f32", "f32h64"])
+@pytest.mark.parametrize("qt", [9, 5])
+@pytest.mark.parametrize("case", list(DEEP))
+def test_small_handles_are_bitwise_single_steps(lbm, case, qt, prec):
+    # handles of at most 256 small tiles run deep launches; every count of
+    # steps up to a launch's most, a replayed graph and a remainder of one
+    ps = DEEP[case](qt)
+    chunks = [1, 2, 3, 4, 5, 6, 7, 197, 1]
+    ref = _run(lbm, ps, prec, sum(chunks), 1)
+    s = lbm.Solver(ps if len(ps) > 1 else ps[0], prec)
+    for c, q in enumerate(ps):
+        s.set_initial(c, *W.initial_temperatures(q, 30 + c, amplitude=1e-2))
+    for n in chunks:
+        s.step(n)
+    got = [(s.state(c), s.diagnostics(c)) for c in range(len(ps))]
+    s.close()
+    _same(ref, got)
+
+
+def test_autotune_keeps_or_leaves_the_deep_launches(lbm, tmp_path):
+    # whichever it picks, the bits stay, and the cached choice is taken again
+    p = _cavity(64, 64, 9)
+    ref = _run(lbm, [p], "f32h64", 200, 1)
+    path = str(tmp_path / "tune.txt")
+    for _ in range(2):
+        s = lbm.Solver(p, "f32h64")
+        s.set_initial(0, *W.initial_temperatures(p, 30, amplitude=1e-2))
+        s.step(7)
+        lbm.lbm_autotune(s.h, 3, path)
+        s.step(193)
+        _same(ref, [(s.state(0), s.diagnostics(0))])
+        s.close()
+    assert len(open(path).read().splitlines()) == 1
