@@ -320,7 +320,7 @@ constexpr int stepk_waves_per_eu() {
 // CU); the 16-bit and D2Q9 FP32_H64 forms fit the bound only by spilling
 // and lose 5-24%.
 #ifndef LBM_WPE_MASK
-#define LBM_WPE_MASK ((1 << ST_F32) | (1 << ST5_F32) | (1 << ST5_F32H))
+#define LBM_WPE_MASK ((1 << ST5_F32) | (1 << ST5_F32H))
 #endif
 template <int ST, class Lay, typename R, int TW, int TH, int NT, int K>
 constexpr int stepk_wpe() {

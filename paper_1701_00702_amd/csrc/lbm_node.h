@@ -125,6 +125,14 @@ LBM_HD void resident(T &v) {
     (void)v;
 #endif
 }
+// The same for a condition held as an integer, so that testing it is a scalar
+// compare and not a lane mask.
+LBM_HD void resident_flag(int &v) {
+#if defined(__HIP_DEVICE_COMPILE__)
+    v = __builtin_amdgcn_readfirstlane(v);
+#endif
+    resident(v);
+}
 template <class Lay, bool VECTOR, class N>
 LBM_HD void reside(N &n) {
     constexpr bool V = VECTOR;
@@ -134,7 +142,8 @@ LBM_HD void reside(N &n) {
     resident<V>(n.inv_phi), resident<V>(n.drag_lin), resident<V>(n.drag_quad), resident<V>(n.l0), resident<V>(n.l0sq);
     resident<V>(n.l1), resident<V>(n.fA7), resident<V>(n.fB7), resident<V>(n.fC7);
     resident<V>(n.hv_m), resident<V>(n.sr_ratio);
-    resident<V>(n.T_ref), resident<V>(n.mA0), resident<V>(n.mB0), resident<V>(n.mA1), resident<V>(n.mA3);
+    if constexpr (sizeof(n.T_ref) != sizeof(n.Tf_ref)) resident<V>(n.T_ref);
+    resident<V>(n.mA0), resident<V>(n.mB0), resident<V>(n.mA1), resident<V>(n.mA3);
     resident<V>(n.me1), resident<V>(n.zA1), resident<V>(n.zB1), resident<V>(n.zA3), resident<V>(n.zB3);
     resident<V>(n.ge1);
     resident(n.bounce_back);
@@ -709,7 +718,7 @@ LBM_HD void macros_of(const NodeConst<R, RH> &n, Moments<R, RH> &mo, Thermo<RH> 
     m.fl = (R)th.fl;
     // Eq. (48), c_pm = 1
     m.dTm = mo.h[0];
-    m.Tm = n.T_ref + m.dTm;
+    m.Tm = (std::is_same<R, RH>::value ? (R)n.Tf_ref : n.T_ref) + m.dTm;
     // Eq. (21)
     m.drho = mo.f[0];
     m.rho = R(1) + m.drho;
@@ -1142,13 +1151,15 @@ LBM_HD void gather(const CavityConst<R> &c, const void *buf, const NodeGeom &g, 
 struct View {
     BandOrigin org;
     uint32_t stride;
-    int nx;
-    bool flat, periodic;
+    int nx, flat, periodic;
 };
+LBM_HD NodeRef place_of(const View &v, int x, int y) {
+    return v.flat ? NodeRef{(uint32_t)((y - v.org.y_first) * v.org.pitch + x), 0u} : v.org(x, y);
+}
 template <typename R>
 LBM_HD View view_of(const CavityConst<R> &c, int ba, int last_row) {
     const BandOrigin org = band_origin(c, ba);
-    return View{org, (uint32_t)c.band_nodes, c.nx, !c.periodic && last_row < org.y_next, c.periodic != 0};
+    return View{org, (uint32_t)c.band_nodes, c.nx, !c.periodic && last_row < org.y_next, c.periodic};
 }
 
 // The node pulled along direction i by the node whose neighbourhood is at
@@ -1304,14 +1315,14 @@ LBM_HD void link_content(const CavityConst<R> &c, int i, const R qf[9], const RH
 // workgroup may be a wall node or next to one; without it the wall code is
 // passed by a scalar branch.
 template <int QT, typename R, typename RH, bool PULL, class Walls, class Tally>
-LBM_HD RH update_node(const Walls &walls, const NodeConst<R, RH> &n, bool edge, const NodeGeom &g, int x, int y,
+LBM_HD RH update_node(const Walls &walls, const NodeConst<R, RH> &n, int edge, const NodeGeom &g, int x, int y,
                       R qf[9], RH qg[9], R qh[9], R sr_prev, bool tally, Tally acc, Thermo<RH> &th, Macro<R> &m) {
     // Wall tallies: an interior node next to a wall owns one slot per wall it
     // touches (x: the vertical wall, y: the horizontal one).  Set and read
     // under the same conditions only.
     LinkSum sx, sy;
-    const bool lo = edge && g.near_x() && x == 1, hi = edge && g.near_x() && x != 1;
     if (edge) {
+        const bool lo = g.near_x() && x == 1, hi = g.near_x() && x != 1;
         // inflow: populations pulled from wall nodes (post-collision of the
         // previous step; the first step has none, and counts the outflow's
         // reference)
@@ -1353,6 +1364,7 @@ LBM_HD RH update_node(const Walls &walls, const NodeConst<R, RH> &n, bool edge, 
     }
 
     if (edge) {
+        const bool lo = g.near_x() && x == 1, hi = g.near_x() && x != 1;
         // outflow: post-collision populations aimed at wall nodes
         if (tally && g.near_x()) {
             const LinkSum o = wall_links<QT, true, true>(walls, lo, false, false, qf, qg, qh);
@@ -1393,7 +1405,7 @@ LBM_HD void step_node(const CavityConst<R> &c, const void *src, void *dst, const
 // The same within a workgroup's view of the buffers (src and dst are the
 // blocks of the view's first band); edge as for update_node.
 template <class Lay, typename R, typename RH, bool PULL>
-LBM_HD void step_node_view(const CavityConst<R> &c, const NodeConst<R, RH> &n, bool edge, Blocks src, Blocks dst,
+LBM_HD void step_node_view(const CavityConst<R> &c, const NodeConst<R, RH> &n, int edge, Blocks src, Blocks dst,
                            const View &v, const R *__restrict__ sr_src, R *__restrict__ sr_dst,
                            double *__restrict__ acc, int x, int y) {
     NodeGeom g{0, x, y};
@@ -1655,10 +1667,10 @@ template <typename R>
 struct TileView {
     View v;
     Tile2 tl;
-    int ny, yb;        // first row
+    int yb;            // first row
     int64_t block;     // byte offset of the block of the first row's band in a state buffer
     int64_t flat_row;  // flat index of the first row
-    bool edge;
+    int edge;
     const CavityConst<R> &c;
 };
 template <class Sh, typename R>
@@ -1667,12 +1679,13 @@ LBM_HD TileView<R> tile_view(const CavityConst<R> &c, Tile2 tl) {
     const int yb = tl.y0 >= K ? tl.y0 - K : 0, last = tl.y0 + tl.h - 1 + K;
     const int ba = band_of(c, yb);
     const View v = view_of(c, ba, last < c.ny ? last : c.ny - 1);
-    const bool edge = c.periodic || tl.w < Sh::TILE_W || tl.x0 < M || tl.x0 + tl.w > c.nx - M || tl.y0 < M ||
-                      tl.y0 + tl.h > c.ny - M;
-    TileView<R> t{v, tl, c.ny, yb, c.pop_off + (int64_t)ba * c.band_bytes, c.node0 + (int64_t)yb * c.nx, edge, c};
-    resident(t.v.org.y_first), resident(t.v.org.y_next), resident(t.v.org.pitch), resident(t.v.org.band_bytes);
-    resident(t.v.stride), resident(t.v.nx), resident(t.tl.x0), resident(t.tl.y0), resident(t.tl.w), resident(t.tl.h);
-    resident(t.yb), resident(t.block), resident(t.flat_row);
+    // one scalar condition, without a branch per term
+    const int edge = (c.periodic != 0) | (tl.w < Sh::TILE_W) | (tl.x0 < M) | (tl.x0 + tl.w > c.nx - M) | (tl.y0 < M) |
+                     (tl.y0 + tl.h > c.ny - M);
+    TileView<R> t{v, tl, yb, c.pop_off + (int64_t)ba * c.band_bytes, c.node0 + (int64_t)yb * c.nx, edge, c};
+    resident(t.v.org.y_first), resident(t.v.org.pitch), resident(t.v.stride), resident(t.v.nx);
+    resident(t.tl.x0), resident(t.tl.y0), resident(t.tl.h), resident(t.block), resident(t.flat_row);
+    resident_flag(t.edge), resident_flag(t.v.flat);
     return t;
 }
 template <class T, typename R>
@@ -1739,7 +1752,7 @@ LBM_HD void stepk_stage_bases(const TileView<R> &tv, const void *src, float *lds
         const int bx = q % Sh::BP;
         if (bx >= tl.w + 2 * K) continue;
         const int x = tl.x0 - K + bx, y = tl.y0 - K + q / Sh::BP;  // unwrapped
-        if (y < 0 || y >= tv.ny) continue;
+        if (y < 0 || y >= tv.c.ny) continue;
         int xx = x;
         if (tv.v.periodic) xx = x < 0 ? x + tv.v.nx : (x >= tv.v.nx ? x - tv.v.nx : x);
         else if (x < 0 || x >= tv.v.nx) continue;
@@ -1811,10 +1824,10 @@ LBM_HD void stepk_first(const TileView<R> &tv, const NodeConst<R, RH> &n, const 
     R qf[9], qh[9];
     RH qg[9];
     LinkSum ax, ay;  // the tallies so far, read with the populations
-    const bool tx = tv.edge && (g.kind & NODE_OWNED) && g.near_x(), ty = tv.edge && (g.kind & NODE_OWNED) && g.near_y();
-    if constexpr (!std::is_same<Tally, CavityTally<double, R>>::value) {
-        if (tx) ax = LinkSum{acc.all.column(x == 1, y)[0], acc.all.column(x == 1, y)[1]};
-        if (ty) ay = LinkSum{acc.all.row(y == 1, x)[0], acc.all.row(y == 1, x)[1]};
+    const auto owned_near = [&](int near) { return (g.kind & (NODE_OWNED | near)) == (NODE_OWNED | near); };
+    if constexpr (!std::is_same<Tally, CavityTally<double, R>>::value) if (tv.edge) {
+        if (owned_near(NODE_NEAR_X)) ax = LinkSum{acc.all.column(x == 1, y)[0], acc.all.column(x == 1, y)[1]};
+        if (owned_near(NODE_NEAR_Y)) ay = LinkSum{acc.all.row(y == 1, x)[0], acc.all.row(y == 1, x)[1]};
     }
     if constexpr (Sh::STAGE_BASE) {
         const int px = x + (g.sx - xx);  // partner column, unwrapped
@@ -1824,9 +1837,9 @@ LBM_HD void stepk_first(const TileView<R> &tv, const NodeConst<R, RH> &n, const 
         gather_view<Lay, R, RH, true>(n, b, tv.v, g, qf, qg, qh);
     }
     (void)lds_b;
-    if constexpr (!std::is_same<Tally, CavityTally<double, R>>::value) {
-        if (tx) acc.column(x == 1, y)[0] = ax.E, acc.column(x == 1, y)[1] = ax.M;
-        if (ty) acc.row(y == 1, x)[0] = ay.E, acc.row(y == 1, x)[1] = ay.M;
+    if constexpr (!std::is_same<Tally, CavityTally<double, R>>::value) if (tv.edge) {
+        if (owned_near(NODE_NEAR_X)) acc.column(x == 1, y)[0] = ax.E, acc.column(x == 1, y)[1] = ax.M;
+        if (owned_near(NODE_NEAR_Y)) acc.row(y == 1, x)[0] = ay.E, acc.row(y == 1, x)[1] = ay.M;
     }
     Thermo<RH> th;
     Macro<R> m;
@@ -1960,7 +1973,7 @@ LBM_HD void stepk_last(const TileView<R> &tv, const NodeConst<R, RH> &n, void *d
     Macro<R> m;
     const RH srf =
         update_node<Sh::QT, R, RH, true>(TableWalls<R, RH>{c}, n, tv.edge, g, x, y, qf, qg, qh, lds_sr[own], true, acc, th, m);
-    const NodeRef k = tv.v.org(x, y);
+    const NodeRef k = place_of(tv.v, x, y);
     const Blocks b = blocks_at(dst, tv.block);
     Lay::template put<R>(b, tv.v.stride, 0, qf, m.drho, k, n);
     Lay::template put<RH>(b, tv.v.stride, 1, qg, n.cf_base * (th.Tf - n.Tf_ref), k, n);
@@ -2132,7 +2145,7 @@ LBM_HD void deep_store(const TileView<R> &tv, const NodeConst<R, RH> &n, void *d
                        double *__restrict__ acc, const DeepNode<R, RH> &q) {
     if (q.depth != 0) return;
     const CavityConst<R> &c = tv.c;
-    const NodeRef k = tv.v.org(q.x, q.y);
+    const NodeRef k = place_of(tv.v, q.x, q.y);
     const Blocks b = blocks_at(dst, tv.block);
     Lay::template put<R>(b, tv.v.stride, 0, q.qf, q.m.drho, k, n);
     Lay::template put<RH>(b, tv.v.stride, 1, q.qg, n.cf_base * (q.th.Tf - n.Tf_ref), k, n);
