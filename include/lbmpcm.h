@@ -200,9 +200,10 @@ typedef struct lbm_diag {
 /* Launch shape of the step kernels.  Every shape gives bit-identical results.
  * As long as no shape has been set, handles of at most 256 small tiles (one
  * cavity of about 256^2 nodes; FP32 and FP64 forms, not periodic) run four to
- * six steps per launch, in tiles of their own, wherever a call has them; what
- * lbm_get_launch reports is then the shape of handles beyond that size, which
- * lbm_set_launch puts in force.  lbm_autotune times both. */
+ * six steps per launch, in tiles of their own, wherever a call has them, and
+ * larger FP64 handles three (D2Q9: from about 320^2 nodes in all); what
+ * lbm_get_launch reports is then the shape that lbm_set_launch with the same
+ * values puts in force.  lbm_autotune times both. */
 typedef struct lbm_launch_config {
     int32_t block;            /* threads per workgroup: 64, 128, 256 or 512      */
     int32_t nodes_per_thread; /* 1, 2 or 4 consecutive-by-block nodes per thread */

@@ -117,6 +117,9 @@ struct Plan {
     // the tile shapes (0: not available for this storage)
     int64_t tilesk[4] = {0, 0, 0, 0};
     size_t off_tilesk[4] = {0, 0, 0, 0};
+    // steps of the library's own K-step launches where a caller can't ask for
+    // that many (0: none)
+    int own_k = 0;
     // deep launches: tile shape (-1: the handle takes none), tiles, most steps
     int deep = -1, deep_k = 0;
     int64_t deep_tiles = 0;
@@ -224,6 +227,19 @@ lbm_status make_plan(const lbm_params *p, int n, lbm_precision prec, Plan &pl) {
         off = align256(off + (size_t)pl.tilesk[k] * sizeof(Tile2));
     }
     choose_deep(p, n, pl);
+    if (!stepk_supported(st, 3) && pl.deep < 0) {
+        int tw, th;
+        stepk_tile(st, 3, 0, &tw, &th);
+        int64_t count = 0;
+        for (int c = 0; c < n; ++c) count += count_tiles2(p[c].nx, p[c].ny, tw, th);
+        if (stepk_three(st, count)) {
+            if (count >= ((int64_t)1 << 31)) return fail(LBM_EINVAL, "too many tiles");
+            pl.own_k = 3;
+            pl.tilesk[3] = count;
+            pl.off_tilesk[3] = off;
+            off = align256(off + (size_t)count * sizeof(Tile2));
+        }
+    }
     pl.off_deep = off;
     off = align256(off + (size_t)pl.deep_tiles * sizeof(Tile2));
     pl.stage_nodes = std::max<int64_t>(std::min(pl.max_nodes, kStageNodes), pl.max_nx);
@@ -274,8 +290,9 @@ struct lbm_handle {
     hipGraph_t gsrc[2] = {nullptr, nullptr};
     hipGraphExec_t graphk[4][2] = {};  // K-step launches, K = 2, 3
     hipGraph_t gsrck[4][2] = {};
-    // the launch shape is the library's own choice (lc: the K-step part of
-    // it): deep launches, where the handle has them
+    // the launch shape is the library's own choice (lc: the part of it that
+    // can be asked for): deep launches, or own_k steps per launch, where the
+    // handle has them
     bool own_shape = true;
     lbm_launch_config own_lc{};
     hipGraphExec_t graphd[2] = {nullptr, nullptr};
@@ -289,6 +306,8 @@ struct lbm_handle {
     Tile *dtiles() { return (Tile *)(ws + pl.off_tiles); }
     Tile2 *dtilesd() { return (Tile2 *)(ws + pl.off_deep); }
     bool deep() const { return own_shape && pl.deep >= 0; }
+    // steps of a launch of lbm_step that is not deep
+    int run_k() const { return own_shape && pl.own_k ? pl.own_k : lc.steps_per_launch; }
     Tile2 *dtilesk(int k) { return (Tile2 *)(ws + pl.off_tilesk[k]); }
     double *fields() { return (double *)(ws + pl.off_fields); }
     double *dout() { return (double *)(ws + pl.off_out); }
@@ -389,8 +408,8 @@ lbm_status build_tiles(lbm_handle *h, const lbm_launch_config &lc) {
     return LBM_OK;
 }
 
-// whether the plan has the tiles of K steps per launch
-bool has_k(const Plan &pl, int k) { return k == 1 || ((k == 2 || k == 3) && pl.tilesk[k] > 0); }
+// whether a caller may ask for K steps per launch
+bool has_k(const Plan &pl, int k) { return k == 1 || ((k == 2 || k == 3) && stepk_supported(pl.st, k)); }
 
 bool valid_launch(const lbm_launch_config &lc, const Plan &pl) {
     const bool b = lc.block == 64 || lc.block == 128 || lc.block == 256 || lc.block == 512;
@@ -510,7 +529,7 @@ lbm_status build_graph(lbm_handle *h, int parity, int kk, bool deep = false) {
 // every change of launch shape), so that no lbm_step spends host time on
 // capture and instantiation while the device waits.
 lbm_status prepare_graphs(lbm_handle *h) {
-    const int kk = h->lc.steps_per_launch;
+    const int kk = h->run_k();
     for (int parity = 0; parity < 2; ++parity) {
         if (h->deep()) {
             if (h->graphd[parity]) continue;
@@ -645,9 +664,9 @@ lbm_status setup(lbm_handle *h) {
         HIP_TRY(hipMemcpyAsync(h->cav(), t.data(), t.size() * sizeof(t[0]), hipMemcpyHostToDevice, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
     }
-    // By default the most steps per launch the form has (measured faster
-    // for every cavity size and batch, the rows being padded to 64 nodes).
-    h->lc.steps_per_launch = h->pl.tilesk[3] > 0 ? 3 : (h->pl.tilesk[2] > 0 ? 2 : 1);
+    // By default the most steps per launch that can be asked for (measured
+    // faster for every cavity size and batch, the rows being padded to 64 nodes).
+    h->lc.steps_per_launch = has_k(h->pl, 3) ? 3 : 2;
     h->own_lc = h->lc;
     lbm_status s = build_tiles(h, h->lc);
     if (s != LBM_OK) return s;
@@ -814,7 +833,7 @@ extern "C" lbm_status lbm_step(lbm_handle *h, int64_t n) {
         }
         return LBM_OK;
     }
-    const int kk = h->lc.steps_per_launch;
+    const int kk = h->run_k();
     if (kk > 1) {
         // runs of kk steps, one launch each (a launch swaps the buffers once)
         while (n >= (int64_t)kk * h->graph_chunk && h->graph_chunk > 0) {
@@ -1047,7 +1066,7 @@ extern "C" lbm_status lbm_get_launch(const lbm_handle *h, lbm_launch_config *out
 
 namespace {
 // Launch shape lc from here on; own: the library's choice, with deep launches
-// where the handle has them.
+// or own_k steps per launch where the handle has them.
 lbm_status apply_shape(lbm_handle *h, const lbm_launch_config &lc, bool own) {
     HIP_TRY(hipStreamSynchronize(h->stream));
     lbm_status s = build_tiles(h, lc);
@@ -1185,18 +1204,22 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
                     }
                 }
     }
-    // deep launches, with the library's own shape for the rest
-    if (h->pl.deep >= 0) {
-        const DeepLaunch L = deep_args(h, h->pl.deep_k, h->cur, h->acc_scratch());
-        hipError_t e = launch_deep(L, h->stream);
+    // the library's own launches: deep ones, or own_k steps each
+    if (h->pl.deep >= 0 || h->pl.own_k) {
+        const int own_k = h->pl.deep >= 0 ? h->pl.deep_k : h->pl.own_k;
+        auto own = [&]() -> hipError_t {
+            return h->pl.deep >= 0 ? launch_deep(deep_args(h, own_k, h->cur, h->acc_scratch()), h->stream)
+                                   : launch_stepk(stepk_args(h, own_k, h->cur, h->acc_scratch(), h->own_lc), h->stream);
+        };
+        hipError_t e = own();
         if (e == hipSuccess) e = hipEventRecord(e0, h->stream);
-        for (int k = 0; k < steps && e == hipSuccess; ++k) e = launch_deep(L, h->stream);
+        for (int k = 0; k < steps && e == hipSuccess; ++k) e = own();
         if (e == hipSuccess) e = hipEventRecord(e1, h->stream);
         if (e == hipSuccess) e = hipEventSynchronize(e1);
         float ms = 0;
         if (e == hipSuccess) e = hipEventElapsedTime(&ms, e0, e1);
-        if (e != hipSuccess) return abandon(fail(LBM_EDEVICE, "deep launch: %s", hipGetErrorString(e)));
-        if (ms / (float)(steps * h->pl.deep_k) < best_ms) {
+        if (e != hipSuccess) return abandon(fail(LBM_EDEVICE, "own launch: %s", hipGetErrorString(e)));
+        if (ms / (float)(steps * own_k) < best_ms) {
             best = h->own_lc;
             best_own = true;
         }

@@ -343,7 +343,7 @@ __global__ __launch_bounds__(NT, WPE) void stepk_kernel(const void *__restrict__
                                                    const CavityConst<R> *__restrict__ cav,
                                                    const Tile2 *__restrict__ tiles, int ntiles, int xcd_remap, int ahead) {
     using Sh = StepKShape<Lay, TW, TH, K>;
-    static_assert(Sh::LDS_BYTES + Sh::NSLOT * sizeof(R) + Sh::BASE_BYTES <= 65536, "tile exceeds 64 KiB of LDS");
+    static_assert(Sh::total_lds(Sh::TILE_TALLY) <= 80 * 1024, "fewer than two tiles per CU");
     static_assert(NT >= Sh::NFIRST && NT % 64 == 0, "one thread per node of the first update");
     __shared__ __align__(16) unsigned char lds_q[Sh::LDS_BYTES];
     __shared__ R lds_sr[Sh::NSLOT];
@@ -377,9 +377,11 @@ static hipError_t launch_stepk_i(const Step2Launch &L, hipStream_t s) {
     // and lose to it (FP32_H64 39.2 -> 37.6 GLUPS, FP64 21.2 -> 19.2).
     // Launches of fewer than three rounds of tiles have little to fetch for and
     // some lose (D2Q5 FP32 1001x613, 1.9 rounds: 11.7 -> 12.1 us a step; 2.6
-    // and 3.1 rounds: even; 4.3 rounds, FP32_H64 1024^2: 25.2 -> 24.6).
+    // and 3.1 rounds: even; 4.3 rounds, FP32_H64 1024^2: 25.2 -> 24.6).  FP64
+    // (two per CU): D2Q9 4096^2 660 -> 644 us a step, 1500^2 even; D2Q5 4096^2
+    // 430 -> 440, so it goes without.
     const int per_xcd = L.n_cu / 8, wgs = Sh::per_cu(Sh::TILE_TALLY);
-    const bool fetch = K == 3 && sizeof(R) == 4 && L.xcd_remap && L.ntiles / (wgs * L.n_cu) >= 3;
+    const bool fetch = K == 3 && ST != ST5_F64 && L.xcd_remap && L.ntiles / (wgs * L.n_cu) >= 3;
     const int ahead = fetch ? per_xcd + wgs * per_xcd / 2 : 0;
     if (L.grid >= L.ntiles) {
         hipLaunchKernelGGL((stepk_kernel<Lay, R, RH, Tl::TW, Tl::TH, Tl::NT, K, false,
@@ -389,7 +391,7 @@ static hipError_t launch_stepk_i(const Step2Launch &L, hipStream_t s) {
                            (const CavityConst<R> *)L.cav, L.tiles, L.ntiles, L.xcd_remap, ahead);
     } else {
         // persistent grids exist for the default shape only
-        if constexpr (I == 0)
+        if constexpr (I == 0 && stepk_offered(ST, K))
             hipLaunchKernelGGL((stepk_kernel<Lay, R, RH, Tl::TW, Tl::TH, Tl::NT, K, true, 1>), dim3(L.grid),
                                dim3(Tl::NT), 0, s, L.src, L.dst, (const R *)L.sr_src, (R *)L.sr_dst, L.acc,
                                (const CavityConst<R> *)L.cav, L.tiles, L.ntiles, L.xcd_remap, 0);
@@ -401,7 +403,8 @@ static hipError_t launch_stepk_i(const Step2Launch &L, hipStream_t s) {
 
 template <int ST, int K>
 static hipError_t launch_stepk_s(const Step2Launch &L, hipStream_t s) {
-    switch (L.shape) {
+    if constexpr (!stepk_offered(ST, K)) return L.shape == 0 ? launch_stepk_i<ST, K, 0>(L, s) : hipErrorInvalidValue;
+    else switch (L.shape) {
         case 0: return launch_stepk_i<ST, K, 0>(L, s);
         case 1: return launch_stepk_i<ST, K, 1>(L, s);
         case 2: return launch_stepk_i<ST, K, 2>(L, s);
@@ -409,7 +412,8 @@ static hipError_t launch_stepk_s(const Step2Launch &L, hipStream_t s) {
     }
 }
 
-bool stepk_supported(int storage, int k) { return stepk_available(storage, k); }
+bool stepk_supported(int storage, int k) { return stepk_offered(storage, k); }
+bool stepk_three(int storage, int64_t tiles) { return three_steps(storage, tiles); }
 
 template <int ST, int K>
 static void tile_of(int shape, int *tw, int *th) {
@@ -427,6 +431,8 @@ void stepk_tile(int storage, int k, int shape, int *tw, int *th) {
             case ST5_F32: return tile_of<ST5_F32, 3>(shape, tw, th);
             case ST_F32H: return tile_of<ST_F32H, 3>(shape, tw, th);
             case ST5_F32H: return tile_of<ST5_F32H, 3>(shape, tw, th);
+            case ST_F64: return shape == 0 ? tile_of<ST_F64, 3>(shape, tw, th) : void();
+            case ST5_F64: return shape == 0 ? tile_of<ST5_F64, 3>(shape, tw, th) : void();
             case ST_F16: return tile_of<ST_F16, 3>(shape, tw, th);
             case ST_BF16: return tile_of<ST_BF16, 3>(shape, tw, th);
             case ST_F16S: return tile_of<ST_F16S, 3>(shape, tw, th);
@@ -458,6 +464,8 @@ hipError_t launch_stepk(const Step2Launch &L, hipStream_t s) {
             case ST5_F32: return launch_stepk_s<ST5_F32, 3>(L, s);
             case ST_F32H: return launch_stepk_s<ST_F32H, 3>(L, s);
             case ST5_F32H: return launch_stepk_s<ST5_F32H, 3>(L, s);
+            case ST_F64: return launch_stepk_s<ST_F64, 3>(L, s);
+            case ST5_F64: return launch_stepk_s<ST5_F64, 3>(L, s);
             case ST_F16: return launch_stepk_s<ST_F16, 3>(L, s);
             case ST_BF16: return launch_stepk_s<ST_BF16, 3>(L, s);
             case ST_F16S: return launch_stepk_s<ST_F16S, 3>(L, s);

@@ -1608,6 +1608,10 @@ template <>
 struct PushLds<Plain<E64, false, 9>, 2> {
     static constexpr bool value = LBM_PUSH_F64_K2;
 };
+template <int QT>  // pulls would need the two-node ring in LDS: 95 KiB (D2Q9), one tile per CU
+struct PushLds<Plain<E64, false, QT>, 3> {
+    static constexpr bool value = true;
+};
 
 template <class Lay>
 struct IsSplitLayout {

@@ -9,13 +9,13 @@ namespace lbm {
 
 constexpr int round64(int n) { return (n + 63) / 64 * 64; }
 
-// Storage forms with a K-step kernel (K = 2, 3): two steps per launch for
-// every form, three for the FP32 and 16-bit ones (an FP64 tile with a
-// two-node ring leaves too few nodes per workgroup).
-constexpr bool stepk_available(int st, int k) {
-    const bool fp32 = st == ST_F32 || st == ST5_F32 || st == ST_F32H || st == ST5_F32H;
-    const bool b16 = st == ST_F16 || st == ST_BF16 || st == ST_F16S || st == ST_BF16S;
-    return k == 2 ? (fp32 || b16 || st == ST_F64 || st == ST5_F64) : (k == 3 ? (fp32 || b16) : false);
+// Storage forms with a K-step kernel: every form, K = 2, 3.
+constexpr bool stepk_available(int, int k) { return k == 2 || k == 3; }
+// Those a caller may ask for, in every tile shape and with a persistent grid.
+// FP64 has two steps per launch at most there; its three-step launches, in one
+// shape, are the library's own choice (three_steps below).
+constexpr bool stepk_offered(int st, int k) {
+    return stepk_available(st, k) && (k == 2 || (st != ST_F64 && st != ST5_F64));
 }
 
 template <int ST>
@@ -136,6 +136,30 @@ template <>
 struct Step3Tile<ST5_F32H> {  // 84 B per slot, 36 x 14 slots (41 KiB: 3 per CU)
     static constexpr int TW = 32, TH = 10, NT = 512;
 };
+
+// FP64: two workgroups per CU (77 and 65 KiB of LDS).  The two-step kernels
+// move 2 x 224 B (D2Q5: 2 x 160 B) a node and launch and are bound by HBM; three
+// steps per launch move two thirds of that a step, for tiles whose first update
+// covers 1.7 times their nodes.  us a step, two steps -> three: D2Q9 1024^2
+// 51.8 -> 45.7, 4096^2 767 -> 644; D2Q5 51.5 -> 31.7 and 758 -> 436.  Other shapes
+// lose: D2Q9 32x6 67.4 (1024^2), 16x16 46.9, 24x11 48.8, one workgroup per CU
+// (32x10 55.7, 32x16 55.3, 48x12 53.5); D2Q5 32x8 35.0, 24x14 33.1, 28x12 32.9, 16x16
+// (three per CU) 37.7, 32x12 40.6.
+template <>
+struct Step3Tile<ST_F64> {  // 224 B per slot, 34 x 10 slots
+    static constexpr int TW = 32, TH = 8, NT = round64((TW + 4) * (TH + 4));
+};
+template <>
+struct Step3Tile<ST5_F64> {  // 160 B per slot, 34 x 12 slots
+    static constexpr int TW = 32, TH = 10, NT = round64((TW + 4) * (TH + 4));
+};
+// Whether a handle of that many three-step FP64 tiles runs them.  D2Q5: always.
+// D2Q9: from three quarters of the workgroups the chip holds (two per CU); with
+// fewer, the three-step kernel's tiles take their time with CUs to spare and
+// the smaller two-step tiles are faster (us a step, two -> three steps: 270^2, 306
+// tiles, 6.56 -> 7.81; 300^2, 380 tiles, 7.64 -> 7.91; 350^2, 484 tiles, 9.82 -> 8.63;
+// 450^2 14.3 -> 13.8; 640^2 24.2 -> 21.2.  D2Q5 270^2, 243 tiles, 8.05 -> 5.69).
+constexpr bool three_steps(int st, int64_t tiles) { return st == ST5_F64 || (st == ST_F64 && tiles >= 384); }
 
 template <int ST, int K>
 struct StepKTile;

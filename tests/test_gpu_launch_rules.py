@@ -1,6 +1,6 @@
 """Launches whose size takes the library to another path than the small
 geometries of the other tests: tiles ordered in several strips, workgroups
-that fetch for a later tile.  Every path gives the bits of single steps.
+that fetch for a later tile, deep launches, three FP64 steps per launch.  Every path gives the bits of single steps.
 """
 import numpy as np
 import pytest
@@ -95,6 +95,55 @@ def test_autotune_keeps_or_leaves_the_deep_launches(lbm, tmp_path):
         s.step(7)
         lbm.lbm_autotune(s.h, 3, path)
         s.step(193)
+        _same(ref, [(s.state(0), s.diagnostics(0))])
+        s.close()
+    assert len(open(path).read().splitlines()) == 1
+
+
+FP64 = {
+    "380 tiles, D2Q9 two steps": lambda q: [_cavity(300, 300, q)],
+    "384 tiles": lambda q: [_cavity(384, 256, q)],
+    "ragged": lambda q: [_cavity(701, 613, q)],
+    "rounds of tiles": lambda q: [_cavity(1601, 1030, q)],
+    "batch": lambda q: [_cavity(333, 270, q), _cavity(64, 48, q), _cavity(5, 400, q)],
+    "bands": lambda q: [dict(_cavity(370, 350, q), band_rows=34)],
+    "periodic": lambda q: [W.make_params(nx=6, ny=17, bc_x=1, gravity_axis=0, porosity=0.9, Ra=100.0, Pr=5.0,
+                                         Da=0.05, Ste=1.0, k_ratio=1.0, cap_ratio=1.0, Nu_i=0.0, k_f=0.02,
+                                         T_hot=1.0, T_cold=0.0, T_init=1.0, T_solidus=-2.0, T_liquidus=-1.0,
+                                         thermal_lattice=q)],
+}
+
+
+@pytest.mark.parametrize("qt", [9, 5])
+@pytest.mark.parametrize("case", list(FP64))
+def test_own_fp64_launches_are_bitwise_single_steps(lbm, case, qt):
+    # beyond the deep sizes: every remainder of three steps, a replayed graph
+    ps = FP64[case](qt)
+    chunks = [1, 3, 4, 5, 100, 1]
+    ref = _run(lbm, ps, "f64", sum(chunks), 1)
+    s = lbm.Solver(ps if len(ps) > 1 else ps[0], "f64")
+    assert lbm.lbm_get_launch(s.h)["steps_per_launch"] == 2
+    for c, q in enumerate(ps):
+        s.set_initial(c, *W.initial_temperatures(q, 30 + c, amplitude=1e-2))
+    for n in chunks:
+        s.step(n)
+    got = [(s.state(c), s.diagnostics(c)) for c in range(len(ps))]
+    with pytest.raises(lbm.LbmError):
+        lbm.lbm_set_launch(s.h, 512, 1, 1, 0, steps_per_launch=3, tile_shape=0)
+    s.close()
+    _same(ref, got)
+
+
+def test_autotune_of_an_fp64_handle_keeps_the_bits(lbm, tmp_path):
+    p = _cavity(400, 333, 5)
+    ref = _run(lbm, [p], "f64", 120, 1)
+    path = str(tmp_path / "tune.txt")
+    for _ in range(2):
+        s = lbm.Solver(p, "f64")
+        s.set_initial(0, *W.initial_temperatures(p, 30, amplitude=1e-2))
+        s.step(8)
+        assert lbm.lbm_autotune(s.h, 3, path)["steps_per_launch"] in (1, 2)
+        s.step(112)
         _same(ref, [(s.state(0), s.diagnostics(0))])
         s.close()
     assert len(open(path).read().splitlines()) == 1

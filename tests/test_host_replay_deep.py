@@ -1,6 +1,7 @@
 """CPU replay of the deep launches (tests/host_replay/deep.cpp): every tile
 shape, storage form and number of steps, under AddressSanitizer with NaN-filled
-LDS and the headers' bounds checks on, equals single steps bit for bit.
+LDS and the headers' bounds checks on, equals single steps bit for bit; so do
+the three-step FP64 launches, which only the library itself chooses.
 """
 import hashlib
 import os
@@ -39,3 +40,14 @@ def test_deep_launches_replay_single_steps(deep, prec, qt):
             job = R._job(dict(p, thermal_lattice=qt), precision=prec, shape=shape, launches=1, seed=5)
             code, out = R._run(deep, job)
             assert code == 0 and "identical" in out, f"{name}, tile shape {shape}: {out}"
+
+
+@pytest.mark.parametrize("qt", [9, 5])
+def test_three_step_fp64_launches_replay_single_steps(qt):
+    if not os.path.exists(R.CXX):
+        pytest.skip("no host clang++")
+    exe = R._binary()
+    for name, p in R._geometries().items():
+        job = R._job(dict(p, thermal_lattice=qt), precision="f64", K=3, shape=0, launches=2, mode="kstep", seed=7)
+        code, out = R._run(exe, job)
+        assert code == 0 and "identical" in out, f"{name}: {out}"
