@@ -575,35 +575,51 @@ constexpr int MB = 256;  // threads per block of the diagnostics kernels
 // Workgroups covering rows nodes of a row range, one node per thread.
 static int row_blocks(int nx, int rows) { return (int)(((int64_t)nx * rows + MB - 1) / MB); }
 
-// Block reduction of N doubles per thread (maxima for P_DT and P_U, sums
-// otherwise), in a fixed order, so the diagnostics are deterministic: a
-// butterfly across each 64-lane wavefront (after it every lane holds the
-// same value, the operations being commutative), then the MB / 64 wave
-// results in wave order.  The result is valid in thread 0.
-template <int N>
-__device__ __forceinline__ void block_reduce(double v[N], double (*sh)[MB / 64]) {
+// Sums (or maxima) across a wavefront in a fixed order, so the diagnostics are
+// deterministic: a butterfly over lane distances 32, 16, ..., 1.
+template <bool MAX>
+__device__ __forceinline__ double wave_fold(double a, int off) {
+    const double o = __shfl_xor(a, off, 64);
+    return MAX ? fmax(a, o) : a + o;
+}
+template <bool MAX>
+__device__ __forceinline__ double wave_reduce(double a) {
 #pragma unroll
-    for (int off = 32; off > 0; off >>= 1) {
+    for (int off = 32; off > 0; off >>= 1) a = wave_fold<MAX>(a, off);
+    return a;
+}
+// The same sums of 16 values at once; returns that of value lane / 4.  At each
+// of the first four distances a lane hands half of its values to its partner
+// and folds the other half: 17 exchanges of doubles instead of 96, and, the
+// additions being commutative, the bits of 16 butterflies.
+__device__ __forceinline__ double wave_reduce16(double v[16]) {
+    const int lane = (int)threadIdx.x % 64;
 #pragma unroll
-        for (int k = 0; k < N; ++k) {
-            const double o = __shfl_xor(v[k], off, 64);
-            v[k] = (k == P_DT || k == P_U) ? fmax(v[k], o) : v[k] + o;
+    for (int n = 8, off = 32; n > 0; n >>= 1, off >>= 1) {
+        const bool up = (lane & off) != 0;
+#pragma unroll
+        for (int k = 0; k < n; ++k) {
+            const double keep = up ? v[k + n] : v[k], give = up ? v[k] : v[k + n];
+            v[k] = keep + __shfl_xor(give, off, 64);
         }
     }
-    const int w = (int)threadIdx.x / 64;
-    if (threadIdx.x % 64 == 0) {
+    return wave_fold<false>(wave_fold<false>(v[0], 2), 1);
+}
+// The partials of a wavefront (maxima for P_DT and P_U, sums otherwise) into
+// column w of sh.
+__device__ __forceinline__ void reduce_partials(double v[NPART], double (*sh)[MB / 64], int w) {
+    static_assert(NPART == 16, "one value per four lanes");
+    const int lane = (int)threadIdx.x % 64;
+    const double dT = wave_reduce<true>(v[P_DT]), u = wave_reduce<true>(v[P_U]);
+    const double a = wave_reduce16(v);
+    if (lane % 4 == 0) sh[lane / 4][w] = lane / 4 == P_DT ? dT : (lane / 4 == P_U ? u : a);
+}
+// The MB / 64 wavefront results of value k in wave order.
+__device__ __forceinline__ double wave_results(const double (*sh)[MB / 64], int k) {
+    double a = sh[k][0];
 #pragma unroll
-        for (int k = 0; k < N; ++k) sh[k][w] = v[k];
-    }
-    __syncthreads();
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < N; ++k) {
-            double a = sh[k][0];
-            for (int q = 1; q < MB / 64; ++q) a = (k == P_DT || k == P_U) ? fmax(a, sh[k][q]) : a + sh[k][q];
-            v[k] = a;
-        }
-    }
+    for (int q = 1; q < MB / 64; ++q) a = (k == P_DT || k == P_U) ? fmax(a, sh[k][q]) : a + sh[k][q];
+    return a;
 }
 
 template <class Lay, typename R, typename RH>
@@ -618,7 +634,8 @@ __global__ __launch_bounds__(MB) void macro_kernel(const void *__restrict__ src,
     double out[6], v[NPART];
 #pragma unroll
     for (int k = 0; k < NPART; ++k) v[k] = 0.0;
-    macro_node<Lay, R, RH>(c, src, raw != 0, (int)(kk % nx), y0 + (int)(kk / nx), out, v);
+    const uint32_t k = (uint32_t)kk, w = (uint32_t)nx;  // a cavity has fewer than 2^31 nodes
+    macro_node<Lay, R, RH>(c, src, raw != 0, (int)(k % w), y0 + (int)(k / w), out, v);
 #pragma unroll
     for (int q = 0; q < 6; ++q) fields[q * nn + kk] = out[q];
 }
@@ -640,91 +657,116 @@ hipError_t launch_macro(const MacroLaunch &L, int nx, int ny, hipStream_t s) {
 
 // Final pass: fixed-order sums of the block partials, Nusselt numbers from
 // one-sided second-order differences, the melt front on the middle row and
-// the wall tallies.
-__global__ __launch_bounds__(MB) void diag_kernel(DiagLaunch L) {
-    const int t = threadIdx.x;
+// the wall tallies.  One workgroup, and a chain of load latencies: four groups
+// of MB threads take the partials, the wall columns' temperatures, the vertical
+// and the horizontal walls' tallies with the front, each with several
+// iterations' loads in flight.  Value k is summed by the same MB threads in the
+// same order as if one group took all.  256^2: 19.7 us -> 7.3, a diagnostics call at
+// 1024^2 131 -> 92 and at 4096^2 680 -> 454 (one group of MB threads, the front sought
+// by one of them, 27 butterflies of 64-bit values).
+constexpr int DIAG_GROUPS = 4;
+__global__ __launch_bounds__(DIAG_GROUPS *MB) void diag_kernel(DiagLaunch L) {
+    const int t = (int)threadIdx.x % MB, w = t / 64;
+    const int group = __builtin_amdgcn_readfirstlane((int)threadIdx.x / MB);
     const int nx = L.nx, ny = L.ny;
     __shared__ double sh[NPART + 3 + 8][MB / 64];
-    double v[NPART + 3 + 8];
+    __shared__ double tot[NPART + 3 + 8];
+    __shared__ int front;
+    if (threadIdx.x == 0) front = nx;
+    __syncthreads();
+    int mine = nx;  // the first f_l = 0.5 crossing of the middle row among this thread's nodes
+    if (group == 0) {
+        double v[NPART];
 #pragma unroll
-    for (int k = 0; k < NPART + 11; ++k) v[k] = 0.0;
-    for (int b = t; b < L.nblocks; b += MB) {
+        for (int k = 0; k < NPART; ++k) v[k] = 0.0;
+#pragma unroll 2
+        for (int b = t; b < L.nblocks; b += MB) {
 #pragma unroll
-        for (int k = 0; k < NPART; ++k) {
-            const double a = L.partials[(int64_t)b * NPART + k];
-            v[k] = (k == P_DT || k == P_U) ? fmax(v[k], a) : v[k] + a;
+            for (int k = 0; k < NPART; ++k) {
+                const double a = L.partials[(int64_t)b * NPART + k];
+                v[k] = (k == P_DT || k == P_U) ? fmax(v[k], a) : v[k] + a;
+            }
         }
-    }
-    if (!L.periodic) {
-        for (int y = 1 + t; y <= ny - 2; y += MB) {
-            const double *Tf = L.tf + (int64_t)y * 6;
-            const double *Tm = L.tm + (int64_t)y * 6;
-            const double dTf = (-3.0 * Tf[0] + 4.0 * Tf[1] - Tf[2]) * 0.5;
-            const double dTm = (-3.0 * Tm[0] + 4.0 * Tm[1] - Tm[2]) * 0.5;
-            v[NPART + 0] += dTf;  // PCM-only gradient
-            const double cTf = (3.0 * Tf[5] - 4.0 * Tf[4] + Tf[3]) * 0.5;
-            const double cTm = (3.0 * Tm[5] - 4.0 * Tm[4] + Tm[3]) * 0.5;
-            v[NPART + 1] += L.kf * dTf + L.km * dTm;
-            v[NPART + 2] += L.kf * cTf + L.km * cTm;
-        }
-    }
-    // wall tallies: slots [left ny][right ny][bottom nx][top nx]
-    const double *acc = L.acc + 2 * L.acc0;
-    for (int y = t; y < ny; y += MB) {
-        v[NPART + 3] += acc[2 * y];
-        v[NPART + 4] += acc[2 * (ny + y)];
-        v[NPART + 7] += acc[2 * y + 1];
-        v[NPART + 8] += acc[2 * (ny + y) + 1];
-    }
-    for (int x = t; x < nx; x += MB) {
-        v[NPART + 5] += acc[2 * (2 * ny + x)];
-        v[NPART + 6] += acc[2 * (2 * ny + nx + x)];
-        v[NPART + 9] += acc[2 * (2 * ny + x) + 1];
-        v[NPART + 10] += acc[2 * (2 * ny + nx + x) + 1];
-    }
-    block_reduce<NPART + 11>(v, sh);
-    if (t == 0) {
-        double *o = L.out;
-        const double nint = L.periodic ? (double)nx * (ny - 2) : (double)(nx - 2) * (ny - 2);
-        o[D_FL] = v[P_FL] / nint;
-        o[D_E] = v[P_E];
-        o[D_M] = v[P_M];
-        o[D_DT] = v[P_DT];
-        o[D_U] = v[P_U];
-        o[D_NF] = v[P_NF];
-        const double nrow = (double)(ny - 2);
-        o[D_NUH] = L.periodic ? 0.0 : -(L.L / (L.ke * L.dT)) * (v[NPART + 1] / nrow);
-        o[D_NUHP] = L.periodic ? 0.0 : -(L.L / L.dT) * (v[NPART + 0] / nrow);
-        o[D_NUC] = L.periodic ? 0.0 : -(L.L / (L.ke * L.dT)) * (v[NPART + 2] / nrow);
-        // melt front: first f_l = 0.5 crossing on row ny/2 seen from x = 0
-        double xf = 1.0;
-        if (!L.periodic) {
-            const double *fl = L.fl_mid;
-            if (fl[0] < 0.5) {
-                xf = 0.0;
-            } else {
-                for (int i = 0; i + 1 < nx; ++i) {
-                    const double a = fl[i], b = fl[i + 1];
-                    if (a >= 0.5 && b < 0.5) {
-                        xf = (i + (a - 0.5) / (a - b)) / L.L;
-                        break;
-                    }
+        reduce_partials(v, sh, w);
+    } else {
+        double v[4] = {0.0, 0.0, 0.0, 0.0};
+        const double *acc = L.acc + 2 * L.acc0;  // slots [left ny][right ny][bottom nx][top nx]
+        int k0[4];
+        if (group == 1) {
+            k0[0] = NPART, k0[1] = NPART + 1, k0[2] = NPART + 2, k0[3] = -1;
+            if (!L.periodic) {
+#pragma unroll 4
+                for (int y = 1 + t; y <= ny - 2; y += MB) {
+                    const double *Tf = L.tf + (int64_t)y * 6;
+                    const double *Tm = L.tm + (int64_t)y * 6;
+                    const double dTf = (-3.0 * Tf[0] + 4.0 * Tf[1] - Tf[2]) * 0.5;
+                    const double dTm = (-3.0 * Tm[0] + 4.0 * Tm[1] - Tm[2]) * 0.5;
+                    v[0] += dTf;  // PCM-only gradient
+                    const double cTf = (3.0 * Tf[5] - 4.0 * Tf[4] + Tf[3]) * 0.5;
+                    const double cTm = (3.0 * Tm[5] - 4.0 * Tm[4] + Tm[3]) * 0.5;
+                    v[1] += L.kf * dTf + L.km * dTm;
+                    v[2] += L.kf * cTf + L.km * cTm;
                 }
             }
         } else {
-            xf = 0.0;
+            const int n = group == 2 ? ny : nx;
+            const double *lo = acc + (group == 2 ? 0 : 4 * (int64_t)ny), *hi = lo + 2 * (int64_t)n;
+            const int f = NPART + (group == 2 ? 3 : 5);
+            k0[0] = f, k0[1] = f + 1, k0[2] = f + 4, k0[3] = f + 5;
+#pragma unroll 4
+            for (int i = t; i < n; i += MB) {
+                v[0] += lo[2 * i];
+                v[1] += hi[2 * i];
+                v[2] += lo[2 * i + 1];
+                v[3] += hi[2 * i + 1];
+            }
+            if (group == 3 && !L.periodic) {
+#pragma unroll 4
+                for (int i = t; i + 1 < nx; i += MB)
+                    if (L.fl_mid[i] >= 0.5 && L.fl_mid[i + 1] < 0.5) mine = min(mine, i);
+                if (mine < nx) atomicMin(&front, mine);
+            }
         }
+#pragma unroll
+        for (int k = 0; k < 4; ++k) {
+            const double a = wave_reduce<false>(v[k]);
+            if (t % 64 == 0 && k0[k] >= 0) sh[k0[k]][w] = a;
+        }
+    }
+    __syncthreads();
+    if (threadIdx.x < NPART + 11) tot[threadIdx.x] = wave_results(sh, (int)threadIdx.x);
+    __syncthreads();
+    double *o = L.out;
+    // melt front: first f_l = 0.5 crossing on row ny/2 seen from x = 0
+    if (group == 3 && (mine < nx ? mine == front : t == 0 && front == nx)) {
+        const double *fl = L.fl_mid;
+        double xf = 1.0;
+        if (L.periodic || fl[0] < 0.5) xf = 0.0;
+        else if (front < nx) xf = (front + (fl[front] - 0.5) / (fl[front] - fl[front + 1])) / L.L;
         o[D_FRONT] = xf;
-        for (int w = 0; w < 4; ++w) {
-            o[D_FLUXE + w] = v[NPART + 3 + w] + v[P_INE0 + w];
-            o[D_FLUXM + w] = v[NPART + 7 + w] + v[P_INM0 + w];
+    }
+    if (threadIdx.x == 0) {
+        const double nint = L.periodic ? (double)nx * (ny - 2) : (double)(nx - 2) * (ny - 2);
+        o[D_FL] = tot[P_FL] / nint;
+        o[D_E] = tot[P_E];
+        o[D_M] = tot[P_M];
+        o[D_DT] = tot[P_DT];
+        o[D_U] = tot[P_U];
+        o[D_NF] = tot[P_NF];
+        const double nrow = (double)(ny - 2);
+        o[D_NUH] = L.periodic ? 0.0 : -(L.L / (L.ke * L.dT)) * (tot[NPART + 1] / nrow);
+        o[D_NUHP] = L.periodic ? 0.0 : -(L.L / L.dT) * (tot[NPART + 0] / nrow);
+        o[D_NUC] = L.periodic ? 0.0 : -(L.L / (L.ke * L.dT)) * (tot[NPART + 2] / nrow);
+        for (int w2 = 0; w2 < 4; ++w2) {
+            o[D_FLUXE + w2] = tot[NPART + 3 + w2] + tot[P_INE0 + w2];
+            o[D_FLUXM + w2] = tot[NPART + 7 + w2] + tot[P_INM0 + w2];
         }
     }
 }
 
 hipError_t launch_diag(const DiagLaunch &L, int nx, int ny, hipStream_t s) {
     if (L.nx != nx || L.ny != ny) return hipErrorInvalidValue;
-    hipLaunchKernelGGL(diag_kernel, dim3(1), dim3(MB), 0, s, L);
+    hipLaunchKernelGGL(diag_kernel, dim3(1), dim3(DIAG_GROUPS * MB), 0, s, L);
     return hipGetLastError();
 }
 
@@ -749,12 +791,12 @@ __global__ __launch_bounds__(MB) void diag_node_kernel(const void *__restrict__ 
                                                        double *__restrict__ tm, double *__restrict__ fl_mid) {
     const CavityConst<R> &c = cav[ci];
     const int nx = c.nx, ny = c.ny;
-    const int64_t nn = (int64_t)nx * ny;
+    const uint32_t nn = (uint32_t)nx * (uint32_t)ny;  // below 2^31, the stride below 2^20
     double tot[NPART];
 #pragma unroll
     for (int k = 0; k < NPART; ++k) tot[k] = 0.0;
-    for (int64_t kk = (int64_t)blockIdx.x * MB + threadIdx.x; kk < nn; kk += (int64_t)gridDim.x * MB) {
-        const int x = (int)(kk % nx), y = (int)(kk / nx);
+    for (uint32_t kk = blockIdx.x * MB + threadIdx.x; kk < nn; kk += gridDim.x * MB) {
+        const int x = (int)(kk % (uint32_t)nx), y = (int)(kk / (uint32_t)nx);
         double out[6], v[NPART];
 #pragma unroll
         for (int k = 0; k < NPART; ++k) v[k] = 0.0;
@@ -771,11 +813,9 @@ __global__ __launch_bounds__(MB) void diag_node_kernel(const void *__restrict__ 
         if (y == ny / 2) fl_mid[x] = out[4];
     }
     __shared__ double sh[NPART][MB / 64];
-    block_reduce<NPART>(tot, sh);
-    if (threadIdx.x == 0) {
-#pragma unroll
-        for (int k = 0; k < NPART; ++k) partials[(int64_t)blockIdx.x * NPART + k] = tot[k];
-    }
+    reduce_partials(tot, sh, (int)threadIdx.x / 64);
+    __syncthreads();
+    if (threadIdx.x < NPART) partials[(int64_t)blockIdx.x * NPART + threadIdx.x] = wave_results(sh, (int)threadIdx.x);
 }
 
 template <int ST>
