@@ -293,7 +293,9 @@ int64_t lbm_step_count(const lbm_handle *h);
 /* Macroscopic fields of one cavity at the current step, from the
  * post-streaming populations: velocity u of Eq. (23), T_f and f_l of
  * Eqs. (38)-(39), T_m of Eq. (48), density of Eq. (21).  Any pointer may be
- * NULL.  Synchronises the stream. */
+ * NULL.  Synchronises the stream.  All six planes of a cavity of 2^19 nodes or
+ * more come through 24 MiB of pinned host memory that the handle holds, copied
+ * out by the caller and up to seven threads that end with the call. */
 lbm_status lbm_fields(lbm_handle *h, int32_t cavity, double *ux, double *uy, double *T_pcm,
                       double *T_mf, double *f_l, double *rho);
 

@@ -5,7 +5,9 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
+#include <condition_variable>
 #include <mutex>
+#include <thread>
 #include <cstddef>
 #include <cmath>
 #include <cstdarg>
@@ -132,6 +134,14 @@ struct Plan {
 // host and device in runs of whole rows of at most this many nodes, so the
 // staging area stays a small part of the memory however large a cavity is.
 constexpr int64_t kStageNodes = (int64_t)1 << 22;
+
+// Field planes come back through pinned slots: four of whole rows of at most
+// kSlotNodes nodes (6 MiB) each for handles with a cavity of kSlotsFrom nodes or
+// more, one for handles whose cavities all fit kOneSlot.  Between the two the
+// runtime's copies are as fast and a handle's first read costs less (256^2: 0.19 ms
+// a read either way, the slots themselves about 2 ms).
+constexpr int64_t kSlotNodes = (int64_t)1 << 17, kSlotsFrom = (int64_t)1 << 19, kOneSlot = (int64_t)1 << 14;
+constexpr int kSlots = 4;
 
 // The deep tile shape of a handle: the first that leaves at most a tile per
 // CU (kDeepTiles).  Periodic problems, whose rings may wrap more than once,
@@ -297,6 +307,15 @@ struct lbm_handle {
     lbm_launch_config own_lc{};
     hipGraphExec_t graphd[2] = {nullptr, nullptr};
     hipGraph_t gsrcd[2] = {nullptr, nullptr};
+
+    // pinned host memory that the diagnostics' results and the field planes
+    // come back through (nullptr: none could be had, copies go the long way)
+    double *hdiag = nullptr;  // NDIAG doubles, written by the last diagnostics kernel
+    double *hslot = nullptr;  // nslots runs of 6 * slot_nodes doubles, written by the macro kernel
+    void *hslots = nullptr;   // their memory, where it is not part of hdiag's
+    int nslots = 0;
+    int64_t slot_nodes = 0;
+    hipEvent_t hready[kSlots] = {};
 
     void *pop(int b) { return ws + pl.off_pop[b]; }
     void *sr(int b) { return ws + pl.off_sr[b]; }
@@ -570,7 +589,7 @@ DiagLaunch diag_args(lbm_handle *h, int c, const double *partials, int nblocks, 
 // The diagnostics kernels of cavity c, their scratch at the given device
 // addresses: per-workgroup partial sums, the temperatures of the columns
 // next to the vertical walls, the middle row's liquid fraction, and the
-// NDIAG results in out.
+// NDIAG results in the handle's pinned memory, or in out without it.
 lbm_status launch_diagnostics(lbm_handle *h, int c, char *part, char *tf, char *tm, char *fl, char *out) {
     const lbm_params &p = h->params[c];
     DiagNodeLaunch M;
@@ -585,11 +604,21 @@ lbm_status launch_diagnostics(lbm_handle *h, int c, char *part, char *tf, char *
     M.tm = (double *)tm;
     M.fl_mid = (double *)fl;
     HIP_TRY(launch_diag_nodes(M, p.nx, p.ny, h->stream));
-    DiagLaunch D = diag_args(h, c, M.partials, M.nblocks, (double *)out);
+    DiagLaunch D = diag_args(h, c, M.partials, M.nblocks, h->hdiag ? h->hdiag : (double *)out);
     D.tf = M.tf;
     D.tm = M.tm;
     D.fl_mid = M.fl_mid;
     HIP_TRY(launch_diag(D, p.nx, p.ny, h->stream));
+    return LBM_OK;
+}
+
+// The results of launch_diagnostics: from pinned memory where the handle has
+// it, else from dev (a copy of 144 bytes to ordinary memory is a kernel, a wait
+// and a copy: a call at 64^2 takes 42 us with it and 31 without).
+lbm_status take_diag(lbm_handle *h, const double *dev, double out[NDIAG]) {
+    if (!h->hdiag) HIP_TRY(hipMemcpyAsync(out, dev, NDIAG * sizeof(double), hipMemcpyDeviceToHost, h->stream));
+    HIP_TRY(hipStreamSynchronize(h->stream));
+    if (h->hdiag) std::memcpy(out, h->hdiag, NDIAG * sizeof(double));
     return LBM_OK;
 }
 
@@ -599,9 +628,7 @@ lbm_status read_diag(lbm_handle *h, int c, double out[NDIAG]) {
     lbm_status s = launch_diagnostics(h, c, w + h->pl.off_part, w + h->pl.off_tf, w + h->pl.off_tm,
                                       w + h->pl.off_fl, w + h->pl.off_out);
     if (s != LBM_OK) return s;
-    HIP_TRY(hipMemcpyAsync(out, h->dout(), NDIAG * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
-    return LBM_OK;
+    return take_diag(h, h->dout(), out);
 }
 
 lbm_status init_cavity(lbm_handle *h, int c, const double *T_pcm, const double *T_mf) {
@@ -639,6 +666,47 @@ lbm_status init_cavity(lbm_handle *h, int c, const double *T_pcm, const double *
     return LBM_OK;
 }
 
+// Pinned memory, or nullptr.  Relaxed: a capture that another thread has under
+// way is not disturbed.
+void *pinned(size_t bytes) {
+    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
+    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    void *m = nullptr;
+    if (hipHostMalloc(&m, bytes, hipHostMallocDefault) != hipSuccess) m = nullptr;
+    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
+    if (!m) (void)hipGetLastError();
+    return m;
+}
+
+// n events and n slots at m for the read-backs of field planes, if all can be had.
+void give_slots(lbm_handle *h, int n, int64_t nodes, void *m) {
+    for (int i = 0; i < n; ++i)
+        if (hipEventCreateWithFlags(&h->hready[i], hipEventDisableTiming) != hipSuccess) {
+            (void)hipGetLastError();
+            h->hready[i] = nullptr;
+            return;
+        }
+    h->hslot = (double *)m;
+    h->nslots = n;
+    h->slot_nodes = nodes;
+}
+
+// Pinned memory for read-backs: the diagnostics' results and, for small
+// cavities, one slot.  A handle works without it.
+void pin_results(lbm_handle *h) {
+    const bool one = h->pl.max_nodes <= kOneSlot;
+    const size_t head = align256(NDIAG * sizeof(double));
+    h->hdiag = (double *)pinned(head + (one ? (size_t)6 * h->pl.max_nodes * sizeof(double) : 0));
+    if (h->hdiag && one) give_slots(h, 1, h->pl.max_nodes, (char *)h->hdiag + head);
+}
+
+// The slots of large cavities, at the first read-back that can use them.
+void pin_slots(lbm_handle *h) {
+    if (h->hslot || h->hslots || h->pl.max_nodes < kSlotsFrom || h->pl.max_nx > kSlotNodes) return;
+    h->hslots = pinned((size_t)kSlots * 6 * kSlotNodes * sizeof(double));
+    if (h->hslots) give_slots(h, kSlots, kSlotNodes, h->hslots);
+}
+
 lbm_status setup(lbm_handle *h) {
     HIP_TRY(hipGetDevice(&h->device));
     {
@@ -646,6 +714,7 @@ lbm_status setup(lbm_handle *h) {
         lbm_status s0 = noalloc_scratch(h->device, &scr);
         if (s0 != LBM_OK) return s0;
     }
+    pin_results(h);
     int ncu = 0;
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
     h->n_cu = ncu > 0 ? ncu : 256;
@@ -775,6 +844,10 @@ extern "C" lbm_status lbm_destroy(lbm_handle *h) {
     if (h->cap) (void)hipStreamDestroy(h->cap);
     if (h->owns_stream && h->stream) (void)hipStreamDestroy(h->stream);
     if (h->owns_ws && h->ws) (void)hipFree(h->ws);
+    for (hipEvent_t e : h->hready)
+        if (e) (void)hipEventDestroy(e);
+    if (h->hslots) (void)hipHostFree(h->hslots);
+    if (h->hdiag) (void)hipHostFree(h->hdiag);
     delete h;
     return LBM_OK;
 }
@@ -904,6 +977,150 @@ extern "C" lbm_status lbm_synchronize(lbm_handle *h) {
 
 extern "C" int64_t lbm_step_count(const lbm_handle *h) { return h ? h->step : -1; }
 
+namespace {
+MacroLaunch macro_args(lbm_handle *h, int c, int y0, int rows, double *fields) {
+    MacroLaunch M;
+    M.storage = h->st;
+    M.raw = h->step == 0 ? 1 : 0;
+    M.cav_index = c;
+    M.src = h->pop(h->cur);
+    M.cav = h->cav();
+    M.y0 = y0;
+    M.rows = rows;
+    M.fields = fields;
+    return M;
+}
+
+// Whether memory is the host's to write.
+bool on_host(const void *p) {
+    hipPointerAttribute_t a;
+    if (hipPointerGetAttributes(&a, p) == hipSuccess) return a.type != hipMemoryTypeDevice;
+    (void)hipGetLastError();  // not known to HIP: ordinary memory
+    return true;
+}
+
+// Copies pieces of field planes out of the slots as they become ready: the
+// caller and helper threads take parts of the ready pieces in order, so that
+// any number of helpers, none included, does the work.  Helpers are started for
+// planes of some size only (one for every 4 MiB; a thread costs about 50 us) and
+// end with the call.
+class PlaneCopy {
+public:
+    static constexpr int kParts = 8;
+    PlaneCopy(double *const outs[6], const double *slots, int64_t slot_doubles, int nslots, int64_t piece, int64_t nodes)
+        : outs_(outs), slots_(slots), slot_doubles_(slot_doubles), nslots_(nslots), piece_(piece), nodes_(nodes),
+          done_((size_t)((nodes + piece - 1) / piece), 0) {
+        const int64_t mib = nodes * 6 * (int64_t)sizeof(double) >> 20;
+        const int cpus = (int)std::thread::hardware_concurrency();
+        const int helpers = (int)std::min<int64_t>({mib / 4, kParts - 1, cpus > 1 ? cpus - 1 : 0});
+        try {
+            for (int i = 0; i < helpers; ++i) threads_.emplace_back([this] { serve(); });
+        } catch (...) {  // fewer helpers, or none
+        }
+    }
+    ~PlaneCopy() {
+        {
+            std::lock_guard<std::mutex> l(m_);
+            quit_ = true;
+        }
+        ready_cv_.notify_all();
+        for (std::thread &t : threads_) t.join();
+    }
+    // The slots of pieces before n are complete.
+    void publish(int64_t n) {
+        {
+            std::lock_guard<std::mutex> l(m_);
+            ready_ = n * kParts;
+        }
+        ready_cv_.notify_all();
+    }
+    // Returns when piece p is copied out; takes part in the copying.
+    void finish(int64_t p) {
+        std::unique_lock<std::mutex> l(m_);
+        while (done_[p] < kParts && take(l)) {
+        }
+        done_cv_.wait(l, [&] { return done_[p] == kParts; });
+    }
+
+private:
+    void serve() {
+        std::unique_lock<std::mutex> l(m_);
+        for (;;) {
+            ready_cv_.wait(l, [this] { return quit_ || next_ < ready_; });
+            if (quit_) return;
+            while (take(l)) {
+            }
+        }
+    }
+    // Copies the next part, if one is ready.
+    bool take(std::unique_lock<std::mutex> &l) {
+        if (next_ >= ready_) return false;
+        const int64_t p = next_ / kParts, part = next_ % kParts;
+        ++next_;
+        l.unlock();
+        const int64_t o = p * piece_, n = std::min(piece_, nodes_ - o);
+        const int64_t a = n * part / kParts, b = n * (part + 1) / kParts;
+        const double *slot = slots_ + (p % nslots_) * slot_doubles_;
+        for (int q = 0; q < 6; ++q)
+            std::memcpy(outs_[q] + o + a, slot + q * n + a, (size_t)(b - a) * sizeof(double));
+        l.lock();
+        if (++done_[p] == kParts) done_cv_.notify_one();
+        return true;
+    }
+
+    double *const *outs_;
+    const double *slots_;
+    int64_t slot_doubles_, nslots_, piece_, nodes_;
+    std::mutex m_;
+    std::condition_variable ready_cv_, done_cv_;
+    int64_t ready_ = 0, next_ = 0;  // parts that may be, that have been taken
+    std::vector<int> done_;         // parts of each piece that are copied
+    bool quit_ = false;
+    std::vector<std::thread> threads_;
+};
+
+// Field planes of rows [y0, y0 + rows) through the pinned slots: the macro
+// kernel writes a piece of whole rows straight into one while earlier pieces
+// are copied out.  The runtime's copies to ordinary memory ran at 10 GB/s (fresh
+// pages are touched by one thread): 8192^2 (3.2 GB) 310 -> 81 ms, 4096^2 77 -> 21,
+// 1024^2 6.4 -> 1.9, 64^2 0.08 -> 0.04.
+lbm_status fields_through_slots(lbm_handle *h, int c, int y0, int rows, double *const outs[6]) {
+    const lbm_params &p = h->params[c];
+    const int per = (int)std::min<int64_t>(rows, h->slot_nodes / p.nx), pieces = (rows + per - 1) / per;
+    const int64_t slot_doubles = 6 * h->slot_nodes;
+    auto launch = [&](int i) -> lbm_status {
+        const int r0 = i * per, nr = std::min(per, rows - r0), k = i % h->nslots;
+        HIP_TRY(launch_macro(macro_args(h, c, y0 + r0, nr, h->hslot + k * slot_doubles), p.nx, p.ny, h->stream));
+        HIP_TRY(hipEventRecord(h->hready[k], h->stream));
+        return LBM_OK;
+    };
+    lbm_status s = LBM_OK;
+    int launched = 0;
+    while (launched < std::min(pieces, h->nslots) && s == LBM_OK) s = launch(launched++);
+    if (s == LBM_OK) {
+        PlaneCopy copy(outs, h->hslot, slot_doubles, h->nslots, (int64_t)per * p.nx, (int64_t)rows * p.nx);
+        for (int i = 0; i < pieces && s == LBM_OK; ++i) {
+            const hipError_t e = hipEventSynchronize(h->hready[i % h->nslots]);
+            if (e != hipSuccess) {
+                s = fail(LBM_EDEVICE, "read-back of field planes: %s", hipGetErrorString(e));
+                break;
+            }
+            copy.publish(i + 1);
+            if (i == 0) continue;
+            copy.finish(i - 1);
+            if (launched < pieces) s = launch(launched++);  // into the slot of piece i - 1
+        }
+        if (s == LBM_OK) copy.finish(pieces - 1);
+    }
+    if (s != LBM_OK) {  // nothing writes the slots any more when the call returns
+        const std::string msg = g_err;
+        (void)hipStreamSynchronize(h->stream);
+        return fail(s, "%s", msg.c_str());
+    }
+    return LBM_OK;
+}
+}  // namespace
+
 extern "C" lbm_status lbm_fields_rows(lbm_handle *h, int32_t c, int32_t y0, int32_t rows, double *ux,
                                       double *uy, double *T_pcm, double *T_mf, double *f_l, double *rho) {
     if (!h) return fail(LBM_EINVAL, "handle is NULL");
@@ -913,18 +1130,14 @@ extern "C" lbm_status lbm_fields_rows(lbm_handle *h, int32_t c, int32_t y0, int3
         return fail(LBM_EINVAL, "rows [%d, %d + %d) outside the cavity's %d rows", y0, y0, rows, p.ny);
     const int chunk = h->stage_rows(c);
     double *outs[6] = {ux, uy, T_pcm, T_mf, f_l, rho};
+    // all planes to host memory: through the slots
+    bool slots = true;
+    for (int k = 0; k < 6 && slots; ++k) slots = outs[k] && on_host(outs[k]);
+    if (slots) pin_slots(h);
+    if (slots && h->hslot) return fields_through_slots(h, c, y0, rows, outs);
     for (int r0 = 0; r0 < rows; r0 += chunk) {
         const int nr = std::min(chunk, rows - r0);
-        MacroLaunch M;
-        M.storage = h->st;
-        M.raw = h->step == 0 ? 1 : 0;
-        M.cav_index = c;
-        M.src = h->pop(h->cur);
-        M.cav = h->cav();
-        M.y0 = y0 + r0;
-        M.rows = nr;
-        M.fields = h->fields();
-        HIP_TRY(launch_macro(M, p.nx, p.ny, h->stream));
+        HIP_TRY(launch_macro(macro_args(h, c, y0 + r0, nr, h->fields()), p.nx, p.ny, h->stream));
         const int64_t nn = (int64_t)p.nx * nr;
         for (int k = 0; k < 6; ++k)
             if (outs[k])
@@ -998,8 +1211,8 @@ extern "C" lbm_status lbm_diagnostics_noalloc(lbm_handle *h, int32_t c, lbm_diag
     s = launch_diagnostics(h, c, base + kScrPart, base + kScrTf, base + kScrTm, base + kScrFl, base + kScrOut);
     if (s != LBM_OK) return s;
     double d[NDIAG];
-    HIP_TRY(hipMemcpyAsync(d, base + kScrOut, NDIAG * sizeof(double), hipMemcpyDeviceToHost, h->stream));
-    HIP_TRY(hipStreamSynchronize(h->stream));
+    s = take_diag(h, (const double *)(base + kScrOut), d);
+    if (s != LBM_OK) return s;
     return diag_from(h, c, d, out);
 }
 
