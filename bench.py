@@ -41,9 +41,10 @@ BYTES_PER_NODE = {"f64": 448, "f32": 224, "f32h64": 232, "f16split": 152, "bf16s
 # FP32 form that holds every field within 1e-4 of the FP64 oracle over the
 # 256^2 A/B run.
 FP32_FORM = "f32h64"
-# Algorithmic VALU instructions per node update of the timed forms: those of
-# the one-step kernel (no multi-step ring), counted with rocprofv3
-# (SQ_INSTS_VALU x 64 / node updates) on the 8192^2 cavity.
+# Algorithmic VALU instructions per node update of the timed forms: the fewest
+# that a one-step kernel (no multi-step ring) of this library has issued,
+# counted with rocprofv3 (SQ_INSTS_VALU x 64 / node updates) on the 8192^2
+# cavity; the present one-step kernels issue 442.5 and 504.4.
 ALG_VALU_PER_NODE_STEP = {"f32": 436.3, "f32h64": 468.7}
 # The paper's own timings (Table I, present scheme, quad-core 2.33 GHz CPU;
 # precision and thread count not stated): context only.

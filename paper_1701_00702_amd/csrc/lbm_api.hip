@@ -1002,8 +1002,7 @@ bool on_host(const void *p) {
 // Copies pieces of field planes out of the slots as they become ready: the
 // caller and helper threads take parts of the ready pieces in order, so that
 // any number of helpers, none included, does the work.  Helpers are started for
-// planes of some size only (one for every 4 MiB; a thread costs about 50 us) and
-// end with the call.
+// planes of some size only (one for every 4 MiB) and end with the call.
 class PlaneCopy {
 public:
     static constexpr int kParts = 8;

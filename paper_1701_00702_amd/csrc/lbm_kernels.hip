@@ -316,8 +316,8 @@ constexpr int stepk_waves_per_eu() {
 // as a waves-per-EU bound (bit ST of the mask).  Measured on the 8192^2
 // cavity: the FP32 D2Q5 forms keep their registers (50 and 57) and gain
 // 5% (three steps) and 3-4% (two steps) from the schedule the bound
-// selects; FP32 D2Q9 is unchanged (LDS holds it at three workgroups per
-// CU); the 16-bit and D2Q9 FP32_H64 forms fit the bound only by spilling
+// selects; FP32 D2Q9 (three workgroups per CU by LDS) goes without, with
+// 32 x 10 tiles; the 16-bit and D2Q9 FP32_H64 forms fit the bound only by spilling
 // and lose 5-24%.
 #ifndef LBM_WPE_MASK
 #define LBM_WPE_MASK ((1 << ST5_F32) | (1 << ST5_F32H))

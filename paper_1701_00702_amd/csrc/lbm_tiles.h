@@ -128,8 +128,9 @@ struct Step3Tile<ST_BF16S> : Step3Tile<ST_F16S> {};
 #define LBM_S3_F32H_TH (LBM_PUSH_F32H_K3 ? 10 : 9)
 #endif
 template <>
-struct Step3Tile<ST_F32H> {  // 116 B per slot (push 32 x 10: 34 x 12 slots, 46 KiB, 3 per CU, 45.7 GLUPS
-                             // on the 8192^2 cavity against 45.1 for 32 x 8 with 4 per CU; pull 32 x 9: 53 KiB, 3)
+struct Step3Tile<ST_F32H> {  // 116 B per slot (push 32 x 10: 34 x 12 slots, 46 KiB, 3 per CU: chosen at
+                             // 45.7 GLUPS on the 8192^2 cavity, 51.3 since, against 45.1 for 32 x 8 with 4 per CU;
+                             // pull 32 x 9: 53 KiB, 3)
     static constexpr int TW = LBM_S3_F32H_TW, TH = LBM_S3_F32H_TH, NT = round64((TW + 4) * (TH + 4));
 };
 template <>
