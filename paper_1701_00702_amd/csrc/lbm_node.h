@@ -1652,8 +1652,11 @@ struct StepKShape {
         return LDS_BYTES + NSLOT * sizeof(R) + BASE_BYTES + (tally ? 32 * (TW + TH) : 0);
     }
     static constexpr int NT = (NFIRST + 63) / 64 * 64;
+    // LDS is given out in units of at most 128 bytes: the two-step FP64 D2Q5 tile
+    // (54400 bytes) fits three times, with tallies in LDS only twice (4096^2: 29.9
+    // GLUPS with its tallies in memory, 22.1 with two per CU).
     static constexpr int per_cu(bool tally) {
-        const int a = (int)(160 * 1024 / ((total_lds(tally) + 511) / 512 * 512)), b = 32 / (NT / 64);
+        const int a = (int)(160 * 1024 / ((total_lds(tally) + 127) / 128 * 128)), b = 32 / (NT / 64);
         return a < b ? a : b;
     }
     static constexpr bool TILE_TALLY = per_cu(true) == per_cu(false);
