@@ -17,8 +17,9 @@ enum Storage {
 enum Wall { W_LEFT = 0, W_RIGHT = 1, W_BOTTOM = 2, W_TOP = 3 };
 
 // Longest cavity row.  A band (below) holds at least LBM_MIN_BAND_ROWS rows,
-// and the step kernels address a tile's rows by 32-bit byte offsets within
-// two consecutive bands: band_nodes * (bytes per node + 8) < 2^31.
+// and the step kernels address a tile's rows by unsigned 32-bit byte offsets
+// within two consecutive bands, each below 2^31 bytes:
+// band_nodes * (bytes per node + 8) < 2^31.
 #define LBM_MAX_NX 262144
 #define LBM_MIN_BAND_ROWS 32
 // Target size of one band of a state buffer (bytes); a build option.

@@ -36,6 +36,19 @@
 
 #define LBM_HD __host__ __device__ __forceinline__
 
+// A bounds check that host builds make and the kernels leave out.
+#if defined(__HIP_DEVICE_COMPILE__)
+#define LBM_HOST_CHECK(cond) ((void)0)
+#else
+#define LBM_HOST_CHECK(cond)                                                              \
+    do {                                                                                  \
+        if (!(cond)) {                                                                    \
+            fprintf(stderr, "lbm: check failed: %s (%s:%d)\n", #cond, __FILE__, __LINE__); \
+            abort();                                                                      \
+        }                                                                                 \
+    } while (0)
+#endif
+
 namespace lbm {
 
 // ---------------------------------------------------------------------------
@@ -228,12 +241,16 @@ LBM_HD T *at(T *plane, FarRef r) {
 // on.  An access is at uniform + lane + imm bytes from there: on the GPU a
 // buffer access, which takes the three as a scalar register, a vector
 // register and a constant, so that the planes of a node differ in the scalar
-// alone and one vector offset serves them all.  Offsets stay below 2^31 (two
-// consecutive bands).
+// alone and one vector offset serves them all.  A workgroup's rows lie in two
+// consecutive bands of less than 2^31 bytes each (the plan refuses longer
+// rows), so every sum stays below 2^32, which is what a buffer access can
+// reach: its three parts are unsigned, and the resource spans kBlocksBytes.
+// Beyond the resource loads give 0 and stores are dropped without an error.
+constexpr uint32_t kBlocksBytes = 0xffffffffu;
 #if defined(__HIP_DEVICE_COMPILE__)
 using Blocks = __amdgpu_buffer_rsrc_t;
 LBM_HD Blocks blocks_of(const void *first) {
-    return __builtin_amdgcn_make_buffer_rsrc((void *)first, 0, 0x7fffffff, 0x00020000);
+    return __builtin_amdgcn_make_buffer_rsrc((void *)first, 0, kBlocksBytes, 0x00020000);
 }
 #else
 using Blocks = char *;
@@ -250,7 +267,8 @@ LBM_HD T ld_block(Blocks b, uint32_t uniform, uint32_t lane, uint32_t imm) {
     else
         return __builtin_bit_cast(T, __builtin_amdgcn_raw_buffer_load_b16(b, lane + imm, uniform, aux));
 #else
-    return *(const T *)(b + (uint32_t)(uniform + lane + imm));
+    LBM_HOST_CHECK((uint64_t)uniform + lane + imm + sizeof(T) <= kBlocksBytes);
+    return *(const T *)(b + ((uint64_t)uniform + lane + imm));
 #endif
 }
 template <typename T>
@@ -266,7 +284,8 @@ LBM_HD void st_block(Blocks b, uint32_t uniform, uint32_t lane, T v) {
         __builtin_amdgcn_raw_buffer_store_b16(__builtin_bit_cast(unsigned short, v), b, lane, uniform, aux);
     }
 #else
-    *(T *)(b + (uint32_t)(uniform + lane)) = v;
+    LBM_HOST_CHECK((uint64_t)uniform + lane + sizeof(T) <= kBlocksBytes);
+    *(T *)(b + ((uint64_t)uniform + lane)) = v;
 #endif
 }
 
@@ -1443,18 +1462,6 @@ LBM_HD void step_node_view(const CavityConst<R> &c, const NodeConst<R, RH> &n, i
 // layout with the FP64 rest enthalpy population: the LDS holds each
 // population in the type it is stored in.
 // ---------------------------------------------------------------------------
-#if defined(__HIP_DEVICE_COMPILE__)
-#define LBM_HOST_CHECK(cond) ((void)0)
-#else
-#define LBM_HOST_CHECK(cond)                                                              \
-    do {                                                                                  \
-        if (!(cond)) {                                                                    \
-            fprintf(stderr, "lbm: check failed: %s (%s:%d)\n", #cond, __FILE__, __LINE__); \
-            abort();                                                                      \
-        }                                                                                 \
-    } while (0)
-#endif
-
 // How a layout keeps its populations in LDS for the K-step kernels: encoded
 // exactly as it stores them (element type, 16-bit scale, split base), so
 // that the next update sees the same values as a one-step launch would

@@ -61,8 +61,8 @@ inline int min_band_rows(int nx) { return std::max(LBM_MIN_BAND_ROWS, (2048 + nx
 
 inline lbm_status map_params(const lbm_params &p, lbm_precision prec, Lattice &l) {
     if (p.nx < 4 || p.ny < 4) return fail(LBM_EINVAL, "grid %dx%d: each side needs >= 4 nodes", p.nx, p.ny);
-    // the step kernels address a tile's rows by 32-bit byte offsets from its
-    // first row: a few dozen rows of 8-byte elements must stay below 2^31
+    // a band holds at least 32 rows and must stay below 2^31 bytes (the step
+    // kernels address two of them by unsigned 32-bit offsets)
     if (p.nx > LBM_MAX_NX) return fail(LBM_EINVAL, "grid %dx%d: rows longer than %d nodes", p.nx, p.ny, LBM_MAX_NX);
     if ((int64_t)((p.nx + 63) & ~63) * p.ny >= ((int64_t)1 << 31) - 4096)
         return fail(LBM_EINVAL, "grid %dx%d: rows padded to 64 nodes exceed 2^31 nodes", p.nx, p.ny);
