@@ -5,9 +5,7 @@
 #include <hip/hip_runtime.h>
 
 #include <algorithm>
-#include <condition_variable>
 #include <mutex>
-#include <thread>
 #include <cstddef>
 #include <cmath>
 #include <cstdarg>
@@ -23,6 +21,7 @@
 #include "../../include/lbmpcm.h"
 #include "lbm_internal.h"
 #include "lbm_plan.h"
+#include "lbm_planes.h"
 #include "lbm_tiles.h"
 
 using namespace lbm;
@@ -142,6 +141,7 @@ constexpr int64_t kStageNodes = (int64_t)1 << 22;
 // a read either way, the slots themselves about 2 ms).
 constexpr int64_t kSlotNodes = (int64_t)1 << 17, kSlotsFrom = (int64_t)1 << 19, kOneSlot = (int64_t)1 << 14;
 constexpr int kSlots = 4;
+static_assert(kSlots <= PlaneCopy::kMaxSlots, "a counter per slot");
 
 // The deep tile shape of a handle: the first that leaves at most a tile per
 // CU (kDeepTiles).  Periodic problems, whose rings may wrap more than once,
@@ -999,85 +999,6 @@ bool on_host(const void *p) {
     return true;
 }
 
-// Copies pieces of field planes out of the slots as they become ready: the
-// caller and helper threads take parts of the ready pieces in order, so that
-// any number of helpers, none included, does the work.  Helpers are started for
-// planes of some size only (one for every 4 MiB) and end with the call.
-class PlaneCopy {
-public:
-    static constexpr int kParts = 8;
-    PlaneCopy(double *const outs[6], const double *slots, int64_t slot_doubles, int nslots, int64_t piece, int64_t nodes)
-        : outs_(outs), slots_(slots), slot_doubles_(slot_doubles), nslots_(nslots), piece_(piece), nodes_(nodes),
-          done_((size_t)((nodes + piece - 1) / piece), 0) {
-        const int64_t mib = nodes * 6 * (int64_t)sizeof(double) >> 20;
-        const int cpus = (int)std::thread::hardware_concurrency();
-        const int helpers = (int)std::min<int64_t>({mib / 4, kParts - 1, cpus > 1 ? cpus - 1 : 0});
-        try {
-            for (int i = 0; i < helpers; ++i) threads_.emplace_back([this] { serve(); });
-        } catch (...) {  // fewer helpers, or none
-        }
-    }
-    ~PlaneCopy() {
-        {
-            std::lock_guard<std::mutex> l(m_);
-            quit_ = true;
-        }
-        ready_cv_.notify_all();
-        for (std::thread &t : threads_) t.join();
-    }
-    // The slots of pieces before n are complete.
-    void publish(int64_t n) {
-        {
-            std::lock_guard<std::mutex> l(m_);
-            ready_ = n * kParts;
-        }
-        ready_cv_.notify_all();
-    }
-    // Returns when piece p is copied out; takes part in the copying.
-    void finish(int64_t p) {
-        std::unique_lock<std::mutex> l(m_);
-        while (done_[p] < kParts && take(l)) {
-        }
-        done_cv_.wait(l, [&] { return done_[p] == kParts; });
-    }
-
-private:
-    void serve() {
-        std::unique_lock<std::mutex> l(m_);
-        for (;;) {
-            ready_cv_.wait(l, [this] { return quit_ || next_ < ready_; });
-            if (quit_) return;
-            while (take(l)) {
-            }
-        }
-    }
-    // Copies the next part, if one is ready.
-    bool take(std::unique_lock<std::mutex> &l) {
-        if (next_ >= ready_) return false;
-        const int64_t p = next_ / kParts, part = next_ % kParts;
-        ++next_;
-        l.unlock();
-        const int64_t o = p * piece_, n = std::min(piece_, nodes_ - o);
-        const int64_t a = n * part / kParts, b = n * (part + 1) / kParts;
-        const double *slot = slots_ + (p % nslots_) * slot_doubles_;
-        for (int q = 0; q < 6; ++q)
-            std::memcpy(outs_[q] + o + a, slot + q * n + a, (size_t)(b - a) * sizeof(double));
-        l.lock();
-        if (++done_[p] == kParts) done_cv_.notify_one();
-        return true;
-    }
-
-    double *const *outs_;
-    const double *slots_;
-    int64_t slot_doubles_, nslots_, piece_, nodes_;
-    std::mutex m_;
-    std::condition_variable ready_cv_, done_cv_;
-    int64_t ready_ = 0, next_ = 0;  // parts that may be, that have been taken
-    std::vector<int> done_;         // parts of each piece that are copied
-    bool quit_ = false;
-    std::vector<std::thread> threads_;
-};
-
 // Field planes of rows [y0, y0 + rows) through the pinned slots: the macro
 // kernel writes a piece of whole rows straight into one while earlier pieces
 // are copied out.  The runtime's copies to ordinary memory ran at 10 GB/s (fresh
@@ -1112,9 +1033,10 @@ lbm_status fields_through_slots(lbm_handle *h, int c, int y0, int rows, double *
         if (s == LBM_OK) copy.finish(pieces - 1);
     }
     if (s != LBM_OK) {  // nothing writes the slots any more when the call returns
-        const std::string msg = g_err;
+        char msg[sizeof(g_err)];
+        std::memcpy(msg, g_err, sizeof(msg));
         (void)hipStreamSynchronize(h->stream);
-        return fail(s, "%s", msg.c_str());
+        return fail(s, "%s", msg);
     }
     return LBM_OK;
 }
