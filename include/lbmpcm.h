@@ -293,9 +293,14 @@ int64_t lbm_step_count(const lbm_handle *h);
 /* Macroscopic fields of one cavity at the current step, from the
  * post-streaming populations: velocity u of Eq. (23), T_f and f_l of
  * Eqs. (38)-(39), T_m of Eq. (48), density of Eq. (21).  Any pointer may be
- * NULL.  Synchronises the stream.  All six planes of a cavity of 2^19 nodes or
- * more come through 24 MiB of pinned host memory that the handle holds, copied
- * out by the caller and up to seven threads that end with the call. */
+ * NULL.  Synchronises the stream.  Reads of all six planes into host memory go
+ * through pinned host memory that the handle holds: on a handle with a cavity
+ * of 2^19 nodes or more and no row above 2^17 nodes 24 MiB, had at the first
+ * read of 2^19 nodes or more or at the third of fewer, and copied out by the
+ * caller and up to seven threads that end with the call; on a handle whose
+ * cavities all have at most 2^14 nodes 48 bytes for each node of the largest,
+ * had at creation.  Other reads, and all if no pinned memory is to be had, are
+ * copied by the runtime. */
 lbm_status lbm_fields(lbm_handle *h, int32_t cavity, double *ux, double *uy, double *T_pcm,
                       double *T_mf, double *f_l, double *rho);
 

@@ -134,12 +134,20 @@ struct Plan {
 // staging area stays a small part of the memory however large a cavity is.
 constexpr int64_t kStageNodes = (int64_t)1 << 22;
 
-// Field planes come back through pinned slots: four of whole rows of at most
-// kSlotNodes nodes (6 MiB) each for handles with a cavity of kSlotsFrom nodes or
-// more, one for handles whose cavities all fit kOneSlot.  Between the two the
-// runtime's copies are as fast and a handle's first read costs less (256^2: 0.19 ms
-// a read either way, the slots themselves about 2 ms).
+// Field planes come back through pinned slots: one for handles whose cavities
+// all fit kOneSlot; for handles with a cavity of kSlotsFrom nodes or more, four of
+// whole rows of at most kSlotNodes nodes (6 MiB) each, from the first read of
+// kSlotsFrom nodes on.  The first read through new slots touches their memory,
+// which costs more than the runtime's copies of a few rows (1024^2, us, slots
+// against copies: 1 row 205 against 109, later 26 against 94; 64 rows 1450 and 212,
+// later 163 and 199; 256 rows 2250 and 773, later 348 and 723), so the first
+// kSmallReads smaller reads of a handle go without.  Cavities between the two
+// limits keep the runtime's copies (whole read, first and later, copies against
+// slots: 256^2 1.2 and 0.20 ms against 1.6 and 0.16; 384^2 0.48 and 0.45 against 2.9 and
+// 0.29; 512^2 0.77 and 0.71 against 2.6 and 0.36; 700^2 1.5 and 1.3 against 3.8 and 0.58):
+// the slots pay there from the fourth read to the fifteenth.
 constexpr int64_t kSlotNodes = (int64_t)1 << 17, kSlotsFrom = (int64_t)1 << 19, kOneSlot = (int64_t)1 << 14;
+constexpr int kSmallReads = 2;
 constexpr int kSlots = 4;
 static_assert(kSlots <= PlaneCopy::kMaxSlots, "a counter per slot");
 
@@ -315,6 +323,7 @@ struct lbm_handle {
     void *hslots = nullptr;   // their memory, where it is not part of hdiag's
     int nslots = 0;
     int64_t slot_nodes = 0;
+    int small_reads = 0;      // reads below kSlotsFrom nodes so far (up to kSmallReads)
     hipEvent_t hready[kSlots] = {};
 
     void *pop(int b) { return ws + pl.off_pop[b]; }
@@ -700,9 +709,13 @@ void pin_results(lbm_handle *h) {
     if (h->hdiag && one) give_slots(h, 1, h->pl.max_nodes, (char *)h->hdiag + head);
 }
 
-// The slots of large cavities, at the first read-back that can use them.
-void pin_slots(lbm_handle *h) {
+// The slots of large cavities, for a read of that many nodes.
+void pin_slots(lbm_handle *h, int64_t nodes) {
     if (h->hslot || h->hslots || h->pl.max_nodes < kSlotsFrom || h->pl.max_nx > kSlotNodes) return;
+    if (nodes < kSlotsFrom && h->small_reads < kSmallReads) {
+        ++h->small_reads;
+        return;
+    }
     h->hslots = pinned((size_t)kSlots * 6 * kSlotNodes * sizeof(double));
     if (h->hslots) give_slots(h, kSlots, kSlotNodes, h->hslots);
 }
@@ -1054,7 +1067,7 @@ extern "C" lbm_status lbm_fields_rows(lbm_handle *h, int32_t c, int32_t y0, int3
     // all planes to host memory: through the slots
     bool slots = true;
     for (int k = 0; k < 6 && slots; ++k) slots = outs[k] && on_host(outs[k]);
-    if (slots) pin_slots(h);
+    if (slots) pin_slots(h, (int64_t)rows * p.nx);
     if (slots && h->hslot) return fields_through_slots(h, c, y0, rows, outs);
     for (int r0 = 0; r0 < rows; r0 += chunk) {
         const int nr = std::min(chunk, rows - r0);
