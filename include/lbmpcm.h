@@ -201,9 +201,12 @@ typedef struct lbm_diag {
  * As long as no shape has been set, handles of at most 256 small tiles (one
  * cavity of about 256^2 nodes; FP32 and FP64 forms, not periodic) run four to
  * six steps per launch, in tiles of their own, wherever a call has them, and
- * larger FP64 handles three (D2Q9: from about 320^2 nodes in all); what
- * lbm_get_launch reports is then the shape that lbm_set_launch with the same
- * values puts in force.  lbm_autotune times both. */
+ * larger FP64 handles three (D2Q9: from about 320^2 nodes in all).  These
+ * launches are the library's own and can't be asked for: lbm_get_launch reports
+ * the shape a caller may set, lbm_launch_steps what runs.  lbm_set_launch, also
+ * with the values lbm_get_launch reports, leaves the own launches for the shape
+ * it names; lbm_autotune times both and keeps the faster, so it may bring them
+ * back. */
 typedef struct lbm_launch_config {
     int32_t block;            /* threads per workgroup: 64, 128, 256 or 512      */
     int32_t nodes_per_thread; /* 1, 2 or 4 consecutive-by-block nodes per thread */
@@ -351,6 +354,12 @@ lbm_status lbm_lattice_of(const lbm_params *p, lbm_precision prec, lbm_lattice *
 /* Read or set the step kernel's launch shape. */
 lbm_status lbm_get_launch(const lbm_handle *h, lbm_launch_config *out);
 lbm_status lbm_set_launch(lbm_handle *h, const lbm_launch_config *cfg);
+
+/* Steps per launch that lbm_step runs now, the library's own launches included
+ * (a remainder of a call takes smaller ones), and their tile in *tile_w and
+ * *tile_h (0 with one step per launch; either pointer may be NULL); -1 on a NULL
+ * handle. */
+int32_t lbm_launch_steps(const lbm_handle *h, int32_t *tile_w, int32_t *tile_h);
 
 /* Time every supported launch shape (one-step launch shapes; two and three
  * steps per launch in every tile shape) for steps_per_trial launches on

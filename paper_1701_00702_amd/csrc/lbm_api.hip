@@ -1211,6 +1211,19 @@ extern "C" lbm_status lbm_get_launch(const lbm_handle *h, lbm_launch_config *out
     return LBM_OK;
 }
 
+extern "C" int32_t lbm_launch_steps(const lbm_handle *h, int32_t *tile_w, int32_t *tile_h) {
+    if (!h) {
+        (void)fail(LBM_EINVAL, "handle is NULL");
+        return -1;
+    }
+    int tw = 0, th = 0, k = h->run_k();
+    if (h->deep()) (void)deep_tile(h->st, h->pl.deep, &tw, &th, &k);
+    else if (k > 1) stepk_tile(h->st, k, h->shapek[k], &tw, &th);
+    if (tile_w) *tile_w = tw;
+    if (tile_h) *tile_h = th;
+    return k;
+}
+
 namespace {
 // Launch shape lc from here on; own: the library's choice, with deep launches
 // or own_k steps per launch where the handle has them.

@@ -117,6 +117,7 @@ def _load():
         "lbm_lattice_of": ([PP, ctypes.c_int, ctypes.POINTER(lbm_lattice)], st),
         "lbm_get_launch": ([H, ctypes.POINTER(lbm_launch_config)], st),
         "lbm_set_launch": ([H, ctypes.POINTER(lbm_launch_config)], st),
+        "lbm_launch_steps": ([H, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)], ctypes.c_int32),
         "lbm_autotune": ([H, ctypes.c_int32, ctypes.c_char_p, ctypes.POINTER(lbm_launch_config)], st),
         "lbm_save": ([H, ctypes.c_char_p], st),
         "lbm_load": ([H, ctypes.c_char_p], st),
@@ -305,6 +306,12 @@ def lbm_set_launch(h: int, block=256, nodes_per_thread=1, xcd_remap=1, persisten
         tile_shape = cur["tile_shape"] if steps_per_launch == cur["steps_per_launch"] else 0
     c = lbm_launch_config(block, nodes_per_thread, xcd_remap, persistent, steps_per_launch, tile_shape, 0, 0)
     _check(_lib.lbm_set_launch(h, ctypes.byref(c)))
+
+
+def lbm_launch_steps(h: int) -> tuple:
+    """(steps per launch that lbm_step runs now, tile_w, tile_h)"""
+    w, t = ctypes.c_int32(0), ctypes.c_int32(0)
+    return int(_lib.lbm_launch_steps(h, ctypes.byref(w), ctypes.byref(t))), w.value, t.value
 
 
 def lbm_autotune(h: int, steps_per_trial: int = 5, cache_path: str | None = None) -> dict:
