@@ -2,8 +2,9 @@
 
 Prints one JSON line.  A step advances every node of the workload by one
 time step; the library's default launch does three steps per launch
-through LDS tiles (two for FP64 storage), bit-identical to one-step
-launches, and the one-step kernel is timed beside it.  Workload (default:
+through LDS tiles (four to six for small cavities, two for FP64 cavities in
+between), bit-identical to one-step launches, and the one-step kernel is
+timed beside it.  Workload (default:
 the 8192 x 8192 cavity, Ra = 1e7, Da = 1e-5, phi = 0.9, Ste = 0.5,
 lambda = 1000, FP32 storage, 67.1 M nodes, 15 GB of double-buffered
 populations).  Inputs are resident in HBM before timing;
@@ -146,6 +147,17 @@ def make_solver(lbm, torch, params, precision, stream):
     base = (ws.data_ptr() + 255) // 256 * 256
     s = lbm.Solver(params, precision, workspace=(base, nbytes), stream=stream.cuda_stream)
     return s, ws
+
+
+def set_shape(lbm, h, args, tile_shape=None):
+    """The launch shape the options name.  Without one the handle keeps the
+    library's own launches (four to six steps for small cavities, three for
+    FP64), which no shape asks for."""
+    if args.block is None and args.npt is None and args.xcd is None and args.persistent is None and \
+            not args.steps_per_launch and tile_shape is None:
+        return
+    lbm.lbm_set_launch(h, args.block or 512, args.npt or 1, 1 if args.xcd is None else args.xcd,
+                       args.persistent or 0, steps_per_launch=args.steps_per_launch or None, tile_shape=tile_shape)
 
 
 def time_steps(lbm, torch, s, stream, steps, warmup, looped=False):
@@ -303,10 +315,10 @@ def main():
     ap.add_argument("--precision", default=None, choices=[None] + list(BYTES_PER_NODE))
     ap.add_argument("--thermal-lattice", type=int, default=9, choices=[9, 5],
                     help="9: D2Q9 thermal fields (the paper's main method); 5: D2Q5 (Appendix B)")
-    ap.add_argument("--block", type=int, default=512)
-    ap.add_argument("--npt", type=int, default=1)
-    ap.add_argument("--xcd", type=int, default=1)
-    ap.add_argument("--persistent", type=int, default=0)
+    ap.add_argument("--block", type=int, default=None, help="launch shape (default: the library's own launches)")
+    ap.add_argument("--npt", type=int, default=None)
+    ap.add_argument("--xcd", type=int, default=None)
+    ap.add_argument("--persistent", type=int, default=None)
     ap.add_argument("--steps-per-launch", type=int, default=0, choices=[0, 1, 2, 3],
                     help="0: the library's default (several steps per launch through LDS where available)")
     ap.add_argument("--tile-shape", type=int, default=None, choices=[0, 1, 2],
@@ -368,9 +380,10 @@ def main():
     if args.autotune:
         launch = lbm.lbm_autotune(s.h, 5, os.path.join(tempfile.gettempdir(), "lbmpcm_autotune_cache.txt"))
     else:
-        lbm.lbm_set_launch(s.h, args.block, args.npt, args.xcd, args.persistent,
-                           steps_per_launch=args.steps_per_launch or None, tile_shape=args.tile_shape)
+        set_shape(lbm, s.h, args, args.tile_shape)
         launch = lbm.lbm_get_launch(s.h)
+    # what runs: the launch shape, or launches of the library's own
+    spl, tile_w, tile_h = lbm.lbm_launch_steps(s.h)
     nodes = sum(p["nx"] * p["ny"] for p in params)
     ms = time_steps(lbm, torch, s, stream, args.steps, args.warmup)
     d = s.diagnostics(0, allow_nonfinite=True)
@@ -378,7 +391,6 @@ def main():
     mlups = nodes / (ms_step * 1e-3) / 1e6
     # A launch reads and writes the state once, whether it advances one step
     # or several (through LDS): bytes are per launch.
-    spl = launch["steps_per_launch"]
     alg = bytes_per_node(prec, qt) * nodes
     launch_ms = ms_step * spl
     launch_s = launch_ms * 1e-3
@@ -434,8 +446,9 @@ def main():
         "data": "synthetic",
         "config": {"workload": desc, "nodes": nodes, "storage": prec, "storage_detail": storage_desc,
                    "thermal_lattice": qt, "launch": launch, "seed": seed,
-                   "step_kernel": (f"lbm::stepk_kernel ({launch['steps_per_launch']} fused steps per launch "
-                                   "through LDS tiles)" if launch["steps_per_launch"] > 1 else
+                   "running": {"steps_per_launch": spl, "tile_w": tile_w, "tile_h": tile_h},
+                   "step_kernel": (f"lbm::{'deep_kernel' if spl > 3 else 'stepk_kernel'} ({spl} fused steps per "
+                                   "launch through LDS tiles)" if spl > 1 else
                                    "lbm::step_kernel (fused pull-stream + NEE walls + 3 MRT collisions)")},
         "roofline": roof,
         "check": {"nonfinite": d["nonfinite"], "liquid_fraction": d["liquid_fraction"],
@@ -499,13 +512,12 @@ def main():
             s2, ws2 = make_solver(lbm, torch, ps, pr, stream)
             T_pcm, T_mf = W.initial_temperatures(ps[0], sd)
             s2.set_initial(0, T_pcm, T_mf)
-            lbm.lbm_set_launch(s2.h, args.block, args.npt, args.xcd, args.persistent,
-                               steps_per_launch=args.steps_per_launch or None)
+            set_shape(lbm, s2.h, args)
             n2 = ps[0]["nx"] * ps[0]["ny"]
             # 96 steps: whole multi-step launches for two and three steps
             t = time_steps(lbm, torch, s2, stream, 96, 12) / 96
             name = f"{wl}_d2q5_{pr}" if q == 5 else f"{wl}_{pr}"
-            sp2 = lbm.lbm_get_launch(s2.h)["steps_per_launch"]
+            sp2 = lbm.lbm_launch_steps(s2.h)[0]
             forms[name] = {"MLUPS": n2 / (t * 1e-3) / 1e6, "ms_per_step": t, "steps_per_launch": sp2,
                            "alg_GBps_per_launch": bytes_per_node(pr, q) * n2 / (t * sp2 * 1e-3) / 1e9}
             s2.close()
@@ -515,8 +527,7 @@ def main():
         s2, ws2 = make_solver(lbm, torch, ps, "f32", stream)
         for c, q in enumerate(ps):
             s2.set_initial(c, *W.initial_temperatures(q, sd + c))
-        lbm.lbm_set_launch(s2.h, args.block, args.npt, args.xcd, args.persistent,
-                           steps_per_launch=args.steps_per_launch or None)
+        set_shape(lbm, s2.h, args)
         n2 = sum(q["nx"] * q["ny"] for q in ps)
         t1 = time_steps(lbm, torch, s2, stream, 200, 10) / 200
         t2 = time_steps(lbm, torch, s2, stream, 20, 2, looped=True) / 20
