@@ -1279,7 +1279,8 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
                           &lc.persistent, &lc.steps_per_launch, &lc.tile_shape) == 7) {
                 if ((key == k || own_key == k) && valid_launch(lc, h->pl)) {
                     fclose(f);
-                    lbm_status s = apply_shape(h, lc, own_key == k);
+                    const bool own = own_key == k;
+                    lbm_status s = apply_shape(h, own ? h->own_lc : lc, own);
                     if (s == LBM_OK && chosen) *chosen = h->lc;
                     return s;
                 }
