@@ -366,8 +366,10 @@ int32_t lbm_launch_steps(const lbm_handle *h, int32_t *tile_w, int32_t *tile_h);
  * the live state (reads the current buffer, writes only scratch), keep the
  * fastest, and report it in *chosen (may be NULL).  With a non-NULL
  * cache_path the choice is looked up in / appended to that text file, keyed
- * by device, precision, number of cavities, total nodes and the first
- * cavity's sizes.  Synchronises the stream. */
+ * by device, precision, number of cavities, total nodes, the first cavity's
+ * sizes and, for handles with launches of the library's own, which of the two
+ * won (lines of such handles without that mark did not time them and are passed
+ * over).  Synchronises the stream. */
 lbm_status lbm_autotune(lbm_handle *h, int32_t steps_per_trial, const char *cache_path,
                         lbm_launch_config *chosen);
 

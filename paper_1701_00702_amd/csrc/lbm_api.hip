@@ -1268,7 +1268,11 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
                                    lbm_launch_config *chosen) {
     if (!h) return fail(LBM_EINVAL, "handle is NULL");
     if (steps < 1) return fail(LBM_EINVAL, "steps_per_trial must be >= 1");
-    const std::string key = tune_key(h), own_key = key + ":own";
+    // The key says what was timed: of a handle with launches of its own a line
+    // is marked with whether they or a shape won (an unmarked one is of a time
+    // without them and is passed over).
+    const bool has_own = h->pl.deep >= 0 || h->pl.own_k;
+    const std::string key = tune_key(h) + (has_own ? ":shape" : ""), own_key = tune_key(h) + ":own";
     if (cache_path) {
         FILE *f = fopen(cache_path, "r");
         if (f) {
@@ -1277,7 +1281,7 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
             std::memset(&lc, 0, sizeof(lc));
             while (fscanf(f, "%255s %d %d %d %d %d %d", k, &lc.block, &lc.nodes_per_thread, &lc.xcd_remap,
                           &lc.persistent, &lc.steps_per_launch, &lc.tile_shape) == 7) {
-                if ((key == k || own_key == k) && valid_launch(lc, h->pl)) {
+                if ((key == k || (has_own && own_key == k)) && valid_launch(lc, h->pl)) {
                     fclose(f);
                     const bool own = own_key == k;
                     lbm_status s = apply_shape(h, own ? h->own_lc : lc, own);
@@ -1366,7 +1370,7 @@ extern "C" lbm_status lbm_autotune(lbm_handle *h, int32_t steps, const char *cac
                 }
     }
     // the library's own launches: deep ones, or own_k steps each
-    if (h->pl.deep >= 0 || h->pl.own_k) {
+    if (has_own) {
         const int own_k = h->pl.deep >= 0 ? h->pl.deep_k : h->pl.own_k;
         auto own = [&]() -> hipError_t {
             return h->pl.deep >= 0 ? launch_deep(deep_args(h, own_k, h->cur, h->acc_scratch()), h->stream)
