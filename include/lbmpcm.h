@@ -400,7 +400,8 @@ lbm_status lbm_copy_state(lbm_handle *h, int32_t cavity, void *host, uint64_t by
 lbm_status lbm_debug_poke(lbm_handle *h, int32_t cavity, int32_t x, int32_t y, int32_t field,
                           int32_t dir, double value);
 
-/* Release the handle and everything the library allocated for it. */
+/* Release the handle and everything the library allocated for it.  A capture of
+ * another stream that is under way goes on. */
 lbm_status lbm_destroy(lbm_handle *h);
 
 /* Message of the last failing call on this thread ("" if none). */

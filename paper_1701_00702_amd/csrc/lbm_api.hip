@@ -675,16 +675,25 @@ lbm_status init_cavity(lbm_handle *h, int c, const double *T_pcm, const double *
     return LBM_OK;
 }
 
-// Pinned memory, or nullptr.  Relaxed: a capture that another thread has under
-// way is not disturbed.
+// This thread's calls under the relaxed capture mode: a capture that is under
+// way, here or in another thread, neither refuses them nor is disturbed.
+class RelaxedCapture {
+    hipStreamCaptureMode mode_ = hipStreamCaptureModeRelaxed;
+    const bool set_ = hipThreadExchangeStreamCaptureMode(&mode_) == hipSuccess;
+
+public:
+    ~RelaxedCapture() {
+        if (set_) (void)hipThreadExchangeStreamCaptureMode(&mode_);
+    }
+};
+
+// Pinned memory, or nullptr.
 void *pinned(size_t bytes) {
-    hipStreamCaptureMode mode = hipStreamCaptureModeRelaxed;
-    const bool relaxed = hipThreadExchangeStreamCaptureMode(&mode) == hipSuccess;
+    const RelaxedCapture relaxed;
     void *m = nullptr;
-    if (hipHostMalloc(&m, bytes, hipHostMallocDefault) != hipSuccess) m = nullptr;
-    if (relaxed) (void)hipThreadExchangeStreamCaptureMode(&mode);
-    if (!m) (void)hipGetLastError();
-    return m;
+    if (hipHostMalloc(&m, bytes, hipHostMallocDefault) == hipSuccess) return m;
+    (void)hipGetLastError();
+    return nullptr;
 }
 
 // n events and n slots at m for the read-backs of field planes, if all can be had.
@@ -852,6 +861,7 @@ extern "C" lbm_status lbm_create_ext(const lbm_params *p, int32_t n, lbm_precisi
 
 extern "C" lbm_status lbm_destroy(lbm_handle *h) {
     if (!h) return LBM_OK;
+    const RelaxedCapture relaxed;  // otherwise the wait and the frees are refused, and the memory is lost
     (void)hipStreamSynchronize(h->stream);
     drop_graphs(h);
     if (h->cap) (void)hipStreamDestroy(h->cap);
