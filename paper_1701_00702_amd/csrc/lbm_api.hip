@@ -250,7 +250,7 @@ lbm_status make_plan(const lbm_params *p, int n, lbm_precision prec, Plan &pl) {
         stepk_tile(st, 3, 0, &tw, &th);
         int64_t count = 0;
         for (int c = 0; c < n; ++c) count += count_tiles2(p[c].nx, p[c].ny, tw, th);
-        if (stepk_three(st, count)) {
+        if (stepk_three(st, count, kCus)) {
             if (count >= ((int64_t)1 << 31)) return fail(LBM_EINVAL, "too many tiles");
             pl.own_k = 3;
             pl.tilesk[3] = count;
@@ -739,7 +739,9 @@ lbm_status setup(lbm_handle *h) {
     pin_results(h);
     int ncu = 0;
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
-    h->n_cu = ncu > 0 ? ncu : 256;
+    h->n_cu = ncu > 0 ? ncu : kCus;
+    if (h->pl.deep >= 0 && !deep_fits(h->pl.deep_tiles, h->n_cu)) h->pl.deep = -1;
+    if (h->pl.own_k && !stepk_three(h->st, h->pl.tilesk[3], h->n_cu)) h->pl.own_k = 0;
     HIP_TRY(hipMemsetAsync(h->ws, 0, h->pl.total, h->stream));
     // cavity table in the kernels' arithmetic type (FP64 forms: double)
     if (real_size(h->st) == 8) {

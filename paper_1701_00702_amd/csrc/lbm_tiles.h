@@ -160,7 +160,12 @@ struct Step3Tile<ST5_F64> {  // 160 B per slot, 34 x 12 slots
 // the smaller two-step tiles are faster (us a step, two -> three steps: 270^2, 306
 // tiles, 6.56 -> 7.81; 300^2, 380 tiles, 7.64 -> 7.91; 350^2, 484 tiles, 9.82 -> 8.63;
 // 450^2 14.3 -> 13.8; 640^2 24.2 -> 21.2.  D2Q5 270^2, 243 tiles, 8.05 -> 5.69).
-constexpr bool three_steps(int st, int64_t tiles) { return st == ST5_F64 || (st == ST_F64 && tiles >= 384); }
+// The plan, which knows no device, reserves for the CUs of an MI355X; a handle
+// on a device with other ones asks again with its own number.
+constexpr int kCus = 256;
+constexpr bool three_steps(int st, int64_t tiles, int n_cu = kCus) {
+    return st == ST5_F64 || (st == ST_F64 && 2 * tiles >= 3 * (int64_t)n_cu);
+}
 
 template <int ST, int K>
 struct StepKTile;
@@ -220,7 +225,8 @@ constexpr TileDims dims_of(int i) {
 // -> 5.70; D2Q5 FP32 64^2 3.93 -> 2.13, 256^2 3.80 -> 2.82.  With two tiles on a
 // CU they lose (FP32_H64 300^2 16x16: 6.0 -> 7.7).
 constexpr int kDeepShapes = 4;
-constexpr int kDeepTiles = 256;  // the CUs of an MI355X
+constexpr int kDeepTiles = kCus;  // reserved for by the plan
+constexpr bool deep_fits(int64_t tiles, int n_cu) { return tiles <= n_cu; }  // what a handle then runs
 struct DeepDims {
     int tw, th, k;
 };
