@@ -119,8 +119,9 @@ struct Plan {
     int64_t tilesk[4] = {0, 0, 0, 0};
     size_t off_tilesk[4] = {0, 0, 0, 0};
     // steps of the library's own K-step launches where a caller can't ask for
-    // that many (0: none)
+    // that many (0: none), and the tiles that decide it
     int own_k = 0;
+    ThreeStepTiles own_tiles{0, 0, 0};
     // deep launches: tile shape (-1: the handle takes none), tiles, most steps
     int deep = -1, deep_k = 0;
     int64_t deep_tiles = 0;
@@ -246,16 +247,21 @@ lbm_status make_plan(const lbm_params *p, int n, lbm_precision prec, Plan &pl) {
     }
     choose_deep(p, n, pl);
     if (!stepk_supported(st, 3) && pl.deep < 0) {
-        int tw, th;
+        int tw, th, tw2, th2;
         stepk_tile(st, 3, 0, &tw, &th);
-        int64_t count = 0;
-        for (int c = 0; c < n; ++c) count += count_tiles2(p[c].nx, p[c].ny, tw, th);
-        if (stepk_three(st, count, kCus)) {
-            if (count >= ((int64_t)1 << 31)) return fail(LBM_EINVAL, "too many tiles");
+        stepk_tile(st, 2, 0, &tw2, &th2);
+        ThreeStepTiles &t = pl.own_tiles;
+        for (int c = 0; c < n; ++c) {
+            t.three += count_tiles2(p[c].nx, p[c].ny, tw, th);
+            t.wall += count_wall_tiles2(p[c].nx, p[c].ny, p[c].bc_x == 1, tw, th, 4);
+            t.two += count_tiles2(p[c].nx, p[c].ny, tw2, th2);
+        }
+        if (three_steps(st, t)) {
+            if (t.three >= ((int64_t)1 << 31)) return fail(LBM_EINVAL, "too many tiles");
             pl.own_k = 3;
-            pl.tilesk[3] = count;
+            pl.tilesk[3] = t.three;
             pl.off_tilesk[3] = off;
-            off = align256(off + (size_t)count * sizeof(Tile2));
+            off = align256(off + (size_t)t.three * sizeof(Tile2));
         }
     }
     pl.off_deep = off;
@@ -741,7 +747,7 @@ lbm_status setup(lbm_handle *h) {
     HIP_TRY(hipDeviceGetAttribute(&ncu, hipDeviceAttributeMultiprocessorCount, h->device));
     h->n_cu = ncu > 0 ? ncu : kCus;
     if (h->pl.deep >= 0 && !deep_fits(h->pl.deep_tiles, h->n_cu)) h->pl.deep = -1;
-    if (h->pl.own_k && !stepk_three(h->st, h->pl.tilesk[3], h->n_cu)) h->pl.own_k = 0;
+    if (h->pl.own_k && !three_steps(h->st, h->pl.own_tiles, h->n_cu)) h->pl.own_k = 0;
     HIP_TRY(hipMemsetAsync(h->ws, 0, h->pl.total, h->stream));
     // cavity table in the kernels' arithmetic type (FP64 forms: double)
     if (real_size(h->st) == 8) {

@@ -259,9 +259,6 @@ struct InitLaunch {
 hipError_t launch_step(const StepLaunch &L, hipStream_t s);
 hipError_t launch_stepk(const Step2Launch &L, hipStream_t s);
 bool stepk_supported(int storage, int k);  // K steps per launch (K = 2, 3), as a caller may ask for
-// Whether the library runs three steps per launch by itself where a caller may
-// not ask for them, for a handle of that many tiles (shape 0).
-bool stepk_three(int storage, int64_t tiles, int n_cu);
 // Tile shape `shape` (0 .. LBM_TILE_SHAPES - 1) of the K-step kernel; 0 x 0
 // when it does not exist.
 #define LBM_TILE_SHAPES 3

@@ -413,7 +413,6 @@ static hipError_t launch_stepk_s(const Step2Launch &L, hipStream_t s) {
 }
 
 bool stepk_supported(int storage, int k) { return stepk_offered(storage, k); }
-bool stepk_three(int storage, int64_t tiles, int n_cu) { return three_steps(storage, tiles, n_cu); }
 
 template <int ST, int K>
 static void tile_of(int shape, int *tw, int *th) {

@@ -516,6 +516,19 @@ inline void cavity_tiles2(int cav, int nx, int ny, int tw, int th, std::vector<T
                 tiles.push_back(Tile2{cav, xs[q].first, yr.first, xs[q].second, yr.second});
 }
 
+// Those of a cavity's tiles that hold a node within `reach` nodes of a wall.
+inline int64_t count_wall_tiles2(int nx, int ny, bool periodic, int tw, int th, int reach) {
+    std::vector<std::pair<int, int>> xs, ys;
+    split_runs(nx, tw, xs);
+    split_runs(ny, th, ys);
+    auto clear = [&](const std::vector<std::pair<int, int>> &runs, int n) {
+        return std::count_if(runs.begin(), runs.end(),
+                             [&](const auto &r) { return r.first >= reach && r.first + r.second <= n - reach; });
+    };
+    const int64_t cols = periodic ? (int64_t)xs.size() : clear(xs, nx);
+    return (int64_t)xs.size() * (int64_t)ys.size() - cols * clear(ys, ny);
+}
+
 inline int64_t count_tiles2(int nx, int ny, int tw, int th) {
     std::vector<std::pair<int, int>> xs, ys;
     split_runs(nx, tw, xs);

@@ -154,17 +154,35 @@ template <>
 struct Step3Tile<ST5_F64> {  // 160 B per slot, 34 x 12 slots
     static constexpr int TW = 32, TH = 10, NT = round64((TW + 4) * (TH + 4));
 };
-// Whether a handle of that many three-step FP64 tiles runs them.  D2Q5: always.
+// The tiles of an FP64 handle: three-step ones, those of them next to a wall,
+// and two-step ones.
+struct ThreeStepTiles {
+    int64_t three, wall, two;
+};
+// Whether a handle with those tiles runs three steps per launch.  D2Q5: always.
 // D2Q9: from three quarters of the workgroups the chip holds (two per CU); with
 // fewer, the three-step kernel's tiles take their time with CUs to spare and
 // the smaller two-step tiles are faster (us a step, two -> three steps: 270^2, 306
 // tiles, 6.56 -> 7.81; 300^2, 380 tiles, 7.64 -> 7.91; 350^2, 484 tiles, 9.82 -> 8.63;
 // 450^2 14.3 -> 13.8; 640^2 24.2 -> 21.2.  D2Q5 270^2, 243 tiles, 8.05 -> 5.69).
+// Beyond one round of tiles (two per CU) a launch takes as long as the fullest CU,
+// so three steps need that CU's tiles to be less than three quarters of the
+// two-step kernel's, unless few tiles are at walls, which cost the three-step
+// kernel about twice the others (two steps -> three: 16 cavities of 101x41 to
+// 240x203, 3 tiles on the fullest CU against 4, two thirds at walls, 10.2 -> 14.6;
+// 30 of 65^2, 4 against 5, all at walls, 13.3 -> 15.1; 20000x4 6.8 -> 8.3; 500x300, 3
+// against 4, a sixth at walls, 10.7 -> 10.5; 957x204, 4 against 5, a seventh, 13.1 ->
+// 11.7).  Of 1756 handles of mixed sizes 32 are then slower than with two steps
+// per launch of the kernels before, the worst by 9%, instead of 150, the worst by
+// 35%.
 // The plan, which knows no device, reserves for the CUs of an MI355X; a handle
 // on a device with other ones asks again with its own number.
 constexpr int kCus = 256;
-constexpr bool three_steps(int st, int64_t tiles, int n_cu = kCus) {
-    return st == ST5_F64 || (st == ST_F64 && 2 * tiles >= 3 * (int64_t)n_cu);
+constexpr bool three_steps(int st, const ThreeStepTiles &t, int n_cu = kCus) {
+    if (st != ST_F64) return st == ST5_F64;
+    const int64_t fullest3 = (t.three + n_cu - 1) / n_cu, fullest2 = (t.two + n_cu - 1) / n_cu;
+    return 2 * t.three >= 3 * (int64_t)n_cu &&
+           (t.three <= 2 * (int64_t)n_cu || 4 * fullest3 < 3 * fullest2 || 10 * t.wall < 3 * t.three);
 }
 
 template <int ST, int K>

@@ -47,6 +47,12 @@ RULES = [
     ("f64", [_cavity(257, 256, 5)], (3, 32, 10)),
     ("f64", [_cavity(128, 64), _cavity(128, 64)], (5, 8, 8)),
     ("f64", [_cavity(384, 200), _cavity(384, 56)], (3, 32, 8)),
+    ("f64", [_cavity(65, 65)] * 30, (2,)),                 # 810, all at walls, 4 on the fullest CU against 5
+    ("f64", [_cavity(20000, 4)], (2,)),
+    ("f64", [_cavity(500, 300)], (3, 32, 8)),              # 608, a sixth at walls
+    ("f64", [_cavity(64, 64)] * 64, (3, 32, 8)),           # 1024, all at walls, 4 against 7
+    ("f64", [_channel(280, 685)], (3, 32, 8)),             # walls at the bottom and the top only
+    ("f64", [_cavity(65, 65, 5)] * 30, (3, 32, 10)),
     ("f64", [_channel(64, 64)], (2,)),              # periodic: not deep
     ("f32h64", [_channel(64, 64)], (3, 32, 10)),
     ("f64", [_channel(320, 330)], (3, 32, 8)),

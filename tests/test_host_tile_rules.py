@@ -18,10 +18,14 @@ int main() {
     for (int cu : {256, 128, 64, 32}) {
         int deep = 0, three = 0;
         while (deep_fits(deep + 1, cu)) ++deep;
-        while (!three_steps(ST_F64, three, cu)) ++three;
-        printf("%d %d %d %d %d\n", cu, deep, three, (int)three_steps(ST5_F64, 1, cu), (int)three_steps(ST_F32, 9999, cu));
+        while (!three_steps(ST_F64, {three, three, three}, cu)) ++three;
+        printf("%d %d %d %d %d\n", cu, deep, three, (int)three_steps(ST5_F64, {1, 1, 1}, cu),
+               (int)three_steps(ST_F32, {9999, 0, 99999}, cu));
     }
-    printf("%d %d\n", kDeepTiles, (int)three_steps(ST_F64, 384));
+    // beyond one round: the fullest CU's tiles, or few at walls
+    auto q9 = [](int64_t three, int64_t wall, int64_t two) { return (int)three_steps(ST_F64, {three, wall, two}); };
+    printf("%d %d %d %d %d %d %d %d\n", kDeepTiles, q9(384, 384, 384), q9(512, 512, 512), q9(513, 513, 1024),
+           q9(513, 513, 1025), q9(768, 230, 768), q9(768, 231, 768), q9(4096, 4096, 6560));
 }
 """
 
@@ -38,4 +42,4 @@ def test_own_launches_follow_the_compute_units(tmp_path):
     rows = [[int(v) for v in line.split()] for line in out.splitlines()]
     # CUs, most deep tiles, fewest three-step FP64 D2Q9 tiles, D2Q5 always, others never
     assert rows[:4] == [[256, 256, 384, 1, 0], [128, 128, 192, 1, 0], [64, 64, 96, 1, 0], [32, 32, 48, 1, 0]]
-    assert rows[4] == [256, 1]
+    assert rows[4] == [256, 1, 1, 0, 1, 1, 0, 1]
