@@ -322,14 +322,17 @@ constexpr int stepk_waves_per_eu() {
 // cavity: the FP32 D2Q5 forms keep their registers (50 and 57) and gain
 // 5% (three steps) and 3-4% (two steps) from the schedule the bound
 // selects; FP32 D2Q9 (three workgroups per CU by LDS) goes without, with
-// 32 x 10 tiles; the 16-bit and D2Q9 FP32_H64 forms fit the bound only by spilling
-// and lose 5-24%.
+// 32 x 10 tiles; D2Q9 FP32_H64 fits the bound only by spilling and loses.  The
+// split forms need it for their third workgroup per CU (80 vector registers; at
+// 81 F16_SPLIT falls from 53.8 to 45.9 GLUPS at 4096^2), but for no more than six
+// waves: the 64 x 6 tile would spill at seven.
 #ifndef LBM_WPE_MASK
-#define LBM_WPE_MASK ((1 << ST5_F32) | (1 << ST5_F32H))
+#define LBM_WPE_MASK ((1 << ST5_F32) | (1 << ST5_F32H) | (1 << ST_F16S) | (1 << ST_BF16S))
 #endif
 template <int ST, class Lay, typename R, int TW, int TH, int NT, int K>
 constexpr int stepk_wpe() {
-    return ((LBM_WPE_MASK >> ST) & 1) ? stepk_waves_per_eu<Lay, R, TW, TH, NT, K>() : 1;
+    constexpr int w = stepk_waves_per_eu<Lay, R, TW, TH, NT, K>();
+    return !((LBM_WPE_MASK >> ST) & 1) ? 1 : (IsSplitLayout<Lay>::value && w > 6 ? 6 : w);
 }
 
 // The tile that starts about when tile b's workgroup ends: `ahead` tiles on

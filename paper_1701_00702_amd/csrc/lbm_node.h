@@ -166,11 +166,10 @@ LBM_HD void reside(N &n) {
     } else {
         resident<V>(n.mB3), resident<V>(n.w4);
     }
-    if constexpr (Lay::SCALED)
-        for (int f = 0; f < 3; ++f) resident<V>(n.scale[f]), resident<V>(n.inv_scale[f]);
+    static_assert(!Lay::SCALED, "the 16-bit forms read theirs from memory");
 }
 
-// The constants of the node update for the step kernels.  With FP32
+// The constants of the node update for the multi-step kernels.  With FP32
 // arithmetic they are loaded once per workgroup and stay in scalar
 // registers; loaded at each use, every update waited on chains of scalar
 // loads (they return out of order, so each wait is for all of them and for
@@ -178,16 +177,25 @@ LBM_HD void reside(N &n) {
 // scalar branch past the wall code this took the three-step FP32_H64 kernel
 // (8192^2) from 1125 VALU, 558 scalar and 98 scalar-load instructions per
 // wave to 961, 302 and 24.  FP64 constants would take twice the registers
-// there are (700 spills to vector lanes, 13% slower) and stay in memory.
+// there are (700 spills to vector lanes, 13% slower) and stay in memory.  So do
+// those of the 16-bit forms, whose scales and codecs fill what is left (27 to
+// 42 spills; GLUPS at 4096^2 with them in registers and in memory: F16 57.9 and
+// 64.3, BF16_SPLIT 50.7 and 54.7, F16_SPLIT 49.4 and 53.8, the latter two in the
+// vector registers of three workgroups per CU).
 template <class Lay, typename RH>
 LBM_HD const NodeConst<double, RH> &node_const(const CavityConst<double> &c) {
     return node_const_of<RH>(c);
 }
 template <class Lay, typename RH>
-LBM_HD NodeConst<float, RH> node_const(const CavityConst<float> &c) {
-    NodeConst<float, RH> n = node_const_of<RH>(c);
-    reside<Lay, false>(n);
-    return n;
+LBM_HD typename std::conditional<Lay::SCALED, const NodeConst<float, RH> &, NodeConst<float, RH>>::type node_const(
+    const CavityConst<float> &c) {
+    if constexpr (Lay::SCALED) {
+        return node_const_of<RH>(c);
+    } else {
+        NodeConst<float, RH> n = node_const_of<RH>(c);
+        reside<Lay, false>(n);
+        return n;
+    }
 }
 
 // ---------------------------------------------------------------------------

@@ -56,3 +56,17 @@ def _of(kernels, pattern):
 def test_one_step_kernels_hold_their_scalars(kernels):
     for name, k in _of(kernels, r"step_kernel<.*, true, 1, false>").items():
         assert k["sgpr_spill_count"] == 0 and k["private_segment_fixed_size"] == 0, (name, k)
+
+
+def test_16_bit_kernels_hold_their_scalars(kernels):
+    # scaled and split storage, both steps per launch, every tile shape
+    for form in (r"Plain<E16, true, 9>", r"Plain<EB16, true, 9>", r"SplitT<E16>", r"SplitT<EB16>"):
+        for name, k in _of(kernels, rf"stepk_kernel<{form}, .*, false, \d>").items():
+            assert k["sgpr_spill_count"] == k["vgpr_spill_count"] == k["private_segment_fixed_size"] == 0, (name, k)
+            if form.startswith("Split"):    # three workgroups of eight waves per CU
+                assert k["vgpr_count"] <= 80, (name, k)
+
+
+def test_default_kernels_use_no_scratch(kernels):
+    for name, k in _of(kernels, r"(deep_kernel<.*>|stepk_kernel<.*, false, \d>)").items():
+        assert k["vgpr_spill_count"] == k["private_segment_fixed_size"] == 0, (name, k)
