@@ -2003,6 +2003,74 @@ LBM_HD void stepk_last(const TileView<R> &tv, const NodeConst<R, RH> &n, void *d
     *(R *)((char *)(sr_dst + tv.flat_row) + (uint32_t)((y - tv.yb) * tv.v.nx + x) * (uint32_t)sizeof(R)) = (R)srf;
 }
 
+// Brings the rows a tile will be the first to read into the XCD's L2: item q
+// of NP planes of elements of ES bytes from byte `plane0` on (stride nodes
+// apart), TH rows each, one load per 128-byte line.  v receives the loads.
+template <int ES, int NP, int TW, int TH, int NT, int N>
+LBM_HD void touch_lines(Blocks b, const BandOrigin &org, uint32_t stride, uint32_t plane0, int x0, int x1, int y0, int y1,
+                        int t, uint32_t (&v)[N]) {
+    constexpr int EL = 128 / ES, LINES = (TW + EL - 1) / EL;  // elements per line, lines per row
+    static_assert(N * NT >= NP * TH * LINES, "one load per item");
+#pragma unroll
+    for (int k = 0; k < N; ++k) {
+        const int q = t + k * NT, line = q % LINES, row = (q / LINES) % TH, p = q / (LINES * TH);
+        const int x = x0 + line * EL, y = y0 + row;
+        v[k] = 0;
+        if (p < NP && x < x1 && y < y1) {
+            const NodeRef r = org(x, y);
+            v[k] = ld_block<uint32_t>(b, plane0, ((p * stride + r.rel) * ES + r.jump) & ~3u, 0);
+        }
+    }
+}
+template <int N>
+LBM_HD void wait_lines(uint32_t (&v)[N]) {
+#if defined(__HIP_DEVICE_COMPILE__)
+#pragma unroll
+    for (int k = 0; k < N; ++k) asm volatile("" : : "v"(v[k]));
+#else
+    (void)v;
+#endif
+}
+// What a tile will be the first to read of its state: its columns of the
+// rows from K below its own first (the tile before it in its column has read
+// those up to there) to K beyond its last.  Run by threads t of NT that have
+// no node in the last update: without it the first update's pulls come from
+// HBM and hold the workgroup for about a quarter of its life with little to
+// overlap (the waves of a tile load together, three tiles share a CU).
+// Measured with the strip order of the tiles (cavity_tiles2), 8192^2, three
+// steps per launch: FP32_H64 46.5 -> 51.3 GLUPS, FP32 48.1 -> 52.8, D2Q5 FP32
+// 72.0 -> 75.0, F16_SPLIT (4096^2) 44.4 -> 49.0.
+template <class Lay, typename R, int TW, int TH, int K, int NT>
+LBM_HD void stepk_prefetch(const CavityConst<R> &c, const Tile2 &tl, const void *src, int t) {
+    const int y0 = tl.y0 ? tl.y0 + K : 0, end = tl.y0 + tl.h + K, y1 = end < c.ny ? end : c.ny;
+    if (y0 >= y1) return;
+    const int ba = band_of(c, y0);
+    const BandOrigin org = band_origin(c, ba);
+    const Blocks b = blocks_at(src, c.pop_off + (int64_t)ba * c.band_bytes);
+    const uint32_t stride = (uint32_t)c.band_nodes;
+    const int x1 = tl.x0 + tl.w;
+    constexpr int TR = TH + K;  // rows of a first tile
+    auto n = [](int es, int planes) { return (planes * TR * ((TW * es + 127) / 128) + NT - 1) / NT; };
+    if constexpr (IsSplitLayout<Lay>::value) {
+        uint32_t v[n(4, 6)], w[n(2, 24)];
+        touch_lines<4, 6, TW, TR, NT>(b, org, stride, 0, tl.x0, x1, y0, y1, t, v);
+        touch_lines<2, 24, TW, TR, NT>(b, org, stride, 24 * stride, tl.x0, x1, y0, y1, t, w);
+        wait_lines(v);
+        wait_lines(w);
+    } else if constexpr (std::is_same<Lay, PlainH64<Lay::QT>>::value) {
+        uint32_t v[n(4, 8 + 2 * Lay::QT)], w[n(8, 1)];
+        touch_lines<4, 8 + 2 * Lay::QT, TW, TR, NT>(b, org, stride, 0, tl.x0, x1, y0, y1, t, v);
+        touch_lines<8, 1, TW, TR, NT>(b, org, stride, (8 + 2 * Lay::QT) * 4 * stride, tl.x0, x1, y0, y1, t, w);
+        wait_lines(v);
+        wait_lines(w);
+    } else {
+        constexpr int es = (int)sizeof(typename Lay::T), np = 9 + 2 * Lay::QT;
+        uint32_t v[n(es, np)];
+        touch_lines<es, np, TW, TR, NT>(b, org, stride, 0, tl.x0, x1, y0, y1, t, v);
+        wait_lines(v);
+    }
+}
+
 // The same from the cavity's table and a tile (host builds).
 template <class Lay, typename R, int TW, int TH, int K, int NT>
 LBM_HD void stepk_stage_bases(const CavityConst<R> &c, const Tile2 &tl, const void *src, float *lds_b, int t) {
