@@ -1054,7 +1054,6 @@ struct NodeGeom {
     LBM_HD bool wall() const { return kind & NODE_WALL; }
     LBM_HD bool near_x() const { return kind & NODE_NEAR_X; }
     LBM_HD bool near_y() const { return kind & NODE_NEAR_Y; }
-    LBM_HD bool near_wall() const { return kind & (NODE_NEAR_X | NODE_NEAR_Y); }
 };
 
 template <typename R>
@@ -1101,9 +1100,6 @@ struct BandOrigin {
         return y < y_next ? NodeRef{(uint32_t)((y - y_first) * pitch + x), 0u}
                           : NodeRef{(uint32_t)((y - y_next) * pitch + x), band_bytes};
     }
-    // row y resolved to its band once; node x of it by at_row
-    LBM_HD NodeRef row(int y) const { return (*this)(0, y); }
-    LBM_HD static NodeRef at_row(NodeRef r, int x) { return NodeRef{r.rel + (uint32_t)x, r.jump}; }
 };
 struct AnyBand {
     int band_rows, pitch;
@@ -1112,8 +1108,6 @@ struct AnyBand {
         const int b = y / band_rows;
         return FarRef{(int64_t)(y - b * band_rows) * pitch + x, (int64_t)b * band_bytes};
     }
-    LBM_HD FarRef row(int y) const { return (*this)(0, y); }
-    LBM_HD static FarRef at_row(FarRef r, int x) { return FarRef{r.rel + x, r.jump}; }
 };
 // Band of row y: a multiplication by the rounded-up reciprocal 2^32 /
 // band_rows, one too large at most.
@@ -2168,7 +2162,7 @@ LBM_HD void deep_load(const TileView<R> &tv, const NodeConst<R, RH> &n, const vo
     const CavityConst<R> &c = tv.c;
     const Tile2 &tl = tv.tl;
     const int lx = mod_by<Sh::PW>(t), ly = div_by<Sh::PW>(t);
-    const int x = tl.x0 - Sh::RING + lx, y = tl.y0 - Sh::RING + ly;  // unwrapped
+    const int x = tl.x0 - Sh::RING + lx, y = tl.y0 - Sh::RING + ly;
     const int ox = lx < Sh::RING ? Sh::RING - lx : lx - Sh::RING - tl.w + 1;
     const int oy = ly < Sh::RING ? Sh::RING - ly : ly - Sh::RING - tl.h + 1;
     q.depth = ox > oy ? (ox > 0 ? ox : 0) : (oy > 0 ? oy : 0);
@@ -2177,8 +2171,7 @@ LBM_HD void deep_load(const TileView<R> &tv, const NodeConst<R, RH> &n, const vo
     q.g = NodeGeom{0, x, y};
     q.from = t;
     if (tv.edge) {
-        if (c.periodic) q.x = x < 0 ? x + c.nx : (x >= c.nx ? x - c.nx : x);
-        if (q.x < 0 || q.x >= c.nx || y < 0 || y >= c.ny) {
+        if (x < 0 || x >= c.nx || y < 0 || y >= c.ny) {  // periodic problems take no deep launches
             q.depth = INT32_MAX;
         } else {
             q.g = geometry(c, q.x, y, true);
