@@ -235,8 +235,12 @@ typedef struct lbm_launch_config {
  * Eq. 26, Eq. A19, Sec. III C rates), validates them (rates in (0,2),
  * interstitial exchange number < 1, Remark I bounds, phi in (0,1)), allocates
  * the double-buffered state with hipMalloc and initialises every node at rest
- * at T_init (isothermal walls at their temperature).  *out receives the
- * handle, or NULL on failure. */
+ * at T_init (isothermal walls at their temperature).  Every handle also takes
+ * 256 bytes of pinned host memory for the diagnostics' results, and some for
+ * read-backs (see lbm_fields: up to 0.75 MiB at creation if all its cavities
+ * are small, so a thousand such handles pin up to 750 MiB), held until
+ * lbm_destroy; without any to be had it works through the runtime's copies.
+ * *out receives the handle, or NULL on failure. */
 lbm_status lbm_create(const lbm_params *p, lbm_precision prec, lbm_handle **out);
 
 /* Create a solver advancing n_cavities independent cavities (p[0..n-1]) in

@@ -763,8 +763,9 @@ lbm_status setup(lbm_handle *h) {
         HIP_TRY(hipMemcpyAsync(h->cav(), t.data(), t.size() * sizeof(t[0]), hipMemcpyHostToDevice, h->stream));
         HIP_TRY(hipStreamSynchronize(h->stream));
     }
-    // By default the most steps per launch that can be asked for (measured
-    // faster for every cavity size and batch, the rows being padded to 64 nodes).
+    // By default the most steps per launch that can be asked for, which is the
+    // fastest of those at every size measured, unless the handle has launches of
+    // its own (deep ones, three FP64 steps), which are faster still.
     h->lc.steps_per_launch = has_k(h->pl, 3) ? 3 : 2;
     h->own_lc = h->lc;
     lbm_status s = build_tiles(h, h->lc);

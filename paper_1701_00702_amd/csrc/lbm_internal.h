@@ -58,8 +58,8 @@ struct MomentType<float, double> {
 // The constants every node update reads, one of each distinct value (Sec.
 // III C relaxes moments 1 and 2, 3 and 5, 4 and 6, 7 and 8 in pairs, each
 // pair with one norm), products of constants formed once on the host with
-// the rounding the update would give them.  The FP32 step kernels load them
-// into scalar registers once per workgroup (node_const).
+// the rounding the update would give them.  The FP32 multi-step kernels load
+// them into scalar registers once per workgroup (node_const).
 template <typename R, typename RH>
 struct NodeConst {
     using RG = typename MomentType<R, RH>::T;

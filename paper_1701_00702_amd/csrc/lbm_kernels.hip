@@ -190,9 +190,10 @@ hipError_t launch_step(const StepLaunch &L, hipStream_t s) {
 // first update covers the tile and its (K-1)-node ring into LDS, a middle
 // update (K = 3) the tile and a one-node ring in place in LDS, the last
 // update the tile into the destination buffer, with barriers between.  Tile
-// shapes fill at most 64 KiB of LDS; the defaults (measured) let three or
-// four workgroups share a CU, whose waves overlap one tile's loads with
-// another's arithmetic.  Two-step tiles first.
+// shapes fill at most 64 KiB of LDS (three FP64 steps: 66 and 77 KiB); the
+// defaults (measured) let three or four workgroups share a CU (three FP64
+// steps: two), whose waves overlap one tile's loads with another's arithmetic.
+// Two-step tiles first.
 // ---------------------------------------------------------------------------
 // One tile per workgroup, or (LOOP) a grid-stride walk over the tiles for
 // the persistent launch.  Without the loop nothing in the tile's code is
@@ -436,7 +437,8 @@ hipError_t launch_stepk(const Step2Launch &L, hipStream_t s) {
 // Bound by the latency of one wave's chain of instructions: at 64^2 (FP32_H64,
 // 8x8 tiles) an update takes 1720 cycles of a wave, 3400 where it holds wall
 // nodes, and 1000 to 1300 for the exchange through LDS.  The constants stay
-// in vector registers, which one workgroup per CU leaves plenty of.
+// in vector registers, which one workgroup per CU leaves enough of (up to 163
+// of the 168 that nine waves of FP32_H64 leave each, 255 with FP64, no scratch).
 // ---------------------------------------------------------------------------
 template <class Lay, typename R, typename RH, int TW, int TH, int K>
 __global__ __launch_bounds__((DeepShape<Lay, TW, TH, K>::NT)) void deep_kernel(

@@ -1661,9 +1661,9 @@ struct StepKShape {
         return LDS_BYTES + NSLOT * sizeof(R) + BASE_BYTES + (tally ? 32 * (TW + TH) : 0);
     }
     static constexpr int NT = (NFIRST + 63) / 64 * 64;
-    // LDS is given out in units of at most 128 bytes: the two-step FP64 D2Q5 tile
-    // (54400 bytes) fits three times, with tallies in LDS only twice (4096^2: 29.9
-    // GLUPS with its tallies in memory, 22.1 with two per CU).
+    // Rounded to 128 bytes: the two-step FP64 D2Q5 tile (54400 bytes) fits a CU
+    // three times, which rounding to 512 would deny, and with tallies in LDS
+    // twice (4096^2: 29.9 GLUPS with its tallies in memory, 22.1 with them in LDS).
     static constexpr int per_cu(bool tally) {
         const int a = (int)(160 * 1024 / ((total_lds(tally) + 127) / 128 * 128)), b = 32 / (NT / 64);
         return a < b ? a : b;
@@ -2033,7 +2033,8 @@ LBM_HD void wait_lines(uint32_t (&v)[N]) {
 // overlap (the waves of a tile load together, three tiles share a CU).
 // Measured with the strip order of the tiles (cavity_tiles2), 8192^2, three
 // steps per launch: FP32_H64 46.5 -> 51.3 GLUPS, FP32 48.1 -> 52.8, D2Q5 FP32
-// 72.0 -> 75.0, F16_SPLIT (4096^2) 44.4 -> 49.0.
+// 72.0 -> 75.0, F16_SPLIT (4096^2) 44.4 -> 49.0 (53.9 since, with its constants
+// in memory).
 template <class Lay, typename R, int TW, int TH, int K, int NT>
 LBM_HD void stepk_prefetch(const CavityConst<R> &c, const Tile2 &tl, const void *src, int t) {
     const int y0 = tl.y0 ? tl.y0 + K : 0, end = tl.y0 + tl.h + K, y1 = end < c.ny ? end : c.ny;

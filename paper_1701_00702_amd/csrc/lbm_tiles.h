@@ -240,8 +240,11 @@ constexpr TileDims dims_of(int i) {
 // 12x12x6 4.46 -> 3.26, 200^2 16x12x6 4.5 -> 3.69, 256^2 16x16x5 4.45 -> 3.77
 // (x6 3.87, x4 4.21); FP64 64^2 8x8x5 5.86 -> 3.44 (x6 3.87, x4 3.83), 151^2
 // 16x8x4 5.41 -> 4.26 (x5 4.60), 200^2 16x12x4 6.18 -> 5.37, 256^2 16x16x4 7.17
-// -> 5.70; D2Q5 FP32 64^2 3.93 -> 2.13, 256^2 3.80 -> 2.82.  With two tiles on a
-// CU they lose (FP32_H64 300^2 16x16: 6.0 -> 7.7).
+// -> 5.70; D2Q5 FP32 64^2 3.93 -> 2.13, 256^2 3.80 -> 2.82.  Batches and thin
+// cavities of up to 256 tiles gain alike (156 handles of all six forms, 1.06 to
+// 2.85 times: FP64 16 of 64^2 6.81 -> 5.93, 256 of 8^2 7.62 -> 3.18, 4x2048 10.1 ->
+// 3.54; D2Q5 16 of 64^2 5.18 -> 4.87).  With two tiles on a CU they lose (FP32_H64
+// 300^2 16x16: 6.0 -> 7.7).
 constexpr int kDeepShapes = 4;
 constexpr int kDeepTiles = kCus;  // reserved for by the plan
 constexpr bool deep_fits(int64_t tiles, int n_cu) { return tiles <= n_cu; }  // what a handle then runs
