@@ -91,8 +91,8 @@ __device__ __forceinline__ void step_tile(const void *__restrict__ src, void *__
     const CavityConst<R> &c = cav[tl.cav];
     // Constants from memory at each use: a launch is bound by HBM, and held in
     // scalar registers with the tile's they do not fit (30 to 50 of them went
-    // through vector lanes: 504.4 VALU instructions a node-step for 468.7 in
-    // FP32_H64, and small launches were slower, us: 300x260 F16_SPLIT 8.4 for 7.8,
+    // through vector lanes: 504.4 VALU instructions a node-step for 404.4 in
+    // FP32_H64, and small launches were slower, us: 300x260 F16_SPLIT 8.4 for 7.9,
     // F16 7.9 for 7.1; 500x700 F16 13.0 for 12.2).
     const NodeConst<R, RH> &n = node_const_of<RH>(c);
     const bool wall = tl.kind != TILE_INTERIOR;

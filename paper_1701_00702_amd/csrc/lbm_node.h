@@ -2172,7 +2172,8 @@ LBM_HD void deep_load(const TileView<R> &tv, const NodeConst<R, RH> &n, const vo
     q.g = NodeGeom{0, x, y};
     q.from = t;
     if (tv.edge) {
-        if (x < 0 || x >= c.nx || y < 0 || y >= c.ny) {  // periodic problems take no deep launches
+        // (periodic problems take no deep launches)
+        if ((unsigned)x >= (unsigned)c.nx || (unsigned)y >= (unsigned)c.ny) {
             q.depth = INT32_MAX;
         } else {
             q.g = geometry(c, q.x, y, true);
