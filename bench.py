@@ -45,8 +45,8 @@ FP32_FORM = "f32h64"
 # Algorithmic VALU instructions per node update of the timed forms: the fewest
 # that a one-step kernel (no multi-step ring) of this library has issued,
 # counted with rocprofv3 (SQ_INSTS_VALU x 64 / node updates) on the 8192^2
-# cavity; the present one-step kernels issue 442.5 and 504.4.
-ALG_VALU_PER_NODE_STEP = {"f32": 436.3, "f32h64": 468.7}
+# cavity: those of the present ones.
+ALG_VALU_PER_NODE_STEP = {"f32": 390.5, "f32h64": 404.4}
 # The paper's own timings (Table I, present scheme, quad-core 2.33 GHz CPU;
 # precision and thread count not stated): context only.
 PAPER_TABLE_I = [
