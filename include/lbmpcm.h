@@ -205,8 +205,8 @@ typedef struct lbm_diag {
  * launches are the library's own and can't be asked for: lbm_get_launch reports
  * the shape a caller may set, lbm_launch_steps what runs.  lbm_set_launch, also
  * with the values lbm_get_launch reports, leaves the own launches for the shape
- * it names; lbm_autotune times both and keeps the faster, so it may bring them
- * back. */
+ * it names; lbm_reset_launch brings them back, and lbm_autotune, which times
+ * both and keeps the faster, may. */
 typedef struct lbm_launch_config {
     int32_t block;            /* threads per workgroup: 64, 128, 256 or 512      */
     int32_t nodes_per_thread; /* 1, 2 or 4 consecutive-by-block nodes per thread */
@@ -364,6 +364,11 @@ lbm_status lbm_set_launch(lbm_handle *h, const lbm_launch_config *cfg);
  * *tile_h (0 with one step per launch; either pointer may be NULL); -1 on a NULL
  * handle. */
 int32_t lbm_launch_steps(const lbm_handle *h, int32_t *tile_w, int32_t *tile_h);
+
+/* Forget any shape set or tuned: the launches of a new handle again.  Returns
+ * the steps per launch that run then, or -1 (lbm_last_error says why).
+ * Synchronises the stream. */
+int32_t lbm_reset_launch(lbm_handle *h);
 
 /* Time every supported launch shape (one-step launch shapes; two and three
  * steps per launch in every tile shape) for steps_per_trial launches on

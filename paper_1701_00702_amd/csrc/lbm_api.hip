@@ -1272,6 +1272,15 @@ extern "C" lbm_status lbm_set_launch(lbm_handle *h, const lbm_launch_config *cfg
     return apply_shape(h, *cfg, false);
 }
 
+extern "C" int32_t lbm_reset_launch(lbm_handle *h) {
+    if (!h) {
+        (void)fail(LBM_EINVAL, "handle is NULL");
+        return -1;
+    }
+    if (apply_shape(h, h->own_lc, true) != LBM_OK) return -1;
+    return lbm_launch_steps(h, nullptr, nullptr);
+}
+
 namespace {
 std::string tune_key(lbm_handle *h) {
     hipDeviceProp_t prop;

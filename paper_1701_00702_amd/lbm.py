@@ -118,6 +118,7 @@ def _load():
         "lbm_get_launch": ([H, ctypes.POINTER(lbm_launch_config)], st),
         "lbm_set_launch": ([H, ctypes.POINTER(lbm_launch_config)], st),
         "lbm_launch_steps": ([H, ctypes.POINTER(ctypes.c_int32), ctypes.POINTER(ctypes.c_int32)], ctypes.c_int32),
+        "lbm_reset_launch": ([H], ctypes.c_int32),
         "lbm_autotune": ([H, ctypes.c_int32, ctypes.c_char_p, ctypes.POINTER(lbm_launch_config)], st),
         "lbm_save": ([H, ctypes.c_char_p], st),
         "lbm_load": ([H, ctypes.c_char_p], st),
@@ -312,6 +313,14 @@ def lbm_launch_steps(h: int) -> tuple:
     """(steps per launch that lbm_step runs now, tile_w, tile_h)"""
     w, t = ctypes.c_int32(0), ctypes.c_int32(0)
     return int(_lib.lbm_launch_steps(h, ctypes.byref(w), ctypes.byref(t))), w.value, t.value
+
+
+def lbm_reset_launch(h: int) -> int:
+    """The library's own launches again; the steps per launch that run then."""
+    n = int(_lib.lbm_reset_launch(h))
+    if n < 0:
+        raise LbmError(LBM_EINVAL, lbm_last_error())
+    return n
 
 
 def lbm_autotune(h: int, steps_per_trial: int = 5, cache_path: str | None = None) -> dict:

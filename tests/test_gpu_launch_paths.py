@@ -74,7 +74,14 @@ def test_launches_by_size(lbm, i):
         lbm.lbm_set_launch(s.h, 512, 1, 1, 0, steps_per_launch=spl, tile_shape=0)
         lc = lbm.lbm_get_launch(s.h)
         assert lbm.lbm_launch_steps(s.h) == (spl, lc["tile_w"], lc["tile_h"])
+    # and the way back, bit for bit like a handle that never left
+    assert lbm.lbm_reset_launch(s.h) == got[0] and lbm.lbm_launch_steps(s.h) == got
+    t = lbm.Solver(ps if len(ps) > 1 else ps[0], prec)
+    assert lbm.lbm_get_launch(s.h) == lbm.lbm_get_launch(t.h)
+    s.step(23), t.step(23)
+    assert np.array_equal(s.state(), t.state())
     s.close()
+    t.close()
 
 
 def test_autotuned_launches_are_reported(lbm, tmp_path):
